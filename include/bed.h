@@ -70,11 +70,13 @@ typedef enum {
 
 /* Launch schedule of a plan.  Zero fields mean "autotuned / default".
  *   threads_big   threads per matrix for the n > 32 size class (64, 128,
- *                 256 or 512; default 512: four waves reduce to tridiagonal
- *                 form while four form the Householder product, which 256 and
- *                 fewer apply in compact-WY form instead)
+ *                 256 or 512; default 256: two waves hold the matrix during
+ *                 the Householder reduction, one forms the reflectors, one
+ *                 the Householder product; 64 and 128 reduce on one wave and
+ *                 apply the product in compact-WY form)
  *   threads_mid   threads per matrix for 16 < n <= 32 (64, 128 or 256; default
- *                 256: one wave reduces, two form Q_H, all four merge)
+ *                 256: one wave holds the matrix, one forms the reflectors,
+ *                 two the Householder product, all four merge)
  *   waves_per_cu  resident teams per compute unit for the persistent launch
  *   order         0: largest n first (LPT), 1: input order
  *   persistent    1: one persistent launch pulls matrices from a device work
@@ -135,8 +137,8 @@ bed_status bed_syevd_noalloc(bed_dtype dt, int64_t batch, const int32_t *n, cons
  * Sec. 2.3.5): Q is not produced.  The merges carry only the first and last
  * row of each node's eigenvector block -- all that the next z (Eq. (5))
  * reads -- instead of the block product, and there is no back-transform.
- * The Householder reduction runs in the data's own precision (bed_syevd uses
- * binary64 arithmetic for binary32 data): an eigenvalue moves by at most the
+ * For n <= 64 the reduction is bed_syevd's (binary64 arithmetic); for 64 < n it
+ * runs in the data's own precision: an eigenvalue moves by at most the
  * reduction's backward error, with no eigenvalue-gap factor, so the results
  * keep bed_syevd's eigenvalue bound but are not bitwise equal to its lambda. */
 bed_status bed_syevals(bed_dtype dt, int64_t batch, const int32_t *n, const void *A,

@@ -27,10 +27,10 @@ extern "C" {
  *                     done, 5 stored;
  *   steps[b*16 + id]  shader-clock cycles at sub-step id of the middle
  *                     Householder step (k = 32 for n > 32, 16 for 16 < n <= 32,
- *                     8 below) in wave 0: 0 start, 1 dot product, 2 partial
- *                     exchange and barrier, 3 reduction p^T v, 4 w broadcast,
- *                     5 reduction of the pivot column norm, 6 reflector,
- *                     7 v broadcast writes, 8 rank-2 update, 9 a
+ *                     8 below) in wave 0: 0 start, 1 update of the step before
+ *                     and product A x, 2 reductions (and, in a team of four or
+ *                     more waves, the exchange and barrier), 3 w and the next
+ *                     pivot column, 8 end, 9 a
  *                     second stamp right after 8 (the cost of one marker,
  *                     which waits for outstanding LDS and scalar operations).
  *   defl[b*2 + t]     (may be NULL) deflations of team b summed over its merge

@@ -20,7 +20,7 @@ PROBE_LIB = os.path.join(LIB_DIR, "libbed_probe.so")
 ARCH = os.environ.get("BED_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["bed_kernels.hip", "bed_backward.hip", "bed_api.cpp", "bed_backward_api.cpp",
+SOURCES = ["bed_kernels.hip", "bed_kernels_f64.hip", "bed_backward.hip", "bed_api.cpp", "bed_backward_api.cpp",
            "bed_tune.cpp", "bed_server.cpp", "bed_noalloc.hip", "bed_spectral.hip", "bed_big.hip"]
 PROBE_SOURCES = ["bed_probe.hip"]
 

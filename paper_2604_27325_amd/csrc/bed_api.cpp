@@ -91,7 +91,7 @@ TeamShape class_shape(int cls, const bed_tune &t)
     case 0: return TeamShape{16, 64, t.leaf > 0 ? t.leaf : leaf_default(16)};
     case 1: return TeamShape{32, t.threads_mid > 0 ? t.threads_mid : 128,
                              t.leaf > 0 ? t.leaf : leaf_default(32)};
-    default: return TeamShape{64, t.threads_big > 0 ? t.threads_big : 512,
+    default: return TeamShape{64, t.threads_big > 0 ? t.threads_big : 256,
                               t.leaf > 0 ? t.leaf : leaf_default(64)};
     }
 }
@@ -99,7 +99,7 @@ TeamShape class_shape(int cls, const bed_tune &t)
 bed_tune default_tune()
 {
     bed_tune t;
-    t.threads_big = 512;
+    t.threads_big = 256;
     t.threads_mid = 256;
     t.waves_per_cu = 0;
     t.order = 0;

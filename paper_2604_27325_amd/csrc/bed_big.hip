@@ -85,6 +85,33 @@ struct RedSmem {
     int expw[BT / 64];
 };
 
+// Reflector of a pivot column (Golub-Van Loan 8.3): alpha = -sgn(x_0) mu, mu =
+// ||x||, v = (1, x_2.. rv0) with rv0 = sgn(x_0) / (|x_0| + mu), tau = (mu +
+// |x_0|) / mu = 2 / (v^T v); tau = 0 when the sub-column is already zero.
+template <typename H> struct Refl {
+    H alpha, tau, rv0;
+};
+template <typename H> __device__ __forceinline__ Refl<H> reflector(const H x0, const H sig)
+{
+    constexpr bool est = sizeof(H) == 8;  // hardware estimate, one Newton step
+    const bool z = (sig == H(0));
+    const H s2 = fma(x0, x0, sig);
+    H rmu;
+    if constexpr (est) rmu = d_rsqrt_nr(s2);
+    else rmu = f_rsqrt(s2);
+    const H mu = s2 * rmu;
+    const H ax = f_abs(x0);
+    const H sg = (x0 < H(0)) ? H(-1) : H(1);
+    H rs;
+    if constexpr (est) rs = d_rcp_nr(ax + mu);
+    else rs = f_rcp(ax + mu);
+    Refl<H> h;
+    h.alpha = z ? x0 : -sg * mu;
+    h.rv0 = z ? H(1) : sg * rs;
+    h.tau = z ? H(0) : fma(ax, rmu, H(1));
+    return h;
+}
+
 // Arithmetic type H: binary64 when Q_H is formed (eigenvectors), binary32
 // for eigenvalues alone (as for n <= 64).  Lane (r, g) = (t % 128, t / 128)
 // keeps row r of the columns c = g + 4j (j < 32) in registers; the four column groups are whole waves, so
@@ -188,7 +215,7 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
         __syncthreads();
         const H x0 = S.u.s.red[2];
         const H sig = S.u.s.red[0] + S.u.s.red[1];
-        const HhRefl<H> h = hh_reflector<float>(x0, sig);
+        const Refl<H> h = reflector<H>(x0, sig);
         // v = (1, x_{k+2..} rv0) = x' rv0 + e_{k+1} with x' the pivot column
         // zeroed at rows <= k + 1 (exact: the products are as before, and the
         // pivot entry is exactly 1 without a per-column select); x is zero

@@ -54,7 +54,7 @@ __device__ long long *g_defl;
 namespace bed {
 
 template <typename T, int NMAX, int NT>
-__global__ void __launch_bounds__(NT)
+__global__ void __launch_bounds__(NT) BED_OCC(NMAX, NT)
 k_probe_uniform(const T *__restrict__ A, int n, int64_t batch, T *__restrict__ lam,
                 T *__restrict__ Q)
 {

@@ -12,8 +12,8 @@
 //   eigenvectors the merges carry only the end rows of each node's block.
 //
 // Team geometry (NT threads, thread t):
-//   Householder: HW reducing waves, lane (r, g) holding row r of the columns
-//     g + G j (G = HW 64 / NMAX groups); the other waves form Q_H.
+//   Householder: wave 0 reduces, lane (i, j) of an 8 x 8 grid holding the
+//     entries (i + 8a, j + 8b); other waves form Q_H.
 //   Per-element phases: wave 0, lane e = element e (n <= 64 fits one wave).
 //   Per-root phases: root q = t / LPR, LPR = NT / NMAX lanes share one root's
 //     pole sums (aligned lane groups, butterfly reductions).
@@ -52,41 +52,60 @@
 
 namespace bed {
 
-// Waves that run the Householder reduction of a team: the row block of a
-// wave (NMAX^2/(64 HW) registers per lane) must fit the register budget.
-// n <= 32 reduces on one wave at every team size (a second one costs its
-// cross-wave exchange in every step; larger teams still widen the merges).
-#ifndef BED_HH_WAVES
-#define BED_HH_WAVES(T, NMAX, NT) ((NMAX) == 64 ? ((NT) / 64 < 4 ? (NT) / 64 : 4) : 1)
-#endif
-template <typename T, int NMAX, int NT> struct HH_WAVES {
-    static constexpr int value = BED_HH_WAVES(T, NMAX, NT);
+// Waves per SIMD that the resident teams of a shape need (four SIMDs per CU);
+// register allocation is capped accordingly.  n > 32: the reducing wave keeps
+// 64 binary64 entries and its operands per lane (over 200 registers), which
+// leaves two waves per SIMD: two teams of 256 threads per CU, one of 512.
+template <int NMAX, int NT> struct Occ {
+    static constexpr int teams_per_cu = NMAX >= 64 ? 2 : (NMAX >= 32 ? 4 : 8);
+    static constexpr int v = (teams_per_cu * NT / 64 + 3) / 4;
+    static constexpr int most = NMAX >= 64 ? 2 : 8;
+    static constexpr int wpe = v < 1 ? 1 : (v > most ? most : v);
 };
+#define BED_OCC(NMAX, NT) __attribute__((amdgpu_waves_per_eu(Occ<NMAX, NT>::wpe)))
 
-// Waves that form Q_H = H_0 H_1 ... H_{n-3} explicitly while the others reduce
-// (0: the back-transform applies the reflectors in compact-WY form instead).
-// Each holds NMAX/AW >= 16 rows of Q_H, at most 32 values per lane.
-template <typename T, int NMAX, int NT> struct QH_WAVES {
-    static constexpr int spare = NT / 64 - HH_WAVES<T, NMAX, NT>::value;
-    static constexpr int p = (spare >= 4 && NMAX >= 64) ? 4 : ((spare >= 2 && NMAX >= 32) ? 2 : (spare >= 1 ? 1 : 0));
-    static constexpr int value = (p > 0 && NMAX * NMAX / (64 * p) <= 32) ? p : 0;
+// Waves of a team during the Householder reduction.  Teams of four or more
+// waves: HW product waves hold the matrix, one control wave forms the norms
+// and reflectors beside them, AW waves accumulate Q_H; smaller teams reduce on
+// one wave (HW = 1, no control wave), a second one accumulating Q_H.
+template <typename T, int NMAX, int NT> struct HhWaves {
+    static constexpr int NW = NT / 64;
+    static constexpr bool team = NW >= 4;
+    static constexpr int HW = NW >= 8 ? 4 : ((NW >= 4 && NMAX >= 64) ? 2 : 1);
+    static constexpr int first_qh = team ? HW + 1 : 1;
 };
-// With a single reducing wave there is no barrier per step; the team meets
-// after every QH_SYNC steps so that the accumulating waves can follow.
+// Waves that form Q_H = H_0 H_1 ... H_{n-3} explicitly beside the reduction
+// (0: the back-transform applies the reflectors in compact-WY form instead).
+// Each holds NMAX/AW >= 16 rows of Q_H, at most 256 bytes of values per lane;
+// the product with Q_H that follows takes a wave per column tile.
+template <typename T, int NMAX, int NT> struct QH_WAVES {
+    static constexpr int spare = NT / 64 - HhWaves<T, NMAX, NT>::first_qh;
+    static constexpr int p = (spare >= 4 && NMAX >= 64) ? 4 : ((spare >= 2 && NMAX >= 32) ? 2 : (spare >= 1 ? 1 : 0));
+    static constexpr int value =
+        (p > 0 && NT / 64 >= NMAX / 16 && NMAX * NMAX / (64 * p) * int(sizeof(T)) <= 256) ? p : 0;
+};
+// A wave that reduces alone needs no barrier; its team meets after every
+// QH_SYNC steps so that the accumulating wave can follow.
 constexpr int QH_SYNC = 4;
 
 constexpr int SEC_CAP = 100;  // Halley-phase evaluations per root before "capped"
 
-// Arithmetic type of the Householder reduction when eigenvectors are formed.
-// Its rounding errors are a backward error of A, which the eigenvalue
-// differences and the eigenvectors of close pairs amplify by 1/gap (the
-// backward of the decomposition divides by those differences).  In binary64
-// -- whose FMA issues at the rate of unpacked binary32 on gfx950 -- they stay
-// far below binary32's unit roundoff; T, the reflectors and tau are then
-// rounded once to the storage type.  (The LDS buffers of the reduction are
-// sized for this type; a reduction in T uses them reinterpreted.)
-template <typename T> struct HhArith {
-    using type = double;
+// The Householder reduction runs in binary64 for both storage types.  Its
+// rounding errors are a backward error of A, which the eigenvalue differences
+// and the eigenvectors of close pairs amplify by 1/gap (the backward of the
+// decomposition divides by those differences).  In binary64 -- whose FMA
+// issues at the rate of unpacked binary32 on gfx950 -- they stay far below
+// binary32's unit roundoff; T, the reflectors and tau are then rounded once to
+// the storage type.
+//
+// Vectors in LDS are laid out for the reduction's 8 x 8 lane grid: position
+// i + 8a at i * HhLds<NMAX>::ST + a, so that a lane reads its NL = NMAX / 8
+// row (or column) values as 16-byte vectors; the stride keeps the eight groups
+// on distinct banks.
+template <int NMAX> struct HhLds {
+    static constexpr int NL = NMAX / 8;
+    static constexpr int ST = NL > 2 ? NL + 2 : 2;
+    static constexpr int SZ = 8 * ST;
 };
 
 // Per-element state of the merges of one depth; arrays indexed by global
@@ -128,14 +147,16 @@ struct Smem {
     alignas(16) T Vt[NMAX * VLD];
     T a[NMAX], b[NMAX], tau[NMAX];
     T lam0[NMAX], lam1[NMAX];
-    using H = typename HhArith<T>::type;
-    static constexpr int HW = HH_WAVES<T, NMAX, NT>::value;
     union {
-        struct {  // Householder (reducing waves only, in the reduction's type)
-            H part[2 * HW * NMAX];
-            H colb[2 * NMAX];
-            alignas(16) H vbuf[HW * NMAX];
-            alignas(16) H wbuf[HW * NMAX];
+        struct {  // Householder: pivot column x and -w (a copy per product wave);
+                  // by step parity: A x, the next pivot column A e, the waves'
+                  // parts of x^T A x, the reflector's scalars
+            alignas(16) double x[HhWaves<T, NMAX, NT>::HW][HhLds<NMAX>::SZ];
+            alignas(16) double w[HhWaves<T, NMAX, NT>::HW][HhLds<NMAX>::SZ];
+            alignas(16) double y[2][HhLds<NMAX>::SZ];
+            alignas(16) double c[2][HhLds<NMAX>::SZ];
+            alignas(16) double q[2][HhWaves<T, NMAX, NT>::HW < 2 ? 2 : HhWaves<T, NMAX, NT>::HW];
+            alignas(16) double sc[2][4];
         } h;
         MergeArrays<T, NMAX> m;
         struct {  // back-transform: per block of 16 reflectors, Gram matrix and T factor
@@ -790,172 +811,385 @@ __device__ __forceinline__ void backmul_rowtile(Smem<T, NMAX, NT>& S, const T* _
     }
 }
 
-// Householder tridiagonalization (Sec. 2; textbook, Golub-Van Loan 8.3) on HW
-// waves of the team.  Lane (r, g) keeps row r of the columns c = g + G j,
-// j < CPT, in registers, with G = HW * 64/NMAX column groups (64/NMAX groups
-// per wave, each holding all rows): a cyclic split, so every group shrinks at
-// the rate of the trailing matrix.  Within a wave p = A v is a per-lane dot
-// product plus a butterfly over its groups; across waves one barrier per step
-// exchanges the partial products together with the owner's pre-update pivot
-// column k+1 (a look-ahead of one column), after which every wave forms w, the
-// next pivot column and the next reflector on its own.  v and w reach a
-// wave's groups through its own LDS copies (group-major: column c at
-// (c % G) CPT + c / G), one 16-byte read per chunk of four columns.
+// Householder tridiagonalization (Sec. 2; textbook, Golub-Van Loan 8.3).  The
+// product waves hold the matrix in registers: lane (i, j) = (8 wave + lane / 8,
+// lane % 8) keeps the entries A(i + GI a, j + 8 b), GI = 8 HW, a < NA = NMAX /
+// GI, b < NB = NMAX / 8: a two-dimensional cyclic split, so that a lane needs
+// only NA row and NB column values of each vector, and chunks of finished rows
+// and columns drop out of the products altogether.  Every wave holds whole
+// rows: A x is complete after a reduction over the eight lanes of a group.
+// The matrix sits at the high end of the NMAX positions (position = index +
+// NMAX - n): the chunks that padding would fill are simply finished ones.
 //
-// Steps whose dead columns (c <= k, where v_c = 0) fill a wave's first Q0
-// chunks run in that wave's instance for Q0, whose chunk range is a
-// compile-time constant.  Software pipeline: step k forms the updated pivot
-// column and its norm first, then the reflector of step k+1 and its LDS
-// broadcast, and issues its own rank-2 update last, so the scalar chain and
-// the reductions overlap the update's FMAs.
-template <typename T>
-struct HhRefl {
-    T alpha, tau, rv0;
+// With x the pivot column below the diagonal, alpha = -sgn(x_0)||x|| and
+// xt = x - alpha e, the reflector is I - beta xt xt^T, beta = 1/(mu(mu + |x_0|)),
+// mu = ||x||.  The products run on x, before its norm is known:
+//   A xt = A x - alpha A e,   xt^T A xt = x^T A x - 2 alpha (A x)_0 + alpha^2 A_00
+// (A e is the next pivot column, which the step needs anyway), so the norm's
+// wave sum and the reflector's scalar chain run beside the rank-2 update of
+// the step before and the product, on a wave of their own in the larger teams.
+// xt is x except at its first entry, where both terms have one sign: no
+// cancellation enters.  With p = beta A xt, K = (beta/2) xt^T p, w = p - K xt
+// the update is A - xt w^T - w xt^T; rows and columns up to the pivot row are
+// finished after it, so the update of the others needs x itself, not xt, and
+// the next pivot column is A e - w xt_0 - x w_0 per row.
+//
+// A step of a team has one barrier: before it the product waves apply the
+// previous update, form A x, their parts of x^T A x and A e; after it every
+// product wave (and the control wave) forms w and the next x for all rows, one
+// row per lane, and hands them to its own lanes through its own LDS copies.
+template <typename T> struct HhRefl {
+    double alpha, beta, rx0;  // rx0 = 1 / (x_0 - alpha)
 };
-template <typename T, typename H>
-__device__ __forceinline__ HhRefl<H> hh_reflector(const H x0, const H sig)
+template <typename T>
+__device__ __forceinline__ HhRefl<T> hh_reflector(const double x0, const double sig)
 {
-    // alpha = -sgn(x0) mu, mu = ||x||; v = (1, x_2.. / (x0 - alpha)) with
-    // x0 - alpha = sgn(x0)(|x0| + mu); tau = (mu + |x0|)/mu = 2/(v^T v) in
-    // exact arithmetic.  Two independent reciprocals (1/mu, 1/(|x0| + mu)).
-    // tau = 0 when the sub-column is already zero.
-    // (binary64 arithmetic for binary32 storage: hardware estimates with one
-    // Newton step, far more accurate than the binary32 result needs; binary64
-    // storage: IEEE operations)
-    constexpr bool est = sizeof(T) < sizeof(H);
-    const bool z = (sig == H(0));
-    const H s2 = fma(x0, x0, sig);
-    const H rmu = est ? d_rsqrt_nr(s2) : f_rsqrt(s2);
-    const H mu = s2 * rmu;
-    const H ax = f_abs(x0);
-    const H sg = (x0 < H(0)) ? H(-1) : H(1);
-    HhRefl<H> h;
-    h.alpha = z ? x0 : -sg * mu;
-    h.rv0 = z ? H(1) : sg * (est ? d_rcp_nr(ax + mu) : f_rcp(ax + mu));
-    h.tau = z ? H(0) : fma(ax, rmu, H(1));
+    // sig = ||x||^2 - x_0^2.  A sub-column below 1e-140 (of a matrix scaled to
+    // magnitude one) counts as zero: beta = 0, alpha = x_0; beta stays finite.
+    // 1/mu and 1/(|x_0| + mu) are hardware estimates refined by Newton steps:
+    // one for binary32 storage (below 1e-12), two for binary64.
+    const bool z = sig < 1e-280;
+    const double s2 = fma(x0, x0, sig);
+    double rmu = d_rsqrt_nr(s2);
+    if constexpr (sizeof(T) == 8) rmu = fma(rmu, 0.5 * fma(-s2 * rmu, rmu, 1.0), rmu);
+    const double mu = s2 * rmu;
+    const double ax = f_abs(x0);
+    double rs = d_rcp_nr(ax + mu);
+    if constexpr (sizeof(T) == 8) rs = fma(rs, fma(-(ax + mu), rs, 1.0), rs);
+    HhRefl<T> h;
+    h.alpha = z ? x0 : -f_copysign(mu, x0);
+    h.beta = z ? 0.0 : rmu * rs;
+    h.rx0 = z ? 0.0 : f_copysign(rs, x0);
     return h;
 }
 
-template <typename T, int NMAX, int NT, int HW, int Q0, typename H>
-__device__ __forceinline__ void hh_range(Smem<T, NMAX, NT>& S, const int n, const int lane,
-                                         const int wave, H (&ar)[NMAX * NMAX / (64 * HW)], H& xr,
-                                         H& sig, H& vr, H& tauk)
+// Lanes of a product wave: lane l holds rows i = l % 8 (+ 8 wave) and columns
+// j = l / 16 + 4 (l / 8 % 2).  A binary64 4x4x4 MFMA (four blocks, block l / 4
+// % 4: A row l % 4, k = l / 16; D row l / 16, column l % 4) against a B of ones
+// in some columns sums a value over the four lanes l / 16 of a row and leaves
+// the sum in lanes l / 16 = row, at those columns: NA such products reduce NA
+// values and place them in different lanes, in one instruction each instead of
+// the moves and selects of a butterfly (7 for a pair of values and stage).
+__device__ __forceinline__ int hh_row_of(const int l) { return l & 7; }
+__device__ __forceinline__ int hh_col_of(const int l) { return (l >> 4) | ((l >> 1) & 4); }
+// Lane l ends with the row hh_out_row(l) and the value a = hh_own<NA>(l).
+__device__ __forceinline__ int hh_out_row(const int l) { return (l >> 4) | (l & 4); }
+template <int NA> __device__ __forceinline__ int hh_own(const int l)
 {
-    constexpr int GW = 64 / NMAX;   // column groups per wave
-    constexpr int G = HW * GW;      // column groups of the team
-    constexpr int CPT = NMAX / G;
-    constexpr int NCH = CPT / 4;
-    const int r = lane % NMAX, gl = lane / NMAX, g = wave * GW + gl;
-    const int glast = wave * GW + GW - 1;  // last group of this wave
-    const bool g0 = gl == 0;
-    const int pos_r = (r % G) * CPT + r / G;
-    H* vb = reinterpret_cast<H*>(S.u.h.vbuf) + wave * NMAX;
-    H* wb = reinterpret_cast<H*>(S.u.h.wbuf) + wave * NMAX;
-    H* colb = reinterpret_cast<H*>(S.u.h.colb);
-    // instance Q0 = NCH: every column of this wave is dead, but the wave
-    // keeps stepping (barriers, pivot column, next reflector) until n - 2
-    const int kb = (Q0 == 0) ? 0 : glast + G * (4 * Q0 - 1);
-    const int ke = (Q0 == NCH) ? n - 2 : min(glast + G * (4 * Q0 + 3), n - 2);
-    // loop invariant: vr, tauk and this wave's LDS copy of v belong to step
-    // k; ar holds the matrix after steps < k
-    for (int k = kb; k < ke; ++k) {
+    if constexpr (NA == 8) return (l & 3) | ((l >> 1) & 4);
+    else if constexpr (NA == 4) return l & 3;
+    else return NA == 2 ? (l >> 1) & 1 : 0;
+}
+// A lane that ends with row i (0..7) and value a.
+template <int NA> __device__ __forceinline__ int hh_lane_of(const int i, const int a)
+{
+    const int o = NA == 8 ? (a & 3) | ((a & 4) << 1) : (NA == 4 ? a : (NA == 2 ? 2 * a : 0));
+    return ((i & 3) << 4) | (i & 4) | o;
+}
+constexpr int DPP_ROR8 = 0x128;  // lane ^ 8 within 16
+
+// The B operands: sel[a] is one in the columns that value a is left in.
+template <int NA> struct HhSelect {
+    static constexpr int NS = NA < 4 ? NA : 4;
+    double sel[NS];
+    __device__ __forceinline__ explicit HhSelect(const int l)
+    {
+#pragma unroll
+        for (int a = 0; a < NS; ++a) sel[a] = (NS == 1 || hh_own<NS>(l) == a) ? 1.0 : 0.0;
+    }
+};
+// y[a] summed over the eight columns' lanes; values of finished chunks (a <
+// A0) are left out.
+template <int NA, int A0>
+__device__ __forceinline__ double hh_reduce_scatter(const double (&y)[NA], const HhSelect<NA>& B,
+                                                    const int l)
+{
+    constexpr int NS = HhSelect<NA>::NS;
+    double u = 0.0, v = 0.0;
+#pragma unroll
+    for (int a = 0; a < NS; ++a) {
+        if (a >= A0) u = __builtin_amdgcn_mfma_f64_4x4x4f64(y[a], B.sel[a], u, 0, 0, 0);
+        if constexpr (NA == 8)
+            if (a + 4 >= A0) v = __builtin_amdgcn_mfma_f64_4x4x4f64(y[a + 4], B.sel[a], v, 0, 0, 0);
+    }
+    if constexpr (NA == 8) {
+        if (A0 >= 4) return v + dpp_move64<DPP_ROR8>(v);
+        const bool up = (l & 8) != 0;
+        const double keep = up ? v : u, send = up ? u : v;
+        return keep + dpp_move64<DPP_ROR8>(send);
+    }
+    return u + dpp_move64<DPP_ROR8>(u);
+}
+
+// One row per lane, in the same places: lane l stands for position
+// hh_out_row(l) + 8 own(l) (duplicates for NMAX < 64).
+template <int NMAX> struct HhRow {
+    static constexpr int NB = NMAX / 8;
+    int pos, slot;
+    __device__ __forceinline__ explicit HhRow(const int lane)
+    {
+        const int i = hh_out_row(lane), o = hh_own<NB>(lane);
+        pos = i + 8 * o;
+        slot = i * HhLds<NMAX>::ST + o;
+    }
+    static __device__ __forceinline__ int slot_of(const int pos)
+    {
+        return (pos & 7) * HhLds<NMAX>::ST + (pos >> 3);
+    }
+    static __device__ __forceinline__ int lane_of(const int pos)
+    {
+        return hh_lane_of<NB>(pos & 7, pos >> 3);
+    }
+    // sum over the positions of a per-row value, in every lane
+    static __device__ __forceinline__ double sum(const double x)
+    {
+        return (NMAX / 64.0) * wave_sum_all(x);  // 64 / NMAX lanes per position
+    }
+};
+
+// Step k once A x (yr), A e (ce), their values s1, a00 at the pivot row and
+// q = x^T A x are known: -w and the next pivot column at this lane's row; w0 =
+// w at the pivot row.  hb = beta^2 / 2.
+struct HhStep {
+    double nw, xn, w0;
+};
+__device__ __forceinline__ HhStep hh_step(const double x, const double yr, const double ce,
+                                          const double s1, const double a00, const double q,
+                                          const double alpha, const double beta, const double hb,
+                                          const double xt0)
+{
+    const double kk = hb * fma(alpha, fma(alpha, a00, -2.0 * s1), q);
+    HhStep o;
+    o.nw = fma(kk, x, -beta * fma(-alpha, ce, yr));
+    o.w0 = fma(-kk, xt0, beta * fma(-alpha, a00, s1));
+    o.xn = fma(o.nw, xt0, fma(-x, o.w0, ce));
+    return o;
+}
+
+// Entries, vectors and the product of one product wave at the chunk level.
+template <int NMAX, int HW> struct HhBlock {
+    static constexpr int GI = 8 * HW;
+    static constexpr int NA = NMAX / GI, NB = NMAX / 8, ST = HhLds<NMAX>::ST;
+    double a[NA][NB];       // A(i + GI a, j + 8 b) after the updates of all steps but the last
+    double xr[NA], xc[NB];  // x of the last step at this lane's rows and columns
+
+    // Applies the update of the last step (-w in wl) and forms the products of
+    // this step with x in xl, for rows and columns from chunks A0, B0 on.  The
+    // column of position 8 B0 + j0 goes to cl.  Returns this lane's part of x^T A x.
+    template <int A0, int B0>
+    __device__ __forceinline__ double step(const double* xl, const double* wl, double* cl,
+                                           const int i, const int j, const int j0, double (&y)[NA])
+    {
+        double wr[NA], wc[NB], nr[NA], nc[NB];
+        const int ri = (i & 7) * ST + (i >> 3);
+#pragma unroll
+        for (int c = A0; c < NA; ++c) {
+            wr[c] = wl[ri + HW * c];
+            nr[c] = xl[ri + HW * c];
+        }
+#pragma unroll
+        for (int b = B0 & ~1; b < NB; ++b) {
+            wc[b] = wl[j * ST + b];
+            nc[b] = xl[j * ST + b];
+        }
+#pragma unroll
+        for (int c = A0; c < NA; ++c)
+#pragma unroll
+            for (int b = B0; b < NB; ++b)
+                a[c][b] = fma(wr[c], xc[b], fma(xr[c], wc[b], a[c][b]));
+        if (j == j0) {
+#pragma unroll
+            for (int c = A0; c < NA; ++c) cl[ri + HW * c] = a[c][B0];
+        }
+        double q = 0.0;
+#pragma unroll
+        for (int c = 0; c < NA; ++c) {
+            y[c] = 0.0;
+            if (c < A0) continue;
+            double y1 = a[c][B0] * nc[B0], y2 = 0.0;
+#pragma unroll
+            for (int b = B0 + 1; b < NB; ++b) {
+                double& acc = ((b - B0) & 1) ? y2 : y1;
+                acc = (b == B0 + 1) ? a[c][b] * nc[b] : fma(a[c][b], nc[b], acc);
+            }
+            y[c] = (B0 + 1 < NB) ? y1 + y2 : y1;
+            q = (c == A0) ? nr[c] * y[c] : fma(nr[c], y[c], q);
+        }
+#pragma unroll
+        for (int c = A0; c < NA; ++c) xr[c] = nr[c];
+#pragma unroll
+        for (int b = B0; b < NB; ++b) xc[b] = nc[b];
+        return q;
+    }
+};
+
+// The steps kp (padded index) whose pivot row kp + 1 = 8 B0 + i0 lies in chunk
+// B0: f(parity constant, kp, i0), the parity of kp fixed per call.
+template <int NMAX, typename F>
+__device__ __forceinline__ void hh_chunk(const int b0, const int pad, F&& f)
+{
+#pragma unroll 1
+    for (int i0 = 0; i0 < 8; i0 += 2) {
+        const int kp = 8 * b0 - 1 + i0;
+        if (kp >= pad && kp < NMAX - 2) f(std::integral_constant<int, 1>{}, kp, i0);
+        if (kp + 1 >= pad && kp + 1 < NMAX - 2) f(std::integral_constant<int, 0>{}, kp + 1, i0 + 1);
+    }
+}
+
+// One wave alone, chunks B0, B0 + 1, ...  x: the pivot column at this lane's
+// row (zero up to the pivot); xl, nwl: x and -w of the last step there.
+template <typename T, int NMAX, int NT, int B0>
+__device__ __forceinline__ void hh_solo(Smem<T, NMAX, NT>& S, const int n, const int lane,
+                                        const HhSelect<NMAX / 8>& sel, HhBlock<NMAX, 1>& H,
+                                        double& x, double& xl, double& nwl)
+{
+    constexpr int NB = NMAX / 8;
+    constexpr int VLD = Smem<T, NMAX, NT>::VLD;
+    constexpr int ST = HhLds<NMAX>::ST;
+    const int wave = 0;
+    (void)wave;
+    const int pad = NMAX - n;
+    const HhRow<NMAX> R(lane);
+    const int vr = R.pos - pad + (R.pos < pad ? NMAX : 0);
+    if (8 * B0 + 7 > pad)
+    hh_chunk<NMAX>(B0, pad, [&](auto, const int kp, const int i0) {
+        const int k = kp - pad;
+        const int s0 = i0 * ST + B0;
         wave_sync();
         BED_HSTEP(k, 0);
-        H vc[CPT];
-#pragma unroll
-        for (int j = 4 * Q0; j < CPT; ++j) vc[j] = vb[g * CPT + j];
-        H pp0 = H(0), pp1 = H(0);
-#pragma unroll
-        for (int q = Q0; q < NCH; ++q) {
-            pp0 = fma(ar[4 * q + 0], vc[4 * q + 0], pp0);
-            pp1 = fma(ar[4 * q + 1], vc[4 * q + 1], pp1);
-            pp0 = fma(ar[4 * q + 2], vc[4 * q + 2], pp0);
-            pp1 = fma(ar[4 * q + 3], vc[4 * q + 3], pp1);
-        }
-        H pr = pp0 + pp1;
-        if constexpr (GW >= 4) pr += xmove<16>(pr, lane);
-        if constexpr (GW >= 2) pr += xmove<32>(pr, lane);
+        const double x0 = S.u.h.x[0][s0];
+        const double sig = HhRow<NMAX>::sum(R.pos > kp + 1 ? x * x : 0.0);
+        double y[NB];
+        double q = H.template step<B0, B0>(S.u.h.x[0], S.u.h.w[0], S.u.h.c[0], hh_row_of(lane),
+                                           hh_col_of(lane), i0, y);
         BED_HSTEP(k, 1);
-        // pivot column k + 1 before this step's update, from its owner group;
-        // in this instance its register index lies in [4 Q0, 4 Q0 + 4)
-        const int c1 = k + 1;
-        const int g1 = c1 % G;
-        H a1 = H(0);  // valid in group g1 (never this wave in instance NCH)
-        if constexpr (Q0 < NCH) a1 = pick<4>(ar + 4 * Q0, (c1 / G) & 3);
-        H cb;
-        if constexpr (HW > 1) {
-            H* pa = reinterpret_cast<H*>(S.u.h.part) + (k & 1) * HW * NMAX;
-            if (g0) pa[wave * NMAX + r] = pr;
-            if (g == g1) colb[(k & 1) * NMAX + r] = a1;
-            team_sync<NT>();
-            H q[HW];
-#pragma unroll
-            for (int w2 = 0; w2 < HW; ++w2) q[w2] = pa[w2 * NMAX + r];
-#pragma unroll
-            for (int st = 1; st < HW; st *= 2)  // pairwise (tree) sum
-#pragma unroll
-                for (int w2 = 0; w2 + st < HW; w2 += 2 * st) q[w2] += q[w2 + st];
-            pr = q[0];
-            cb = colb[(k & 1) * NMAX + r];
-            BED_HSTEP(k, 2);
-        } else {
-            cb = a1;
-            if constexpr (GW == 2) {
-                const H o32 = xmove<32>(a1, lane);
-                cb = (g == g1) ? a1 : o32;
-            } else if constexpr (GW == 4) {
-                const H o16 = xmove<16>(a1, lane);
-                const H o32 = xmove<32>(a1, lane);
-                const H o48 = xmove<32>(o16, lane);
-                const int dd = g ^ g1;
-                cb = dd == 0 ? a1 : (dd == 1 ? o16 : (dd == 2 ? o32 : o48));
-            }
-        }
-        pr *= tauk;
-        const H pv = wave_sum_all(g0 ? pr * vr : H(0));
-        BED_HSTEP(k, 3);
-        const H wr = pr - H(0.5) * tauk * pv * vr;
-        if (g0) wb[pos_r] = wr;
-        // v and w at column k + 1 are the values of row k + 1
-        const H v1 = bcast(vr, k + 1), w1 = bcast(wr, k + 1);
+        const HhRefl<T> h = hh_reflector<T>(x0, sig);
         wave_sync();
-        H wc[CPT];
-#pragma unroll
-        for (int j = 4 * Q0; j < CPT; ++j) wc[j] = wb[g * CPT + j];
-        BED_HSTEP(k, 4);
-        const H xn = fma(-wr, v1, fma(-vr, w1, cb));  // pivot column k + 1, row r
-        const H sn = wave_sum_all((g0 && r > k + 2) ? xn * xn : H(0));
-        BED_HSTEP(k, 5);
-        // reflector of step k + 1 (harmless past the last step: nothing reads
-        // reflector n - 2, and b[n - 2], a[n - 2] are rewritten afterwards)
-        const HhRefl<H> h = hh_reflector<T>(bcast(xn, k + 2), sn);
-        const H vn = (r == k + 2) ? H(1) : ((r > k + 2 && sn != H(0)) ? xn * h.rv0 : H(0));
-        BED_HSTEP(k, 6);
-        if (wave == 0 && lane == 0) {
-            S.tau[k + 1] = T(h.tau);
-            S.b[k + 1] = T(h.alpha);
-        }
-        if (g0) {
-            if (wave == 0) {
-                if (r == k + 1) S.a[k + 1] = T(xn);
-                S.Vt[(k + 1) * Smem<T, NMAX, NT>::VLD + r] = T(vn);
-            }
-            vb[pos_r] = vn;
-        }
-        BED_HSTEP(k, 7);
-        // rank-2 update of step k
-#pragma unroll
-        for (int j = 4 * Q0; j < CPT; ++j) ar[j] = fma(-wr, vc[j], fma(-vr, wc[j], ar[j]));
+        const double ce = S.u.h.c[0][R.slot], a00 = S.u.h.c[0][s0];
+        const double yr = hh_reduce_scatter<NB, B0>(y, sel, lane);
+        q = wave_sum_all(q);
+        const double s1 = bcast(yr, hh_lane_of<NB>(i0, B0));
+        BED_HSTEP(k, 2);
+        const double xt0 = x0 - h.alpha;
+        const HhStep o = hh_step(x, yr, ce, s1, a00, q, h.alpha, h.beta, 0.5 * h.beta * h.beta, xt0);
+        xl = x;
+        nwl = o.nw;
+        // reflector k, normalized to v_{k+1} = 1, at index r of the original
+        // matrix (padding positions hold zeros at indices >= n)
+        const double v = (R.pos == kp + 1) ? 1.0 : x * h.rx0;
+        x = (R.pos > kp + 1) ? o.xn : 0.0;
+        S.u.h.w[0][R.slot] = o.nw;
+        S.u.h.x[0][R.slot] = x;
+        BED_HSTEP(k, 3);
+        S.Vt[k * VLD + vr] = T(v);
+        // (every lane writes the same values)
+        S.tau[k] = T(h.beta * xt0 * xt0);
+        S.b[k] = T(h.alpha);
+        S.a[k + 1] = T(fma(-2.0 * xt0, o.w0, a00));
         BED_HSTEP(k, 8);
-        xr = xn;
-        sig = sn;
-        vr = vn;
-        tauk = h.tau;
-        if constexpr (HW == 1 && QH_WAVES<T, NMAX, NT>::value > 0)
+        if constexpr (QH_WAVES<T, NMAX, NT>::value > 0)
             if (k % QH_SYNC == QH_SYNC - 1) team_sync<NT>();
-    }
-    if constexpr (Q0 < NCH)
-        hh_range<T, NMAX, NT, HW, Q0 + 1, H>(S, n, lane, wave, ar, xr, sig, vr, tauk);
+    });
+    if constexpr (B0 + 1 < NB) hh_solo<T, NMAX, NT, B0 + 1>(S, n, lane, sel, H, x, xl, nwl);
+}
+
+// A product wave of a team (wave < HW).
+template <typename T, int NMAX, int NT, int B0>
+__device__ __forceinline__ void hh_product(Smem<T, NMAX, NT>& S, const int n, const int lane,
+                                           const int wave,
+                                           const HhSelect<HhBlock<NMAX, HhWaves<T, NMAX, NT>::HW>::NA>& sel,
+                                           HhBlock<NMAX, HhWaves<T, NMAX, NT>::HW>& H, double& x,
+                                           double& xl, double& nwl)
+{
+    constexpr int HW = HhWaves<T, NMAX, NT>::HW;
+    using B = HhBlock<NMAX, HW>;
+    constexpr int A0 = 8 * B0 / B::GI;
+    constexpr int ST = HhLds<NMAX>::ST;
+    const int pad = NMAX - n;
+    const HhRow<NMAX> R(lane);
+    const int i = 8 * wave + hh_row_of(lane), j = hh_col_of(lane);
+    double* X = S.u.h.x[wave];
+    double* W = S.u.h.w[wave];
+    // this lane's row after the reduction over the columns
+    const int yslot = HhRow<NMAX>::slot_of(8 * wave + hh_out_row(lane) + B::GI * hh_own<B::NA>(lane));
+    if (8 * B0 + 7 > pad)
+    hh_chunk<NMAX>(B0, pad, [&](auto P, const int kp, const int i0) {
+        constexpr int par = decltype(P)::value;
+        const int k = kp - pad;
+        (void)k;
+        const int s0 = i0 * ST + B0;
+        wave_sync();
+        BED_HSTEP(k, 0);
+        double y[B::NA];
+        double q = H.template step<A0, B0>(X, W, S.u.h.c[par], i, j, i0, y);
+        BED_HSTEP(k, 1);
+        const double yo = hh_reduce_scatter<B::NA, A0>(y, sel, lane);
+        q = wave_sum_all(q);
+        S.u.h.y[par][yslot] = yo;
+        S.u.h.q[par][wave] = q;  // (every lane writes the same value)
+        team_sync<NT>();
+        BED_HSTEP(k, 2);
+        const double yr = S.u.h.y[par][R.slot], ce = S.u.h.c[par][R.slot];
+        const double s1 = S.u.h.y[par][s0], a00 = S.u.h.c[par][s0];
+        const double alpha = S.u.h.sc[par][0], beta = S.u.h.sc[par][1];
+        const double hb = S.u.h.sc[par][2], xt0 = S.u.h.sc[par][3];
+        double qs = S.u.h.q[par][0];
+#pragma unroll
+        for (int w2 = 1; w2 < HW; ++w2) qs += S.u.h.q[par][w2];
+        const HhStep o = hh_step(x, yr, ce, s1, a00, qs, alpha, beta, hb, xt0);
+        xl = x;
+        nwl = o.nw;
+        x = (R.pos > kp + 1) ? o.xn : 0.0;
+        W[R.slot] = o.nw;
+        X[R.slot] = x;
+        BED_HSTEP(k, 3);
+        BED_HSTEP(k, 8);
+    });
+    if constexpr (B0 + 1 < NMAX / 8)
+        hh_product<T, NMAX, NT, B0 + 1>(S, n, lane, wave, sel, H, x, xl, nwl);
+}
+
+// The control wave of a team: norm and reflector of step k before its barrier,
+// then (as the product waves) the next pivot column; writes T, the reflectors
+// and tau (values that all lanes hold alike are written by all of them).
+template <typename T, int NMAX, int NT>
+__device__ __forceinline__ void hh_control(Smem<T, NMAX, NT>& S, const int n, const int lane, double x)
+{
+    constexpr int HW = HhWaves<T, NMAX, NT>::HW;
+    constexpr int VLD = Smem<T, NMAX, NT>::VLD;
+    constexpr int ST = HhLds<NMAX>::ST;
+    const int pad = NMAX - n;
+    const HhRow<NMAX> R(lane);
+    const int vr = R.pos - pad + (R.pos < pad ? NMAX : 0);
+#pragma unroll 1
+    for (int b0 = pad / 8; b0 < NMAX / 8; ++b0)
+        hh_chunk<NMAX>(b0, pad, [&](auto P, const int kp, const int i0) {
+            constexpr int par = decltype(P)::value;
+            const int k = kp - pad;
+            const int s0 = i0 * ST + b0;
+            const double x0 = bcast(x, hh_lane_of<NMAX / 8>(i0, b0));
+            const double sig = HhRow<NMAX>::sum(R.pos > kp + 1 ? x * x : 0.0);
+            const HhRefl<T> h = hh_reflector<T>(x0, sig);
+            const double xt0 = x0 - h.alpha, hb = 0.5 * h.beta * h.beta;
+            S.u.h.sc[par][0] = h.alpha;
+            S.u.h.sc[par][1] = h.beta;
+            S.u.h.sc[par][2] = hb;
+            S.u.h.sc[par][3] = xt0;
+            // normalized to v_{k+1} = 1, at index r of the original matrix
+            // (padding positions hold zeros at indices >= n)
+            S.Vt[k * VLD + vr] = T((R.pos == kp + 1) ? 1.0 : x * h.rx0);
+            S.tau[k] = T(h.beta * xt0 * xt0);
+            S.b[k] = T(h.alpha);
+            team_sync<NT>();
+            const double yr = S.u.h.y[par][R.slot], ce = S.u.h.c[par][R.slot];
+            const double s1 = S.u.h.y[par][s0], a00 = S.u.h.c[par][s0];
+            double qs = S.u.h.q[par][0];
+#pragma unroll
+            for (int w2 = 1; w2 < HW; ++w2) qs += S.u.h.q[par][w2];
+            const HhStep o = hh_step(x, yr, ce, s1, a00, qs, h.alpha, h.beta, hb, xt0);
+            x = (R.pos > kp + 1) ? o.xn : 0.0;
+            S.a[k + 1] = T(fma(-2.0 * xt0, o.w0, a00));
+        });
 }
 
 // Explicit Q_H = H_0 H_1 ... H_{n-3} on the AW waves that do not reduce:
@@ -1002,90 +1236,88 @@ __device__ __forceinline__ void qh_apply(const Smem<T, NMAX, NT>& S, const int l
     for (int i = 0; i < VPL; ++i) qh[i] = fma(-ts, v[i], qh[i]);
 }
 
-// Barrier schedule of the reduction: one barrier at the start of every step
-// with several reducing waves; with one, a barrier after every QH_SYNC-th step
-// when Q_H is accumulated, else none.  Every wave of the team follows it.
-template <int HW, int AW>
-__device__ __forceinline__ bool hh_barrier_at(const int k)
-{
-    return HW > 1 || (AW > 0 && k % QH_SYNC == QH_SYNC - 1);
-}
-
-template <typename T, int NMAX, int NT, int HW, typename H>
+template <typename T, int NMAX, int NT>
 __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, const int lane,
                                            const int wave, const bool want_q, const T sc,
                                            T (&qh)[QhShape<T, NMAX, NT>::VPL])
 {
     constexpr int LD = Smem<T, NMAX, NT>::LD;
-    constexpr int GW = 64 / NMAX;
-    constexpr int G = HW * GW;
-    constexpr int CPT = NMAX / G;
+    using WV = HhWaves<T, NMAX, NT>;
+    constexpr int HW = WV::HW;
     constexpr int AW = QH_WAVES<T, NMAX, NT>::value;
-    static_assert(CPT % 4 == 0, "chunks of four columns");
-    if (wave >= HW) {
+    if (wave >= WV::first_qh) {
+        // barriers of the reduction: every step of a team, else every QH_SYNC-th
+        // where a wave accumulates Q_H
+        constexpr int step = WV::team ? 1 : QH_SYNC;
         if constexpr (AW > 0) {
-            if (wave < HW + AW) {
+            if (wave < WV::first_qh + AW) {
                 // returns the first reflector not yet applied (the rest follow
                 // the barrier that closes the reduction)
                 constexpr int RW = QhShape<T, NMAX, NT>::RW;
                 constexpr int VPL = QhShape<T, NMAX, NT>::VPL;
-                const int row = (wave - HW) * RW + lane % RW, c0 = (lane / RW) * VPL;
+                const int row = (wave - WV::first_qh) * RW + lane % RW, c0 = (lane / RW) * VPL;
 #pragma unroll
                 for (int i = 0; i < VPL; ++i) qh[i] = (row == c0 + i) ? T(1) : T(0);
                 int j = 0;
-                for (int k = 0; k < n - 2; ++k) {
-                    if (!hh_barrier_at<HW, AW>(k)) continue;
-                    team_sync<NT>();
-                    // visible: reflectors up to k (barrier before step k) or up
-                    // to k + 1 (barrier after step k)
-                    const int jl = min(HW > 1 ? k : k + 1, n - 3);
-                    for (; j <= jl; ++j)
+                for (int k = step - 1; k < n - 2; k += step) {
+                    team_sync<NT>();  // visible: reflectors up to k
+                    for (; j <= k; ++j)
                         if (want_q) qh_apply<T, NMAX, NT>(S, lane, j, qh);
                 }
                 return j;
             }
         }
-        // waves outside the reduction only keep the barrier count
-        for (int k = 0; k < n - 2; ++k)
-            if (hh_barrier_at<HW, AW>(k)) team_sync<NT>();
+        // the other waves only keep the barrier count
+        if constexpr (WV::team || AW > 0)
+            for (int k = step - 1; k < n - 2; k += step) team_sync<NT>();
         return 0;
     }
     // The reduction is one dependent chain; its waves issue ahead of the
     // accumulating waves that share their SIMDs.
     if constexpr (AW > 0) __builtin_amdgcn_s_setprio(1);
-    const int r = lane % NMAX, gl = lane / NMAX, g = wave * GW + gl;
-    const bool g0 = gl == 0;
-    const H hs = H(sc);  // exact power of two
-    H ar[CPT];
+    const double hs = double(sc);  // exact power of two
+    const int pad = NMAX - n;
+    // lower triangle, zero in the padding, from a clamped address (no branch)
+    auto entry = [&](const int pr, const int pc) {
+        const int hi = max(pr, pc) - pad, lo = min(pr, pc) - pad;
+        const T v = S.M[lo >= 0 ? hi * LD + lo : 0];
+        return lo >= 0 ? hs * double(v) : 0.0;
+    };
+    const HhRow<NMAX> R(lane);
+    const double col0 = entry(R.pos, pad);
+    double x = R.pos > pad ? col0 : 0.0;
+    if (WV::team && wave == HW) {
+        if (lane == 0) S.a[0] = T(hs * double(S.M[0]));
+        hh_control<T, NMAX, NT>(S, n, lane, x);
+    } else {
+        using B = HhBlock<NMAX, HW>;
+        const int i = 8 * wave + hh_row_of(lane), j = hh_col_of(lane);
+        const HhSelect<B::NA> sel(lane);
+        B H;
 #pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-        const int c = g + G * j;
-        ar[j] = (r < n && c < n) ? hs * H(c <= r ? S.M[r * LD + c] : S.M[c * LD + r]) : H(0);
-    }
-    H xr = (r < n) ? hs * H(S.M[r * LD]) : H(0);  // pivot column 0 (lower triangle)
-    H sig = wave_total((g0 && r > 1) ? xr * xr : H(0));
-    // reflector of step 0 (harmless when n <= 2, as above)
-    const HhRefl<H> h = hh_reflector<T>(bcast(xr, 1), sig);
-    H vr = (r == 1) ? H(1) : ((r > 1 && sig != H(0)) ? xr * h.rv0 : H(0));
-    H tauk = h.tau;
-    if (wave == 0 && lane == 0) {
-        S.tau[0] = T(h.tau);
-        S.b[0] = T(h.alpha);
-    }
-    if (g0) {
-        if (wave == 0) {
-            if (r == 0) S.a[0] = T(xr);
-            S.Vt[r] = T(vr);
+        for (int a = 0; a < B::NA; ++a) {
+            H.xr[a] = 0.0;
+#pragma unroll
+            for (int b = 0; b < B::NB; ++b) H.a[a][b] = entry(i + B::GI * a, j + 8 * b);
         }
-        reinterpret_cast<H*>(S.u.h.vbuf)[wave * NMAX + (r % G) * CPT + r / G] = vr;
+#pragma unroll
+        for (int b = 0; b < B::NB; ++b) H.xc[b] = 0.0;
+        S.u.h.w[wave][R.slot] = 0.0;
+        S.u.h.x[wave][R.slot] = x;
+        double xl = 0.0, nwl = 0.0;  // x and -w of the last step at this lane's row
+        if constexpr (WV::team) hh_product<T, NMAX, NT, 0>(S, n, lane, wave, sel, H, x, xl, nwl);
+        else {
+            if (lane == 0) S.a[0] = T(hs * double(S.M[0]));
+            hh_solo<T, NMAX, NT, 0>(S, n, lane, sel, H, x, xl, nwl);
+        }
+        // last entries: b_{n-2} is the pivot column's last value, a_{n-1} the
+        // last diagonal entry after the last update (position NMAX - 1: lane 63
+        // of the last product wave)
+        if (wave == HW - 1 && lane == 63 && n >= 2) {
+            S.b[n - 2] = T(x);
+            S.a[n - 1] = T(fma(2.0 * xl, nwl, H.a[B::NA - 1][B::NB - 1]));
+        }
     }
-    hh_range<T, NMAX, NT, HW, 0, H>(S, n, lane, wave, ar, xr, sig, vr, tauk);
-    wave_sync();
-    if (wave == 0 && g0 && n >= 2) {
-        if (r == n - 2) S.a[n - 2] = T(xr);
-        if (r == n - 1) S.b[n - 2] = T(xr);
-    }
-    if (g == (n - 1) % G && r == n - 1) S.a[n - 1] = T(pick<CPT>(ar, (n - 1) / G));
     if constexpr (AW > 0) __builtin_amdgcn_s_setprio(0);
     return 0;
 }
@@ -1182,43 +1414,26 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
     BED_PHASE(1);
 
     // ------------------------------------------------------------ Householder
-    constexpr int HW = HH_WAVES<T, NMAX, NT>::value;
     constexpr int AW = QH_WAVES<T, NMAX, NT>::value;
-    const bool qh_wave = AW > 0 && wave >= HW && wave < HW + AW && Q_out != nullptr;
+    constexpr int QW = HhWaves<T, NMAX, NT>::first_qh;
+    const bool qh_wave = AW > 0 && wave >= QW && wave < QW + AW && Q_out != nullptr;
     T qh[QhShape<T, NMAX, NT>::VPL];
-    // binary64 arithmetic when eigenvectors are formed; for eigenvalues alone
-    // the storage type (their error is the reduction's backward error, which
-    // no eigenvalue gap amplifies)
-    using H64 = typename HhArith<T>::type;
     int qj;
     if constexpr (TRI) {
-        static_assert(QH_WAVES<T, NMAX, NT>::value > 0, "tridiagonal input: explicit Q_H shapes");
         // exact power-of-two scaling of the given diagonals (the same threads
-        // wrote them); Q_H = I on the waves that would form it
+        // wrote them); Q_H = I is never formed
         const T sc = fexp<T>::pow2(input_shift(S));
         for (int e = t; e < 2 * n - 1; e += NT) {
             if (e < n) S.a[e] *= sc;
             else S.b[e - n] *= sc;
         }
-        if (qh_wave) {
-            constexpr int RW = QhShape<T, NMAX, NT>::RW;
-            constexpr int VPL = QhShape<T, NMAX, NT>::VPL;
-            const int row = (wave - HW) * RW + lane % RW, c0 = (lane / RW) * VPL;
-#pragma unroll
-            for (int i = 0; i < VPL; ++i) qh[i] = (row == c0 + i) ? T(1) : T(0);
-        }
         qj = n - 2;
-    } else if constexpr (std::is_same<H64, T>::value)
-        qj = householder<T, NMAX, NT, HW, T>(S, n, lane, wave, Q_out != nullptr,
-                                             fexp<T>::pow2(input_shift(S)), qh);
-    else if (Q_out)
-        qj = householder<T, NMAX, NT, HW, H64>(S, n, lane, wave, true,
-                                               fexp<T>::pow2(input_shift(S)), qh);
-    else
-        qj = householder<T, NMAX, NT, HW, T>(S, n, lane, wave, false,
-                                             fexp<T>::pow2(input_shift(S)), qh);
+    } else {
+        qj = householder<T, NMAX, NT>(S, n, lane, wave, Q_out != nullptr,
+                                      fexp<T>::pow2(input_shift(S)), qh);
+    }
     team_sync<NT>();
-    if constexpr (AW > 0) {
+    if constexpr (AW > 0 && !TRI) {
         // reflectors written after the last barrier of the reduction
         if (qh_wave)
             for (; qj < n - 2; ++qj) qh_apply<T, NMAX, NT>(S, lane, qj, qh);
@@ -1236,7 +1451,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
             constexpr int VLD = Smem<T, NMAX, NT>::VLD;
             constexpr int VW = 16 / sizeof(T);
             typedef T vec_t __attribute__((ext_vector_type(VW)));
-            const int row = (wave - HW) * RW + lane % RW, c0 = (lane / RW) * VPL;
+            const int row = (wave - QW) * RW + lane % RW, c0 = (lane / RW) * VPL;
             vec_t* qp = reinterpret_cast<vec_t*>(S.Vt + row * VLD + c0);
 #pragma unroll
             for (int q = 0; q < VPL / VW; ++q) {

@@ -5,7 +5,7 @@ include/bed_probe.h) on the batch-512 workload and prints, as markdown, the
 mean time of every phase over the teams and the cycle breakdown of one
 Householder step.
 
-    python -m paper_2604_27325_amd.probe --n 64 [--threads 512] [--batch 256]
+    python -m paper_2604_27325_amd.probe --n 64 [--threads 256] [--batch 256]
 """
 import argparse
 import ctypes
@@ -16,9 +16,8 @@ import numpy as np
 _HERE = os.path.dirname(os.path.abspath(__file__))
 PROBE_LIB = os.path.join(_HERE, "_lib", "libbed_probe.so")
 PHASES, SUBSTEPS = 64, 16
-SUB_NAMES = {1: "dot product", 2: "partial exchange + barrier", 3: "reduction p^T v",
-             4: "w broadcast (write, read)", 5: "reduction of the pivot column norm",
-             6: "reflector scalars", 7: "v broadcast writes", 8: "rank-2 update"}
+SUB_NAMES = {1: "update and product", 2: "reductions (and exchange, barrier)",
+             3: "w and next pivot column", 8: "outputs"}
 
 
 def phase_names(n):
@@ -98,7 +97,7 @@ def report(n, threads, hstep, marks, steps, defl=None):
                 lines.append(f"| {SUB_NAMES[i]} | {c:.0f} |")
                 prev = i
         full = float(np.mean(st[:, 8] - st[:, 0]))
-        lines.append(f"| **step (start to end of update, markers included)** | {full:.0f} |")
+        lines.append(f"| **step (start to end, markers included)** | {full:.0f} |")
     if defl is not None:
         lines += ["", f"deflations per matrix (mean over {defl.shape[0]}): type 1 "
                   f"{defl[:, 0].mean():.2f}, type 2 {defl[:, 1].mean():.3f}; matrices with a "
@@ -114,7 +113,7 @@ def main():
     ap.add_argument("--batch", type=int, default=512,
                     help="matrices (at most 512; 256 puts one team on each CU)")
     a = ap.parse_args()
-    threads = a.threads or (64 if a.n <= 16 else (256 if a.n <= 32 else 512))
+    threads = a.threads or (64 if a.n <= 16 else 256)
     hstep = 8 if a.n <= 16 else (16 if a.n <= 32 else 32)
     marks, steps, defl = run(a.n, threads, lib_path=a.lib, batch=a.batch)
     print(report(a.n, threads, hstep, marks, steps, defl))
