@@ -88,11 +88,11 @@ int size_class(int n) { return n <= 16 ? 0 : (n <= 32 ? 1 : 2); }
 TeamShape class_shape(int cls, const bed_tune &t)
 {
     switch (cls) {
-    case 0: return TeamShape{16, 64, t.leaf > 0 ? t.leaf : leaf_default(16)};
+    case 0: return TeamShape{16, 64, t.leaf};
     case 1: return TeamShape{32, t.threads_mid > 0 ? t.threads_mid : 128,
-                             t.leaf > 0 ? t.leaf : leaf_default(32)};
+                             t.leaf};
     default: return TeamShape{64, t.threads_big > 0 ? t.threads_big : 256,
-                              t.leaf > 0 ? t.leaf : leaf_default(64)};
+                              t.leaf};
     }
 }
 

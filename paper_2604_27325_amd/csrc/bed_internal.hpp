@@ -27,18 +27,16 @@ struct PtrItem {
     int32_t pad;
 };
 
-// Size classes: a team of `nt` threads solves matrices with n <= nmax,
-// splitting the tridiagonal matrix down to leaves of at most `leaf` elements
-// (2, 4 or 8).  Default cutoff per class (measured on the batch-512
-// workloads): 8 for the n > 32 class, whose one fewer merge depth outweighs
-// the longer Jacobi sweeps, 4 below.
-__host__ __device__ constexpr int leaf_default(int nmax) { return nmax >= 64 ? 8 : 4; }
+// Size classes: a team of `nt` threads solves matrices with n <= nmax.  leaf =
+// 0: binary32 spectra are solved directly (bed_syevd.hpp), with the divide step
+// for what that leaves; leaf = 2, 4 or 8: by the divide step, splitting the
+// tridiagonal matrix down to leaves of at most `leaf` elements.
 struct TeamShape {
     int nmax;
     int nt;
-    int leaf = 4;
+    int leaf = 0;
 };
-inline bool leaf_supported(int leaf) { return leaf == 2 || leaf == 4 || leaf == 8; }
+inline bool leaf_supported(int leaf) { return leaf == 0 || leaf == 2 || leaf == 4 || leaf == 8; }
 
 // Largest order of the one-shot solve (64 < n <= NMAX_BIG: binary32, uniform
 // batches, one tearing step above the n <= 64 kernels).

@@ -56,27 +56,28 @@ namespace bed {
 template <typename T, int NMAX, int NT>
 __global__ void __launch_bounds__(NT) BED_OCC(NMAX, NT)
 k_probe_uniform(const T *__restrict__ A, int n, int64_t batch, T *__restrict__ lam,
-                T *__restrict__ Q)
+                T *__restrict__ Q, int leaf)
 {
     __shared__ Smem<T, NMAX, NT> S;
     const int64_t b = blockIdx.x;
     if (b >= batch) return;
     const int64_t n2 = (int64_t)n * n;
     syevd_team<T, NMAX, NT>(A + b * n2, n, lam + b * n, Q ? Q + b * n2 : nullptr, nullptr, S,
-                            threadIdx.x, leaf_default(NMAX));
+                            threadIdx.x, leaf);
 }
 
 #define BED_PROBE_SHAPES(X) X(16, 64) X(32, 64) X(32, 128) X(32, 256) X(64, 256) X(64, 512)
 
 template <typename T>
 static hipError_t probe_t(int nt, const void *A, int n, int64_t batch, void *lam, void *Q,
-                          hipStream_t s)
+                          bool divide, hipStream_t s)
 {
     const int nmax = n <= 16 ? 16 : (n <= 32 ? 32 : 64);
 #define X(NM, NTT)                                                                          \
     if (nmax == NM && nt == NTT) {                                                          \
         hipLaunchKernelGGL((k_probe_uniform<T, NM, NTT>), dim3((unsigned)batch), dim3(NTT), \
-                           0, s, (const T *)A, n, batch, (T *)lam, (T *)Q);                 \
+                           0, s, (const T *)A, n, batch, (T *)lam, (T *)Q,                  \
+                           divide ? leaf_default(NM) : 0);                                  \
         return hipGetLastError();                                                           \
     }
     BED_PROBE_SHAPES(X)
@@ -108,7 +109,7 @@ extern "C" int32_t bed_probe_phases(int32_t dtype, int32_t threads, int32_t n, i
                                    hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);  // the host values above are locals
     if (e == hipSuccess)
-        e = dtype == 0 ? bed::probe_t<float>(threads, A, n, batch, lambda, Q, s)
-                       : bed::probe_t<double>(threads, A, n, batch, lambda, Q, s);
+        e = dtype == 0 ? bed::probe_t<float>(threads, A, n, batch, lambda, Q, defl != nullptr, s)
+                       : bed::probe_t<double>(threads, A, n, batch, lambda, Q, defl != nullptr, s);
     return e == hipSuccess ? 0 : 3;
 }

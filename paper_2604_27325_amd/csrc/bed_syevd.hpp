@@ -2,14 +2,18 @@
 // eigendecomposition of one symmetric n x n matrix (n <= NMAX <= 64) held in
 // LDS/VGPRs:
 //
-//   load -> Householder tridiagonalization (binary64 arithmetic) -> rank-one
-//   tearing (Sec. 2.1, Eq. (1)-(3)) -> leaves of at most 2, 4 or 8 elements by
-//   cyclic Jacobi (Sec. 2.2) -> bottom-up merges (Sec. 2.3): z/sort (Eq.
-//   (4)-(5)), deflation, secular roots by hybrid-section + Halley under bounded
-//   interlacing (Eq. (8)-(21)), progressive removal of converged roots (Eq.
-//   (22)), Loewner eigenvectors (Eq. (23)-(25)), back-multiplication (Eq. (4))
-//   -> Householder back-transform -> sign canonicalization -> store.  Without
-//   eigenvectors the merges carry only the end rows of each node's block.
+//   load -> Householder tridiagonalization (binary64 arithmetic) -> spectrum of
+//   T -> Householder back-transform -> sign canonicalization -> store.
+//
+// The spectrum of T, by the divide step of the note: rank-one tearing (Sec.
+// 2.1, Eq. (1)-(3)) -> leaves of at most 2, 4 or 8 elements by cyclic Jacobi
+// (Sec. 2.2) -> bottom-up merges (Sec. 2.3): z/sort (Eq. (4)-(5)), deflation,
+// secular roots by hybrid-section + Halley under bounded interlacing (Eq.
+// (8)-(21)), progressive removal of converged roots (Eq. (22)), Loewner
+// eigenvectors (Eq. (23)-(25)), back-multiplication (Eq. (4)); without
+// eigenvectors the merges carry only the end rows of each node's block.  By
+// default binary32 spectra without nearly equal eigenvalues are solved directly
+// instead (direct_solve below).
 //
 // Team geometry (NT threads, thread t):
 //   Householder: wave 0 reduces, lane (i, j) of an 8 x 8 grid holding the
@@ -88,6 +92,11 @@ template <typename T, int NMAX, int NT> struct QH_WAVES {
 // QH_SYNC steps so that the accumulating wave can follow.
 constexpr int QH_SYNC = 4;
 
+// Cutoff of the divide step when none is given (measured on the batch-512
+// workloads): 8 for the n > 32 class, whose one fewer merge depth outweighs the
+// longer Jacobi sweeps, 4 below.
+__host__ __device__ constexpr int leaf_default(int nmax) { return nmax >= 64 ? 8 : 4; }
+
 constexpr int SEC_CAP = 100;  // Halley-phase evaluations per root before "capped"
 
 // The Householder reduction runs in binary64 for both storage types.  Its
@@ -145,6 +154,7 @@ struct Smem {
     // vector reads; the buffer holds Q_H (row-major) once the reduction ends.
     static constexpr int VLD = QH_WAVES<T, NMAX, NT>::value ? NMAX + 4 : NMAX + 1;
     alignas(16) T Vt[NMAX * VLD];
+    double ta[NMAX], tb[NMAX];  // T as the reduction leaves it
     T a[NMAX], b[NMAX], tau[NMAX];
     T lam0[NMAX], lam1[NMAX];
     union {
@@ -159,6 +169,18 @@ struct Smem {
             alignas(16) double sc[2][4];
         } h;
         MergeArrays<T, NMAX> m;
+        struct {  // direct solver: rows {a_i, b_{i-1}^2} from the top and {a_i, b_i^2} from
+                  // the bottom, b_i in both orders, eigenvalues, first grid
+            alignas(16) double ab[2][NMAX][2];
+            double b[2][NMAX];
+            double lam[NMAX];
+            double lo, hi, unscale;
+            double gf[NT];
+            int gc[NT];
+            int cell[NMAX];
+            uint64_t close;  // j: eigenvalues j and j + 1 are close
+            int ok;
+        } t;
         struct {  // back-transform: per block of 16 reflectors, Gram matrix and T factor
             // 16 x 16 tiles with row stride 17 (bank-conflict free column reads)
             T gram[((NMAX + 13) / 16) * 272];
@@ -844,11 +866,11 @@ template <typename T> struct HhRefl {
 template <typename T>
 __device__ __forceinline__ HhRefl<T> hh_reflector(const double x0, const double sig)
 {
-    // sig = ||x||^2 - x_0^2.  A sub-column below 1e-140 (of a matrix scaled to
-    // magnitude one) counts as zero: beta = 0, alpha = x_0; beta stays finite.
+    // sig = ||x||^2 - x_0^2.  A sub-column below 1e-75 (of a matrix scaled to
+    // magnitude one) counts as zero: beta = 0, alpha = x_0; beta^2 stays finite.
     // 1/mu and 1/(|x_0| + mu) are hardware estimates refined by Newton steps:
     // one for binary32 storage (below 1e-12), two for binary64.
-    const bool z = sig < 1e-280;
+    const bool z = sig < 1e-150;
     const double s2 = fma(x0, x0, sig);
     double rmu = d_rsqrt_nr(s2);
     if constexpr (sizeof(T) == 8) rmu = fma(rmu, 0.5 * fma(-s2 * rmu, rmu, 1.0), rmu);
@@ -1084,8 +1106,8 @@ __device__ __forceinline__ void hh_solo(Smem<T, NMAX, NT>& S, const int n, const
         S.Vt[k * VLD + vr] = T(v);
         // (every lane writes the same values)
         S.tau[k] = T(h.beta * xt0 * xt0);
-        S.b[k] = T(h.alpha);
-        S.a[k + 1] = T(fma(-2.0 * xt0, o.w0, a00));
+        S.tb[k] = h.alpha;
+        S.ta[k + 1] = fma(-2.0 * xt0, o.w0, a00);
         BED_HSTEP(k, 8);
         if constexpr (QH_WAVES<T, NMAX, NT>::value > 0)
             if (k % QH_SYNC == QH_SYNC - 1) team_sync<NT>();
@@ -1179,7 +1201,7 @@ __device__ __forceinline__ void hh_control(Smem<T, NMAX, NT>& S, const int n, co
             // (padding positions hold zeros at indices >= n)
             S.Vt[k * VLD + vr] = T((R.pos == kp + 1) ? 1.0 : x * h.rx0);
             S.tau[k] = T(h.beta * xt0 * xt0);
-            S.b[k] = T(h.alpha);
+            S.tb[k] = h.alpha;
             team_sync<NT>();
             const double yr = S.u.h.y[par][R.slot], ce = S.u.h.c[par][R.slot];
             const double s1 = S.u.h.y[par][s0], a00 = S.u.h.c[par][s0];
@@ -1188,7 +1210,7 @@ __device__ __forceinline__ void hh_control(Smem<T, NMAX, NT>& S, const int n, co
             for (int w2 = 1; w2 < HW; ++w2) qs += S.u.h.q[par][w2];
             const HhStep o = hh_step(x, yr, ce, s1, a00, qs, h.alpha, h.beta, hb, xt0);
             x = (R.pos > kp + 1) ? o.xn : 0.0;
-            S.a[k + 1] = T(fma(-2.0 * xt0, o.w0, a00));
+            S.ta[k + 1] = fma(-2.0 * xt0, o.w0, a00);
         });
 }
 
@@ -1287,7 +1309,7 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
     const double col0 = entry(R.pos, pad);
     double x = R.pos > pad ? col0 : 0.0;
     if (WV::team && wave == HW) {
-        if (lane == 0) S.a[0] = T(hs * double(S.M[0]));
+        if (lane == 0) S.ta[0] = hs * double(S.M[0]);
         hh_control<T, NMAX, NT>(S, n, lane, x);
     } else {
         using B = HhBlock<NMAX, HW>;
@@ -1307,19 +1329,473 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
         double xl = 0.0, nwl = 0.0;  // x and -w of the last step at this lane's row
         if constexpr (WV::team) hh_product<T, NMAX, NT, 0>(S, n, lane, wave, sel, H, x, xl, nwl);
         else {
-            if (lane == 0) S.a[0] = T(hs * double(S.M[0]));
+            if (lane == 0) S.ta[0] = hs * double(S.M[0]);
             hh_solo<T, NMAX, NT, 0>(S, n, lane, sel, H, x, xl, nwl);
         }
         // last entries: b_{n-2} is the pivot column's last value, a_{n-1} the
         // last diagonal entry after the last update (position NMAX - 1: lane 63
         // of the last product wave)
         if (wave == HW - 1 && lane == 63 && n >= 2) {
-            S.b[n - 2] = T(x);
-            S.a[n - 1] = T(fma(2.0 * xl, nwl, H.a[B::NA - 1][B::NB - 1]));
+            S.tb[n - 2] = x;
+            S.ta[n - 1] = fma(2.0 * xl, nwl, H.a[B::NA - 1][B::NB - 1]);
         }
     }
     if constexpr (AW > 0) __builtin_amdgcn_s_setprio(0);
     return 0;
+}
+
+// ---------------------------------------------------------------- direct solver
+// Binary32 spectra whose eigenvalues are not extremely close are solved without
+// the divide step: every eigenvalue by sections and secants of det(T - x I) in
+// binary64, every eigenvector by the twisted factorization of T - lambda I
+// (Dhillon, Parlett).  Both work on all eigenvalues at once, lanes apart from
+// each other, where the divide step is three or four dependent merges of five
+// to seven phases each: batch 512, n = 64: 36 -> 20 us after the reduction, n =
+// 32: 21 -> 11 us.  A vector's error is about 3e-14 / gap (eigenvalue rounding
+// times the vector's length over its twist entry), inside the space of its
+// close neighbours: vectors of eigenvalues closer than DIRECT_CLOSE are made
+// orthogonal in order.  A matrix with a pair closer than DIRECT_GAP, with more
+// than DIRECT_MOST close pairs, or whose determinants leave the exponent range,
+// goes through the divide step, which does not depend on gaps.
+// Distances are of the Gershgorin interval's scale (|T| in [1/2, 1)).
+constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 1e-10;
+constexpr int DIRECT_MOST = 4;
+constexpr int DIRECT_CAP = 64;       // rounds per eigenvalue
+
+// Wave 0: T scaled by a power of two to |T| in [1/2, 1) (Gershgorin), as rows
+// {a_i, b_{i-1}^2} from the top and, for the bottom half's minors, {a_i, b_i^2}
+// from the bottom of the padded order m; padding rows are {4, 0}, whose factors
+// 4 - x keep signs.
+template <int LPR> __device__ __forceinline__ int direct_order(const int n)
+{
+    return LPR == 8 ? (n + 15) & ~15 : (n + 7) & ~7;
+}
+template <typename T, int NMAX, int NT>
+__device__ __forceinline__ void direct_setup(Smem<T, NMAX, NT>& S, const int n, const int lane)
+{
+    const int e = lane;
+    const bool in = e < n;
+    const double a = S.ta[in ? e : 0];
+    const double bl = (in && e > 0) ? S.tb[e - 1] : 0.0;
+    const double br = (e + 1 < n) ? S.tb[e] : 0.0;
+    const double r = f_abs(bl) + f_abs(br);
+    float hi = in ? float(a + r) : -3e38f, nlo = in ? float(r - a) : -3e38f;
+#define BED_MAX_STAGE(ST) hi = f_max(hi, xmove<ST>(hi, lane)), nlo = f_max(nlo, xmove<ST>(nlo, lane))
+    BED_MAX_STAGE(1);
+    BED_MAX_STAGE(2);
+    BED_MAX_STAGE(4);
+    BED_MAX_STAGE(8);
+    BED_MAX_STAGE(16);
+    BED_MAX_STAGE(32);
+#undef BED_MAX_STAGE
+    const int ex = exp_field(f_max(hi, nlo));
+    const int sh = min(max(fexp<float>::BIAS - 1 - ex, -fexp<float>::SMAX), fexp<float>::SMAX);
+    const double sc = double(fexp<float>::pow2(sh));
+    const int m = direct_order<NT / NMAX>(n);
+    if (e < m) {
+        const double as = in ? a * sc : 4.0, bs = bl * sc, bt = br * sc;
+        S.u.t.ab[0][e][0] = as;
+        S.u.t.ab[0][e][1] = bs * bs;
+        S.u.t.ab[1][m - 1 - e][0] = as;
+        S.u.t.ab[1][m - 1 - e][1] = bt * bt;
+        S.u.t.b[0][e] = bt;
+        S.u.t.b[1][in ? n - 1 - e : e] = in ? bs : 0.0;  // coupling of row e to the row above
+        S.u.t.cell[e] = -2;
+    }
+    if (e == 0) {
+        S.u.t.lo = -double(nlo) * sc - 1e-6;
+        S.u.t.hi = double(hi) * sc + 1e-6;
+        S.u.t.unscale = double(fexp<float>::pow2(-sh));
+        S.u.t.ok = (n >= 2 && ex > fexp<float>::BIAS - 64) ? 1 : 0;
+    }
+}
+
+// Minors of T - x I over `blocks` blocks of eight rows of a table {a, b^2}, p_i =
+// (a_i - x) p_{i-1} - b^2 p_{i-2}: the last two (p1, p0) and the number of sign
+// changes.  |a_i - x| <= 2, so n <= 64 minors stay within 2^64.
+__device__ __forceinline__ int direct_minors(const double* rows, const int blocks, const double x,
+                                             double& p1, double& p0)
+{
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    p0 = 0.0;
+    p1 = 1.0;
+    uint32_t m = 0;  // signs of the minors, the latest in bit 0
+    int c = 0;
+    const d2* row = reinterpret_cast<const d2*>(rows);
+#pragma unroll 1
+    for (int b = 0; b < blocks; ++b) {
+        d2 cur[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) cur[q] = row[q];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const double p2 = fma(cur[q].x - x, p1, -(cur[q].y * p0));
+            m = __builtin_amdgcn_alignbit(m, (uint32_t)__double2hiint(p2), 31);
+            p0 = p1;
+            p1 = p2;
+        }
+        c += __popc((m ^ (m >> 1)) & 0xFFu);
+        row += 8;
+    }
+    return c;
+}
+
+// det(T - x I) and the number of eigenvalues below x.  LPR = 8: the lane and
+// lane ^ 4 share a point x, the first taking the leading minors P of the upper
+// half, the other the trailing minors R of the lower half (rows h ..):
+//   det = P_h R_h - b_{h-1}^2 P_{h-1} R_{h+1},
+// and the count is the inertia of the factorization twisted at row h, whose last
+// pivot has the sign of det / (P_h R_{h+1}).  `tiny`: too small to trust.
+template <int LPR, int NMAX>
+__device__ __forceinline__ double direct_det(const double (*ab)[NMAX][2], const int m, const int sub,
+                                             const double x, int& count, bool& tiny)
+{
+    // both of the last minors near the end of the exponent range (for halves,
+    // of their products)
+    auto vanished = [](const double u, const double v) {
+        const int eu = __double2hiint(u) & 0x7fffffff, ev = __double2hiint(v) & 0x7fffffff;
+        return max(eu, ev) < (1023 - (LPR == 8 ? 480 : 950)) << 20;
+    };
+    double p1, p0;
+    if constexpr (LPR == 4) {
+        count = direct_minors(&ab[0][0][0], m >> 3, x, p1, p0);
+        tiny = vanished(p1, p0);
+        return p1;
+    } else {
+        const bool low = sub >= 4;
+        int c = direct_minors(&ab[low ? 1 : 0][0][0], m >> 4, x, p1, p0);
+        const double bh = ab[0][m >> 1][1];
+        const double q1 = lxor<4>(p1), q0 = lxor<4>(p0);
+        const int oc = lxor<4>(c);
+        const double det = fma(p1, q1, -(bh * (p0 * q0)));
+        const double P = low ? q1 : p1, R = low ? p0 : q0, Rh = low ? p1 : q1;
+        auto neg = [](const double v) { return __double2hiint(v) < 0; };
+        count = c + oc - (neg(Rh) != neg(R) ? 1 : 0) + ((neg(det) != neg(P)) != neg(R) ? 1 : 0);
+        tiny = vanished(p1, p0);
+        return det;
+    }
+}
+
+// Eigenvalues: the team evaluates a grid of NT points first, which brackets
+// every eigenvalue; then each eigenvalue's lanes evaluate four points a round
+// inside its bracket: equally spaced, or, once the bracket holds this
+// eigenvalue alone, around the root of the cubic that interpolates x as a
+// function of det at the last four points, at one and eight times its error.
+// That is taken as its distance from the quadratic's root, or as what the
+// quadratic's distance from the secant's lets expect (the distance alone can
+// vanish by accident where det varies strongly).  A root stops when it is below
+// 2^-44 of the interval and the points enclose this eigenvalue alone (the
+// cubic's own error is then at rounding level).  About four rounds after the grid.
+// With vectors: every gap at least DIRECT_GAP.  Returns whether solved.
+template <typename T, int NMAX, int NT>
+__device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, const int t,
+                                             const bool want_q, T* __restrict__ Lc)
+{
+    constexpr int LPR = NT / NMAX;
+    constexpr int LD = Smem<T, NMAX, NT>::LD;
+    static_assert(LPR == 4 || LPR == 8, "lanes per eigenvalue");
+    const int lane = t & 63;
+    const int m = direct_order<LPR>(n);
+    if (!S.u.t.ok) return false;
+    const int j = t / LPR, sub = t % LPR;
+    const bool act = j < n;
+    bool bad = false;
+    {
+        const double glo = S.u.t.lo, ghi = S.u.t.hi;
+        // grid points: lane pairs of LPR = 8 share one
+        constexpr int NG = LPR == 8 ? NT / 2 : NT;
+        const int gi = LPR == 8 ? (t >> 3) * 4 + (t & 3) : t;
+        const double step = (ghi - glo) * (1.0 / (NG + 1));
+        auto grid = [&](const int i) { return fma(double(i + 1), step, glo); };
+        double lo = glo, hi = ghi;
+        int clo = 0, chi = n;
+        double X[4] = {0.0, 0.0, 0.0, 0.0}, F[4] = {0.0, 0.0, 0.0, 0.0};
+        bool have = false;    // X, F hold four points
+        bool strict = false;  // they enclose this eigenvalue and no other
+        {
+            int c;
+            bool tiny;
+            const double f = direct_det<LPR, NMAX>(S.u.t.ab, m, sub, grid(gi), c, tiny);
+            bad = tiny;
+            if (LPR == 4 || sub < 4) {
+                S.u.t.gf[gi] = f;
+                S.u.t.gc[gi] = c;
+            }
+            team_sync<NT>();
+            if (LPR == 4 || sub < 4) {
+                // eigenvalues between this point and the next (before the first)
+                const int cn = (gi + 1 < NG) ? S.u.t.gc[gi + 1] : n;
+                for (int q = max(c, 0); q < min(cn, n); ++q) S.u.t.cell[q] = gi;
+                if (gi == 0)
+                    for (int q = 0; q < min(c, n); ++q) S.u.t.cell[q] = -1;
+            }
+            team_sync<NT>();
+            const int cell = act ? S.u.t.cell[j] : -2;
+            if (cell >= 0) lo = grid(cell), clo = S.u.t.gc[cell];
+            if (cell >= -1 && cell + 1 < NG) hi = grid(cell + 1), chi = S.u.t.gc[cell + 1];
+            const int k0 = min(max(cell - 1, 0), NG - 4);
+            have = cell >= -1;
+            {
+                const int ca = S.u.t.gc[k0], cb = S.u.t.gc[k0 + 3];
+                strict = ca == j && cb == j + 1;
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                X[q] = grid(k0 + q);
+                F[q] = S.u.t.gf[k0 + q];
+            }
+        }
+        const int pt = sub & 3;
+        const double spread = pt == 0 ? -8.0 : (pt == 1 ? -1.0 : (pt == 2 ? 1.0 : 8.0));
+        const double even = double(pt + 1) * 0.2, fl = double(pt + 1) * 0x1p-9, fh = double(4 - pt) * -0x1p-9;
+        double lam = 0.0;
+        bool done = !act;
+        int rounds = 0;
+        for (;;) {
+            const double w = hi - lo;
+            // inverse interpolation at det = 0 (Neville), offsets from X[1]
+            double est = fma(0.5, w, lo), err = w;
+            {
+                const double x2 = X[2] - X[1], x0 = X[0] - X[1], x3 = X[3] - X[1];
+                auto comb = [](const double pa, const double pb, const double fa, const double fb) {
+                    return fma(pb - pa, fa * __builtin_amdgcn_rcp(fa - fb), pa);
+                };
+                const double a0 = x2 * (F[1] * __builtin_amdgcn_rcp(F[1] - F[2]));
+                const double a1 = comb(x2, x0, F[2], F[0]);
+                const double a2 = comb(x0, x3, F[0], F[3]);
+                const double b0 = comb(a0, a1, F[1], F[0]);
+                const double b1 = comb(a1, a2, F[2], F[3]);
+                const double c0 = comb(b0, b1, F[1], F[3]);
+                const double e = X[1] + c0;
+                // (comparisons are false for a NaN)
+                const bool in = have && chi - clo == 1 && e >= lo && e <= hi;
+                est = in ? e : est;
+                const double d = b0 - a0;
+                err = in ? f_max(f_max(f_abs(c0 - b0), d * d * __builtin_amdgcn_rcp(f_abs(x2))), 0x1p-53) : w;
+            }
+            const bool stop = !(w > 0x1p-51) || (strict && err <= 0x1p-44);
+            lam = done ? lam : est;
+            done = done || stop;
+            if (rounds >= DIRECT_CAP) {
+                bad = bad || !done;
+                done = true;
+            }
+            if (!__ballot(!done)) break;  // Eq. (22): converged lanes idle till here
+            // points in ascending order over the lanes
+            const double xn = fmin(fmax(fma(err, spread, est), fma(w, fl, lo)), fma(w, fh, hi));
+            const double x = err < 0.25 * w ? xn : fma(w, even, lo);
+            int c;
+            bool tiny;
+            const double f = direct_det<LPR, NMAX>(S.u.t.ab, m, sub, x, c, tiny);
+            bad = bad || (tiny && !done);
+            int C[4];
+            bool Bl[4];
+            auto gather = [&](auto Q, const double v) {
+                constexpr int q = decltype(Q)::value;
+                return dpp_move64<q * 0x55>(v);  // quad_perm [q, q, q, q]
+            };
+            static_for<0, 4>([&](auto Q) {
+                constexpr int q = decltype(Q)::value;
+                X[q] = gather(Q, x);
+                F[q] = gather(Q, f);
+                C[q] = __builtin_amdgcn_mov_dpp(c, q * 0x55, 0xF, 0xF, false);
+                Bl[q] = C[q] <= j;
+            });
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                lo = Bl[q] ? X[q] : lo;
+                clo = Bl[q] ? C[q] : clo;
+                hi = Bl[3 - q] ? hi : X[3 - q];
+                chi = Bl[3 - q] ? chi : C[3 - q];
+            }
+            have = true;
+            strict = C[0] == j && C[3] == j + 1;
+            ++rounds;
+        }
+        if (act && sub == 0) {
+            S.u.t.lam[j] = lam;
+            Lc[j] = T(lam * S.u.t.unscale);
+        }
+    }
+    if (__ballot(bad) && lane == 0) S.u.t.ok = 0;
+    team_sync<NT>();
+    BED_PHASE(3);
+    if (want_q && t < 64) {
+        const double gap = t + 1 < n ? S.u.t.lam[t + 1 < n ? t + 1 : 0] - S.u.t.lam[t < n ? t : 0] : 1.0;
+        const uint64_t close = __ballot(!(gap >= DIRECT_CLOSE));
+        if (lane == 0) S.u.t.close = close;
+        if (__ballot(!(gap >= DIRECT_GAP)) != 0 || __popcll(close) > DIRECT_MOST) S.u.t.ok = 0;
+    }
+    team_sync<NT>();
+    if (!S.u.t.ok) return false;
+    if (!want_q) return true;
+
+    // Factors of T - lambda I from the top (L D L^T) and from the bottom (U D
+    // U^T), one lane each per eigenvalue: l_i = b / D_i toward the next row,
+    // rounded to T (a relative perturbation of the vector's entries).  A zero
+    // pivot becomes 1e-25, far below the rounding of T.
+    if (t < 2 * NMAX) {
+        const int e = t % NMAX;
+        const bool up = t / NMAX != 0;
+        if (e < n) {
+            const double x = S.u.t.lam[e];
+            const double* ar = &S.u.t.ab[up ? 1 : 0][up ? m - n : 0][0];
+            const double* br = &S.u.t.b[up ? 1 : 0][0];
+            T* L = up ? S.Q1 + (n - 1) * LD + e : S.Q0 + e;
+            const int dL = up ? -LD : LD;
+            double bp = 0.0, l = 0.0;
+#pragma unroll 4
+            for (int k = 0; k < n; ++k) {
+                const double bn = br[k];
+                double D = fma(-bp, l, ar[2 * k] - x);
+                D = f_abs(D) < 1e-25 ? 1e-25 : D;
+                double r = __builtin_amdgcn_rcp(D);
+                r = fma(r, fma(-D, r, 1.0), r);
+                r = fma(r, fma(-D, r, 1.0), r);
+                l = bn * r;
+                *L = T(l);
+                L += dL;
+                bp = bn;
+            }
+        }
+    }
+    team_sync<NT>();
+    BED_PHASE(6);
+    // Twist at the row of smallest |gamma_i| = |e_i^T (T - lambda)^{-1} e_i|^{-1},
+    // z = 1 there, and products of -l outward; rows of a group's lane are
+    // consecutive, its products are finished by a scan over the group.
+    {
+        constexpr int SG = NMAX / LPR;
+        const int e = act ? j : 0;
+        const double x = S.u.t.lam[e];
+        const T* Lp = S.Q0 + e;  // toward the row below
+        const T* Lm = S.Q1 + e;  // toward the row above
+        const int i0 = sub * SG;
+        T lp[SG], lm[SG];
+#pragma unroll
+        for (int s = 0; s < SG; ++s) {
+            const int i = min(i0 + s, n - 1);
+            lp[s] = Lp[i * LD];
+            lm[s] = Lm[i * LD];
+        }
+        T best = T(3e38);
+        int r = 0;
+        {
+            const int ia = min(max(i0 - 1, 0), n - 1);
+            T lprev = Lp[ia * LD];  // of the row before
+            T bprev = i0 > 0 ? T(S.u.t.b[0][ia]) : T(0);
+            const T lafter = Lm[min(i0 + SG, n - 1) * LD];
+#pragma unroll
+            for (int s = 0; s < SG; ++s) {
+                const int i = i0 + s;
+                const int ic = min(i, n - 1);
+                const T bn = T(S.u.t.b[0][ic]);  // zero at the last row
+                const T d = T(S.u.t.ab[0][ic][0] - x);
+                const T ln = s + 1 < SG ? lm[s + 1 < SG ? s + 1 : 0] : lafter;
+                const T ag = f_abs(fma(-bprev, lprev, fma(-bn, ln, d)));
+                const bool take = i < n && ag < best;
+                r = take ? i : r;
+                best = take ? ag : best;
+                lprev = lp[s];
+                bprev = bn;
+            }
+        }
+        auto least = [&](const T ob, const int orr) {
+            const bool take = ob < best || (ob == best && orr < r);
+            best = take ? ob : best;
+            r = take ? orr : r;
+        };
+        least(xmove<1>(best, lane), xmove<1>(r, lane));
+        least(xmove<2>(best, lane), xmove<2>(r, lane));
+        if constexpr (LPR == 8) least(xmove<4>(best, lane), xmove<4>(r, lane));
+        double z[SG];
+        double n2 = 0.0;
+        // second pass: from the largest entry, where the first twist row was
+        // much smaller (gamma is only known to binary32 rounding)
+        for (int pass = 0; pass < 2; ++pass) {
+            // products within the lane, from its last row up to the twist and
+            // from its first row down, one where the twist does not lie beyond
+            double up = 1.0, dn = 1.0;
+#pragma unroll
+            for (int s = SG - 1; s >= 0; --s) {
+                const bool above = i0 + s < r;
+                up = above ? -up * double(lp[s]) : 1.0;
+                z[s] = up;
+            }
+#pragma unroll
+            for (int s = 0; s < SG; ++s) {
+                const int i = i0 + s;
+                dn = i > r ? -dn * double(i < n ? lm[s] : T(0)) : 1.0;
+                z[s] = i > r ? dn : z[s];
+            }
+            // products of the lanes below (up) and above (dn) in the group
+            double cu = 1.0, cd = 1.0;
+#pragma unroll
+            for (int q = 1; q < LPR; ++q) {
+                const double ou = __shfl(up, lane + q), od = __shfl(dn, lane - q);
+                cu *= sub + q < LPR ? ou : 1.0;
+                cd *= sub - q >= 0 ? od : 1.0;
+            }
+            n2 = 0.0;
+            double zb = 0.0;
+            int ri = 0;
+#pragma unroll
+            for (int s = 0; s < SG; ++s) {
+                const int i = i0 + s;
+                z[s] *= i < r ? cu : (i > r ? cd : 1.0);
+                n2 = fma(z[s], z[s], n2);
+                const double az = f_abs(z[s]);
+                ri = az > zb ? i : ri;
+                zb = f_max(zb, az);
+            }
+            n2 = group_sum<LPR>(n2, lane);
+            const bool far = act && zb > 8.0;
+            if (!__ballot(far)) break;
+            auto most = [&](const double ob, const int orr) {
+                const bool take = ob > zb || (ob == zb && orr < ri);
+                zb = take ? ob : zb;
+                ri = take ? orr : ri;
+            };
+            most(xmove<1>(zb, lane), xmove<1>(ri, lane));
+            most(xmove<2>(zb, lane), xmove<2>(ri, lane));
+            if constexpr (LPR == 8) most(xmove<4>(zb, lane), xmove<4>(ri, lane));
+            r = zb > 8.0 ? ri : r;
+        }
+        const double sc = d_rsqrt_nr(n2);
+        wave_sync();
+        if (act) {
+#pragma unroll
+            for (int s = 0; s < SG; ++s)
+                if (i0 + s < n) S.Q0[(i0 + s) * LD + e] = T(z[s] * sc);
+        }
+    }
+    team_sync<NT>();
+    if (S.u.t.close) {
+        // Gram-Schmidt along each run of close eigenvalues (one row per lane)
+        if (t < 64) {
+            T* row = S.Q0 + (lane < n ? lane : 0) * LD;
+            int first = 0;  // of the current run
+            uint64_t todo = S.u.t.close;
+            int last = -2;
+            while (todo) {
+                const int j = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                first = j == last + 1 ? first : j;
+                last = j;
+                double v = lane < n ? double(row[j + 1]) : 0.0;
+                for (int q = first; q <= j; ++q) {
+                    const double u = lane < n ? double(row[q]) : 0.0;
+                    v = fma(-wave_sum_all(u * v), u, v);
+                }
+                v *= d_rsqrt_nr(wave_sum_all(v * v));
+                if (lane < n) row[j + 1] = T(v);
+                wave_sync();
+            }
+        }
+        team_sync<NT>();
+    }
+    BED_PHASE(7);
+    return true;
 }
 
 // TRI: the input is already tridiagonal, given as its diagonal a (n values)
@@ -1331,20 +1807,18 @@ template <typename T, int NMAX, int NT, bool TRI = false>
 __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int n,
                                            T* __restrict__ lam_out, T* __restrict__ Q_out,
                                            int* __restrict__ info_out, Smem<T, NMAX, NT>& S,
-                                           const int t, const int leaf = 4,
+                                           const int t, const int leaf_arg = 0,
                                            T* __restrict__ ends_out = nullptr)
 {
     static_assert(NMAX <= 64 && (NMAX & (NMAX - 1)) == 0, "NMAX: power of two <= 64");
     static_assert(NT % 64 == 0 && NT >= NMAX && NT % NMAX == 0, "team geometry");
     constexpr int LD = Smem<T, NMAX, NT>::LD;
     constexpr int NW = NT / 64;
-    constexpr int G = NT / NMAX;
-    constexpr int CPT = NMAX / G;
     constexpr int LPR = NT / NMAX;
     const int lane = t & 63;
     const int wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int r = t % NMAX, g = t / NMAX;
     const T u = fp<T>::u;
+    const int leaf = leaf_arg > 0 ? leaf_arg : leaf_default(NMAX);
 
     BED_PHASE(0);
     // ------------------------------------------------------------ load
@@ -1438,10 +1912,11 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
         if (qh_wave)
             for (; qj < n - 2; ++qj) qh_apply<T, NMAX, NT>(S, lane, qj, qh);
     }
-    // The staging buffer becomes the merge matrix M: clear it so that entries
-    // outside every node block (never written by a merge) are zero -- the MFMA
-    // back-multiplication reads them against zero A entries.
-    for (int e = t; e < NMAX * LD; e += NT) S.M[e] = T(0);
+    constexpr bool DIRECT = std::is_same<T, float>::value && !TRI && LPR >= 4;
+    const bool direct = DIRECT && leaf_arg == 0;
+    if constexpr (DIRECT) {
+        if (direct && wave == 0) direct_setup(S, n, lane);
+    }
     team_sync<NT>();
     if constexpr (AW > 0 && !TRI) {
         // every reflector has been read: Q_H replaces them
@@ -1464,13 +1939,30 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
     }
     BED_PHASE(2);
 
-    // ------------------------------------------------------------ tear + leaves
-    int D = 0;  // depth of the smallest leaves
-    while (((n + (1 << D) - 1) >> D) > leaf) ++D;
     T* Qc = S.Q0;
     T* Qn = S.Q1;
     T* Lc = S.lam0;
     T* Ln = S.lam1;
+    // the direct solver takes the matrix unless its spectrum is too close
+    bool solved = false;
+    if constexpr (DIRECT) {
+        if (direct) solved = direct_solve(S, n, t, Q_out != nullptr, Lc);
+    }
+    if (!solved) {
+    // ------------------------------------------------------------ tear + leaves
+    // The staging buffer becomes the merge matrix M: clear it so that entries
+    // outside every node block (never written by a merge) are zero -- the MFMA
+    // back-multiplication reads them against zero A entries.
+    for (int e = t; e < NMAX * LD; e += NT) S.M[e] = T(0);
+    if constexpr (!TRI) {  // T in the storage type
+        for (int e = t; e < n; e += NT) {
+            S.a[e] = T(S.ta[e]);
+            S.b[e] = T(e + 1 < n ? S.tb[e] : 0.0);
+        }
+    }
+    team_sync<NT>();
+    int D = 0;  // depth of the smallest leaves
+    while (((n + (1 << D) - 1) >> D) > leaf) ++D;
     if (wave == 0) {
         const int e = lane;
         T ae = (e < n) ? S.a[e] : T(0);
@@ -1766,6 +2258,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
         BED_PHASE(10 + 8 * d + 5);
         T* tq = Qc; Qc = Qn; Qn = tq;
         T* tl = Lc; Lc = Ln; Ln = tl;
+    }
     }
 
     if (!Q_out) {  // eigenvalues only

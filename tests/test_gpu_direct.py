@@ -1,0 +1,97 @@
+"""The direct spectral solver (binary32, default schedule): eigenvalues by
+sections and secants of the determinant, eigenvectors by twisted
+factorizations, against the binary64 oracle -- at the edges of its blocks of
+eight rows and of the team shapes, on split and degenerate spectra that it
+hands to the divide step, and at eigenvalue distances around that line."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_27325_amd import workloads
+from tests.parity import compare_batch
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2604_27325_amd as bed  # noqa: E402
+
+
+def reference(A):
+    """The oracle; LAPACK for a matrix whose oracle vectors are not orthonormal
+    (it loses them on the all-ones matrix of order 32)."""
+    lam, Q, _ = oracle.syevd(A)
+    for b in range(A.shape[0]):
+        if np.linalg.norm(Q[b].T @ Q[b] - np.eye(A.shape[1])) > 1e-10:
+            lam[b], Q[b] = np.linalg.eigh(A[b])
+    return lam, Q
+
+
+def check(A_np, label, tune=None):
+    A_np = np.ascontiguousarray(A_np, dtype=np.float32)
+    b, n = A_np.shape[0], A_np.shape[1]
+    print(f"[{label}] batch {b} n={n}", flush=True)
+    A = torch.from_numpy(A_np).cuda()
+    lam = torch.empty(b * n, device="cuda")
+    Q = torch.empty(b * n * n, device="cuda")
+    info = torch.empty(b, dtype=torch.int32, device="cuda")
+    bed.Plan(torch.float32, [n] * b, tune=tune).run(A.view(-1), lam, Q, info)
+    vals = bed.syevals(A)
+    torch.cuda.synchronize()
+    lam_o, Q_o = reference(A_np.astype(np.float64))
+    worst, fails = compare_batch(A_np, lam.view(b, n).cpu().numpy(),
+                                 Q.view(b, n, n).cpu().numpy(), lam_o, Q_o, np.float32,
+                                 info=info.cpu().numpy())
+    print(f"  worst {worst}", flush=True)
+    assert not fails, f"{label}: {len(fails)} failing, first {fails[:2]}"
+    nrm = np.abs(lam_o).max(axis=1).clip(1e-300)
+    err = np.abs(vals.cpu().numpy() - lam_o).max(axis=1) / nrm
+    assert err.max() <= 1e-5, f"{label}: eigenvalues only {err.max()}"
+
+
+@pytest.mark.parametrize("n", [1, 2, 3, 7, 8, 9, 15, 16, 17, 24, 25, 31, 32, 33, 40, 41, 48, 49, 63, 64])
+def test_sizes(n):
+    rng = np.random.default_rng(9000 + n)
+    check(np.concatenate([workloads.gaussian_sym(rng, 6, n), workloads.covariance(rng, 6, n)]),
+          f"sizes n={n}")
+
+
+@pytest.mark.parametrize("n", [5, 16, 27, 32, 50, 64])
+@pytest.mark.parametrize("mid,big", [(256, 256), (128, 512)])
+def test_split_and_degenerate_spectra(n, mid, big):
+    """Diagonal, zero, identity, block-diagonal, rank-deficient and graded
+    matrices, a Wilkinson matrix and two glued copies of it, tridiagonal
+    Toeplitz (both coupling signs)."""
+    rng = np.random.default_rng(9100 + n)
+    off = np.ones(n - 1)
+    wil = np.diag(np.abs(np.arange(n) - (n - 1) / 2.0)) + np.diag(off, 1) + np.diag(off, -1)
+    glued = wil.copy()
+    h = n // 2
+    glued[h - 1, h] = glued[h, h - 1] = 1e-7
+    blk = workloads.gaussian_sym(rng, 1, n)[0]
+    blk[:h, h:] = blk[h:, :h] = 0.0
+    u = rng.standard_normal((n, 2))
+    V, _ = np.linalg.qr(rng.standard_normal((n, n)))
+    graded = (V * 10.0 ** -np.linspace(0, 6, n)) @ V.T
+    mats = [np.diag(np.arange(n) - 2.0), np.zeros((n, n)), np.eye(n) * 3.0, blk, u @ u.T,
+            0.5 * (graded + graded.T), wil, glued,
+            2 * np.eye(n) + 0.5 * (np.diag(off, 1) + np.diag(off, -1)),
+            np.diag(off, 1) * -1.0 + np.diag(off, -1) * -1.0, np.ones((n, n))]
+    check(np.stack(mats), f"degenerate n={n}", tune={"threads_mid": mid, "threads_big": big})
+
+
+@pytest.mark.parametrize("gap", [1e-5, 1e-6, 1e-7, 1e-8, 4e-9, 1e-9, 1e-11])
+@pytest.mark.parametrize("n", [16, 32, 64])
+def test_close_pairs(n, gap):
+    """A 2 x 2 block whose eigenvalues differ by 2 gap, decoupled from the rest
+    up to a permutation (so that the stored binary32 matrix keeps the gap)."""
+    rng = np.random.default_rng(9200 + n)
+    A = workloads.gaussian_sym(rng, 8, n) / np.sqrt(n)
+    p, q = n // 3, n // 2
+    for M in A:
+        M[[p, q], :] = 0.0
+        M[:, [p, q]] = 0.0
+        M[p, p] = M[q, q] = 0.25
+        M[p, q] = M[q, p] = gap
+    check(A, f"pair {gap} n={n}")
