@@ -48,6 +48,12 @@ bool team_supported(bed_dtype dt, TeamShape ts);
 hipError_t launch_uniform(bed_dtype dt, TeamShape ts, const void *A, int n, int64_t batch,
                           void *lam, void *Q, int32_t *info, hipStream_t s);
 
+// Uniform batch of order n <= SMALL_MAX: one lane per matrix (launch_uniform's
+// choice where no cutoff of the divide step is asked for).
+constexpr int SMALL_MAX = 4;
+hipError_t launch_small(bed_dtype dt, const void *A, int n, int64_t batch, void *lam, void *Q,
+                        int32_t *info, hipStream_t s);
+
 // Uniform batch of binary32 tridiagonal matrices (diagonal then off-diagonal,
 // 2n values apart); team shapes (32, 128), (32, 256) and (64, 256).  With Q == nullptr
 // (eigenvalues only) ends, if not null, receives each matrix's first and last

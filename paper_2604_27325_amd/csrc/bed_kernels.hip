@@ -38,6 +38,7 @@ hipError_t launch_uniform(bed_dtype dt, TeamShape ts, const void *A, int n, int6
                           void *lam, void *Q, int32_t *info, hipStream_t s)
 {
     if (batch <= 0) return hipSuccess;
+    if (n <= SMALL_MAX && ts.leaf == 0) return launch_small(dt, A, n, batch, lam, Q, info, s);
     return dt == BED_F32 ? uniform_t<float>(ts, A, n, batch, lam, Q, info, s)
                          : uniform_t<double>(ts, A, n, batch, lam, Q, info, s);
 }
