@@ -77,6 +77,11 @@ def load_library():
                                        ctypes.c_double, vp, vp]
     lib.bed_spectral_backward.argtypes = [ctypes.c_int, i64, i32p, vp, vp, ctypes.c_int32,
                                           ctypes.c_double, vp, vp, vp]
+    # uniform batches by their size alone (no array of equal sizes)
+    i32, f64 = ctypes.c_int32, ctypes.c_double
+    lib.bedi_solve_uniform.argtypes = [ctypes.c_int, i64, i32, vp, vp, vp, vp, i32, vp]
+    lib.bedi_backward_uniform.argtypes = [ctypes.c_int, i64, i32, vp, vp, vp, vp, vp, f64, vp]
+    lib.bedi_spectral_uniform.argtypes = [ctypes.c_int, i64, i32, vp, vp, i32, f64, i32, vp, vp, vp]
     lib.bed_tune_set.argtypes = [ctypes.c_int, i64, i32p, ctypes.POINTER(Tune)]
     lib.bed_cache_entries.restype = ctypes.c_int32
     lib.bed_syevd_backward.argtypes = [ctypes.c_int, i64, i32p, vp, vp, vp, vp, vp,
@@ -164,6 +169,22 @@ def syevd_noalloc_packed(n_list, A, lam, Q, info=None, stream=None):
                                  _stream_ptr(stream)))
 
 
+def _solve_uniform(A, stream, want_vectors, want_info):
+    """(lam, Q or None, info or None) of a contiguous (batch, n, n) tensor."""
+    import torch
+    lib = load_library()
+    b, n = A.shape[0], A.shape[1]
+    dt = _dtype_code(A.dtype)
+    lam = torch.empty(b, n, dtype=A.dtype, device=A.device)
+    Q = torch.empty(b, n, n, dtype=A.dtype, device=A.device) if want_vectors else None
+    info = torch.empty(b, dtype=torch.int32, device=A.device) if want_info else None
+    _check(lib.bedi_solve_uniform(dt, b, n, _dev(A, "A"), _dev(lam, "lambda"),
+                                  _dev(Q, "Q") if want_vectors else None,
+                                  _dev(info, "info") if want_info else None, int(want_vectors),
+                                  _stream_ptr(stream)))
+    return lam, Q, info
+
+
 def syevd(A, return_info=False, stream=None):
     """Eigen-decomposition of a (batch, n, n) or (n, n) symmetric GPU tensor
     (lower triangle read).  Returns (lam ascending, Q) [, info]."""
@@ -171,22 +192,25 @@ def syevd(A, return_info=False, stream=None):
     Ab = A.unsqueeze(0) if single else A
     if Ab.dim() != 3 or Ab.shape[1] != Ab.shape[2]:
         raise ValueError("A must be (batch, n, n) or (n, n)")
-    Ab = Ab.contiguous()
-    b, n = Ab.shape[0], Ab.shape[1]
-    lam, Q, info = syevd_packed([n] * b, Ab.view(-1), stream=stream)
-    lam, Q = lam.view(b, n), Q.view(b, n, n)
+    lam, Q, info = _solve_uniform(Ab.contiguous(), stream, True, return_info)
     if single:
-        lam, Q, info = lam[0], Q[0], info[0]
+        lam, Q, info = lam[0], Q[0], (info[0] if return_info else None)
     return (lam, Q, info) if return_info else (lam, Q)
 
 
 def syevals(A, stream=None):
     """Eigenvalues only of a (batch, n, n) symmetric GPU tensor."""
     Ab = (A.unsqueeze(0) if A.dim() == 2 else A).contiguous()
-    b, n = Ab.shape[0], Ab.shape[1]
-    lam, _, info = syevd_packed([n] * b, Ab.view(-1), stream=stream, want_vectors=False)
-    lam = lam.view(b, n)
+    if Ab.numel() != Ab.shape[0] * Ab.shape[1] * Ab.shape[1]:
+        raise ValueError(f"A has {Ab.numel()} elements, packed sizes need "
+                         f"{Ab.shape[0] * Ab.shape[1] * Ab.shape[1]}")
+    lam, _, _ = _solve_uniform(Ab, stream, False, False)
     return lam[0] if A.dim() == 2 else lam
+
+
+def _uniform_shape(lam):
+    """(batch, n) of the eigenvalues of a uniform batch (or of one matrix)."""
+    return (lam.shape[0] if lam.dim() == 2 else 1), lam.shape[-1]
 
 
 def syevd_backward(lam, Q, dlam=None, dQ=None, eps=0.0, n_list=None, stream=None, out=None):
@@ -194,21 +218,21 @@ def syevd_backward(lam, Q, dlam=None, dQ=None, eps=0.0, n_list=None, stream=None
     or flat packed tensors with n_list).  `out` (Q's shape) receives dA."""
     import torch
     lib = load_library()
-    if n_list is None:
-        b, n = lam.shape[-2] if lam.dim() == 2 else 1, lam.shape[-1]
-        n_list = [n] * b
-    n_arr, n_ptr = _n_array(n_list)
     lam_c, Q_c = lam.contiguous(), Q.contiguous()
     dl = dlam.contiguous() if dlam is not None else None
     dq = dQ.contiguous() if dQ is not None else None
     dA = torch.empty_like(Q_c) if out is None else out
     if dA.shape != Q_c.shape or dA.dtype != Q_c.dtype:
         raise ValueError("out must have Q's shape and dtype")
-    _check(lib.bed_syevd_backward(
-        _dtype_code(Q.dtype), len(n_arr), n_ptr, _dev(lam_c, "lambda"), _dev(Q_c, "Q"),
-        _dev(dl, "dlambda") if dl is not None else None,
-        _dev(dq, "dQ") if dq is not None else None, _dev(dA, "dA"), float(eps),
-        _stream_ptr(stream)))
+    dt = _dtype_code(Q.dtype)
+    args = (_dev(lam_c, "lambda"), _dev(Q_c, "Q"), _dev(dl, "dlambda") if dl is not None else None,
+            _dev(dq, "dQ") if dq is not None else None, _dev(dA, "dA"), float(eps),
+            _stream_ptr(stream))
+    if n_list is None:
+        _check(lib.bedi_backward_uniform(dt, *_uniform_shape(lam), *args))
+    else:
+        n_arr, n_ptr = _n_array(n_list)
+        _check(lib.bed_syevd_backward(dt, len(n_arr), n_ptr, *args))
     return dA
 
 
@@ -221,24 +245,21 @@ def _fn_code(fn):
     return FUNCTIONS[fn]
 
 
-def _batch_shape(lam, Q, n_list):
-    if n_list is None:
-        b, n = (lam.shape[0] if lam.dim() == 2 else 1), lam.shape[-1]
-        n_list = [n] * b
-    return n_list
-
-
 def spectral_apply(lam, Q, fn, p=0.0, n_list=None, stream=None, out=None):
     """F = Q f(Lambda) Q^T for a decomposition (uniform (batch, n[, n]) tensors,
     or flat packed tensors with n_list); fn in sqrt, invsqrt, exp, log, pow."""
     import torch
     lib = load_library()
-    n_arr, n_ptr = _n_array(_batch_shape(lam, Q, n_list))
     lam_c, Q_c = lam.contiguous(), Q.contiguous()
     F = torch.empty_like(Q_c) if out is None else out
-    _check(lib.bed_spectral_apply(_dtype_code(Q.dtype), len(n_arr), n_ptr, _dev(lam_c, "lambda"),
-                                  _dev(Q_c, "Q"), _fn_code(fn), float(p), _dev(F, "F"),
-                                  _stream_ptr(stream)))
+    dt = _dtype_code(Q.dtype)
+    ptrs, tail = (_dev(lam_c, "lambda"), _dev(Q_c, "Q"), _fn_code(fn), float(p)), _stream_ptr(stream)
+    if n_list is None:
+        _check(lib.bedi_spectral_uniform(dt, *_uniform_shape(lam), *ptrs, 0, None, _dev(F, "F"),
+                                         tail))
+    else:
+        n_arr, n_ptr = _n_array(n_list)
+        _check(lib.bed_spectral_apply(dt, len(n_arr), n_ptr, *ptrs, _dev(F, "F"), tail))
     return F
 
 
@@ -246,13 +267,17 @@ def spectral_backward(lam, Q, dF, fn, p=0.0, n_list=None, stream=None, out=None)
     """dA = Q (K o Q^T sym(dF) Q) Q^T, K the divided differences of f."""
     import torch
     lib = load_library()
-    n_arr, n_ptr = _n_array(_batch_shape(lam, Q, n_list))
     lam_c, Q_c, dF_c = lam.contiguous(), Q.contiguous(), dF.contiguous()
     dA = torch.empty_like(Q_c) if out is None else out
-    _check(lib.bed_spectral_backward(_dtype_code(Q.dtype), len(n_arr), n_ptr,
-                                     _dev(lam_c, "lambda"), _dev(Q_c, "Q"), _fn_code(fn),
-                                     float(p), _dev(dF_c, "dF"), _dev(dA, "dA"),
-                                     _stream_ptr(stream)))
+    dt = _dtype_code(Q.dtype)
+    ptrs, tail = (_dev(lam_c, "lambda"), _dev(Q_c, "Q"), _fn_code(fn), float(p)), _stream_ptr(stream)
+    if n_list is None:
+        _check(lib.bedi_spectral_uniform(dt, *_uniform_shape(lam), *ptrs, 1, _dev(dF_c, "dF"),
+                                         _dev(dA, "dA"), tail))
+    else:
+        n_arr, n_ptr = _n_array(n_list)
+        _check(lib.bed_spectral_backward(dt, len(n_arr), n_ptr, *ptrs, _dev(dF_c, "dF"),
+                                         _dev(dA, "dA"), tail))
     return dA
 
 

@@ -95,14 +95,12 @@ bed_status with_worklist(bed_dtype dt, int64_t batch, const int32_t *n, hipStrea
 }
 }  // namespace bed
 
-extern "C" bed_status bed_syevd_backward(bed_dtype dt, int64_t batch, const int32_t *n,
-                                         const void *lambda, const void *Q, const void *dlambda,
-                                         const void *dQ, void *dA, double degeneracy_eps,
-                                         void *stream)
+// n == nullptr: `batch` matrices of order n0
+static bed_status backward(bed_dtype dt, int64_t batch, const int32_t *n, int32_t n0,
+                           const void *lambda, const void *Q, const void *dlambda, const void *dQ,
+                           void *dA, double degeneracy_eps, void *stream)
 {
-    bed_status st = check_sizes(dt, batch, n);
-    if (st != BED_OK) return st;
-    if (batch == 0) return BED_OK;
+    bed_status st;
     if ((st = check_ptr(lambda, dt, "lambda", false)) != BED_OK) return st;
     if ((st = check_ptr(Q, dt, "Q", false)) != BED_OK) return st;
     if ((st = check_ptr(dlambda, dt, "dlambda", true)) != BED_OK) return st;
@@ -111,13 +109,33 @@ extern "C" bed_status bed_syevd_backward(bed_dtype dt, int64_t batch, const int3
     const double eps = degeneracy_eps > 0 ? degeneracy_eps
                                           : 1e3 * (dt == BED_F32 ? 0x1p-24 : 0x1p-53);
     hipStream_t s = (hipStream_t)stream;
-    const bool uniform = std::all_of(n, n + batch, [&](int32_t v) { return v == n[0]; });
-    if (uniform) {
-        hipError_t e = launch_backward_uniform(dt, n[0], lambda, Q, dlambda, dQ, dA, n[0], batch,
-                                               eps, s);
+    if (!n || all_equal(batch, n)) {
+        const int32_t nu = n ? n[0] : n0;
+        hipError_t e = launch_backward_uniform(dt, nu, lambda, Q, dlambda, dQ, dA, nu, batch, eps, s);
         return e == hipSuccess ? BED_OK : hip_fail(e, "backward launch");
     }
     return with_worklist(dt, batch, n, s, [&](const WorkItem *items, int count, int nmax) {
         return launch_backward(dt, nmax, lambda, Q, dlambda, dQ, dA, items, count, eps, s);
     });
+}
+
+extern "C" bed_status bed_syevd_backward(bed_dtype dt, int64_t batch, const int32_t *n,
+                                         const void *lambda, const void *Q, const void *dlambda,
+                                         const void *dQ, void *dA, double degeneracy_eps,
+                                         void *stream)
+{
+    const bed_status st = check_sizes(dt, batch, n);
+    if (st != BED_OK || batch == 0) return st;
+    return backward(dt, batch, n, 0, lambda, Q, dlambda, dQ, dA, degeneracy_eps, stream);
+}
+
+// As bedi_solve_uniform: a uniform batch by its size alone, for the Python binding.
+extern "C" bed_status bedi_backward_uniform(bed_dtype dt, int64_t batch, int32_t n,
+                                            const void *lambda, const void *Q,
+                                            const void *dlambda, const void *dQ, void *dA,
+                                            double degeneracy_eps, void *stream)
+{
+    const bed_status st = check_uniform(dt, batch, n);
+    if (st != BED_OK || batch == 0) return st;
+    return backward(dt, batch, nullptr, n, lambda, Q, dlambda, dQ, dA, degeneracy_eps, stream);
 }

@@ -14,6 +14,10 @@ namespace bed {
 bed_status fail(bed_status st, const char *fmt, ...);
 bed_status hip_fail(hipError_t e, const char *what);
 size_t dtype_size(bed_dtype dt);
+// Whether all sizes are equal (one pass of memcmp).
+bool all_equal(int64_t batch, const int32_t *n);
+// check_sizes of `batch` matrices of order n.
+bed_status check_uniform(bed_dtype dt, int64_t batch, int32_t n, int nmax = 64);
 bed_status check_sizes(bed_dtype dt, int64_t batch, const int32_t *n, int nmax = 64);
 bed_status check_ptr(const void *p, bed_dtype dt, const char *name, bool nullable);
 bool stream_capturing(hipStream_t s);
@@ -25,6 +29,7 @@ bed_tune default_tune();
 // Autotuner cache lookup: the stored schedule for this (arch, dtype, size mix)
 // or the default one.  Never launches work.
 bed_tune tuned_or_default(bed_dtype dt, int64_t batch, const int32_t *n);
+bed_tune tuned_or_default_uniform(bed_dtype dt, int64_t batch, int32_t n);
 
 bed_status plan_run_impl(const bed_plan *p, const void *A, void *lam, void *Q, int32_t *info,
                          hipStream_t s);

@@ -194,12 +194,12 @@ static hipError_t spectral_launch(bed_dtype dt, bool bwd, int nmax, const void *
                : spectral_t<double, false>(nmax, lam, Q, in, out, n, count, items, fn, p, s);
 }
 
-static bed_status spectral(bed_dtype dt, bool bwd, int64_t batch, const int32_t *n,
+// n == nullptr: `batch` matrices of order n0
+static bed_status spectral(bed_dtype dt, bool bwd, int64_t batch, const int32_t *n, int32_t n0,
                            const void *lam, const void *Q, int32_t fn, double param,
                            const void *in, void *out, void *stream)
 {
-    bed_status st = check_sizes(dt, batch, n);
-    if (st != BED_OK) return st;
+    bed_status st;
     if (fn < BED_FN_SQRT || fn > BED_FN_POW) return fail(BED_ERR_INVALID_ARG, "unknown function %d", fn);
     if (batch == 0) return BED_OK;
     if ((st = check_ptr(lam, dt, "lambda", false)) != BED_OK) return st;
@@ -207,10 +207,9 @@ static bed_status spectral(bed_dtype dt, bool bwd, int64_t batch, const int32_t 
     if (bwd && (st = check_ptr(in, dt, "dF", false)) != BED_OK) return st;
     if ((st = check_ptr(out, dt, bwd ? "dA" : "F", false)) != BED_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const bool uniform = std::all_of(n, n + batch, [&](int32_t v) { return v == n[0]; });
-    if (uniform) {
-        hipError_t e = spectral_launch(dt, bwd, n[0], lam, Q, in, out, n[0], batch, nullptr, fn,
-                                       param, s);
+    if (!n || all_equal(batch, n)) {
+        const int32_t nu = n ? n[0] : n0;
+        hipError_t e = spectral_launch(dt, bwd, nu, lam, Q, in, out, nu, batch, nullptr, fn, param, s);
         return e == hipSuccess ? BED_OK : hip_fail(e, "spectral launch");
     }
     return with_worklist(dt, batch, n, s, [&](const WorkItem *items, int count, int nmax) {
@@ -224,12 +223,28 @@ extern "C" bed_status bed_spectral_apply(bed_dtype dt, int64_t batch, const int3
                                          const void *lambda, const void *Q, int32_t fn,
                                          double param, void *F, void *stream)
 {
-    return bed::spectral(dt, false, batch, n, lambda, Q, fn, param, nullptr, F, stream);
+    const bed_status st = bed::check_sizes(dt, batch, n);
+    if (st != BED_OK) return st;
+    return bed::spectral(dt, false, batch, n, 0, lambda, Q, fn, param, nullptr, F, stream);
 }
 
 extern "C" bed_status bed_spectral_backward(bed_dtype dt, int64_t batch, const int32_t *n,
                                             const void *lambda, const void *Q, int32_t fn,
                                             double param, const void *dF, void *dA, void *stream)
 {
-    return bed::spectral(dt, true, batch, n, lambda, Q, fn, param, dF, dA, stream);
+    const bed_status st = bed::check_sizes(dt, batch, n);
+    if (st != BED_OK) return st;
+    return bed::spectral(dt, true, batch, n, 0, lambda, Q, fn, param, dF, dA, stream);
+}
+
+// As bedi_solve_uniform: a uniform batch by its size alone, for the Python
+// binding.
+extern "C" bed_status bedi_spectral_uniform(bed_dtype dt, int64_t batch, int32_t n,
+                                            const void *lambda, const void *Q, int32_t fn,
+                                            double param, int32_t bwd, const void *dF, void *out,
+                                            void *stream)
+{
+    const bed_status st = bed::check_uniform(dt, batch, n);
+    if (st != BED_OK) return st;
+    return bed::spectral(dt, bwd != 0, batch, nullptr, n, lambda, Q, fn, param, dF, out, stream);
 }

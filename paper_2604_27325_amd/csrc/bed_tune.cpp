@@ -36,10 +36,8 @@ std::string arch_name()
     return colon == std::string::npos ? a : a.substr(0, colon);
 }
 
-std::string tune_key(bed_dtype dt, int64_t batch, const int32_t *n)
+std::string tune_key(bed_dtype dt, int64_t batch, const int64_t (&hist)[65])
 {
-    int64_t hist[65] = {0};
-    for (int64_t b = 0; b < batch; ++b) hist[n[b]]++;
     uint64_t h = 1469598103934665603ull;  // FNV-1a over the histogram
     for (int i = 1; i <= 64; ++i) {
         uint64_t v = (uint64_t)hist[i];
@@ -52,6 +50,13 @@ std::string tune_key(bed_dtype dt, int64_t batch, const int32_t *n)
     snprintf(buf, sizeof buf, "%s|%s|%lld|%016llx", arch_name().c_str(),
              dt == BED_F64 ? "f64" : "f32", (long long)batch, (unsigned long long)h);
     return buf;
+}
+
+std::string tune_key(bed_dtype dt, int64_t batch, const int32_t *n)
+{
+    int64_t hist[65] = {0};
+    for (int64_t b = 0; b < batch; ++b) hist[n[b]]++;
+    return tune_key(dt, batch, hist);
 }
 
 void load_file_locked()
@@ -101,6 +106,19 @@ bed_tune tuned_or_default(bed_dtype dt, int64_t batch, const int32_t *n)
     load_file_locked();
     if (!g_tuned.empty()) {
         auto it = g_tuned.find(tune_key(dt, batch, n));
+        if (it != g_tuned.end()) return it->second;
+    }
+    return default_tune();
+}
+
+bed_tune tuned_or_default_uniform(bed_dtype dt, int64_t batch, int32_t n)
+{
+    std::lock_guard<std::mutex> lk(g_mu);
+    load_file_locked();
+    if (!g_tuned.empty()) {
+        int64_t hist[65] = {0};
+        hist[n] = batch;
+        auto it = g_tuned.find(tune_key(dt, batch, hist));
         if (it != g_tuned.end()) return it->second;
     }
     return default_tune();
