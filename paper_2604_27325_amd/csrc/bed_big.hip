@@ -5,8 +5,7 @@
 // the n <= 64 solver laid out for 128 elements.
 //
 //   k_big_reduce  Householder tridiagonalization T = Q_H^T A Q_H with binary64
-//                 arithmetic (binary32 for eigenvalues alone, as for n <= 64);
-//                 T torn at s = floor(n/2) (Eq. (3)) into T1 (s x s) and T2
+//                 arithmetic; T torn at s = floor(n/2) (Eq. (3)) into T1 (s x s) and T2
 //                 ((n-s) x (n-s)), written as their diagonals; with
 //                 eigenvectors the reflectors go to the workspace
 //   k_big_qh      Q_H = H_0 ... H_{n-3} from the reflectors in compact-WY
@@ -36,7 +35,6 @@ namespace big {
 
 constexpr int BN = NMAX_BIG;  // largest order
 constexpr int BT = 512;       // threads per matrix (8 waves)
-constexpr int CPL = BN * BN / BT;  // matrix entries per lane (32)
 
 struct Meta {
     float beta;  // coupling b_{s-1} of the torn tridiagonal matrix (scaled)
@@ -63,111 +61,152 @@ struct Ws {
 };
 
 // ------------------------------------------------------------------ reduction
-// About 66 KB, so that two teams share a CU: the load staging and the
-// buffers of the steps share the space.
-template <typename H>
+constexpr int RT_ = 256;  // threads of a reducing team
+constexpr int RHW = RT_ / 64;
+
+// 66 KB, so that two teams share a CU: the load staging and the buffers of the
+// steps (a copy of x, by parity, and -w per wave; by parity A x, A e and the
+// waves' parts of x^T A x) share the space.
 struct RedSmem {
     static constexpr int SLD = BN + 1;  // odd stride
+    static constexpr int SZ = HhLds<BN>::SZ;
     union {
         float st[BN * SLD];  // load staging (binary32)
         struct {
-            H xe[2][BN][2];  // pivot column as (x_r, 0) below row k + 1, (0, 1) at it
-                             // (v = x rv0 + e), by step parity: the update of step k
-                             // reads it while the next owner group writes step k + 1's
-            H w[BN];         // w = p - (tau/2)(p^T v) v
-            H part[4][BN];   // per column group: partial products
-            H red[8];        // per wave: partial sums
-            H red2[8];
+            alignas(16) double x[2][RHW][SZ];
+            alignas(16) double w[RHW][SZ];
+            alignas(16) double y[2][SZ];
+            alignas(16) double c[2][SZ];
+            alignas(16) double q[2][RHW];
         } s;
     } u;
     float a[BN], b[BN];
-    int badw[BT / 64];
-    int expw[BT / 64];
+    int badw[RHW];
+    int expw[RHW];
 };
 
-// Reflector of a pivot column (Golub-Van Loan 8.3): alpha = -sgn(x_0) mu, mu =
-// ||x||, v = (1, x_2.. rv0) with rv0 = sgn(x_0) / (|x_0| + mu), tau = (mu +
-// |x_0|) / mu = 2 / (v^T v); tau = 0 when the sub-column is already zero.
-template <typename H> struct Refl {
-    H alpha, tau, rv0;
+// Two rows per lane, 64 positions apart (HhRow for 128 positions).
+struct RedRow {
+    int p0, p1, s0;
+    __device__ __forceinline__ explicit RedRow(const int lane)
+    {
+        p0 = hh_out_row(lane) + 8 * hh_own<8>(lane);
+        p1 = p0 + 64;
+        s0 = hh_out_row(lane) * HhLds<BN>::ST + hh_own<8>(lane);  // p1 at s0 + 8
+    }
 };
-template <typename H> __device__ __forceinline__ Refl<H> reflector(const H x0, const H sig)
+
+struct RedState {
+    HhBlock<BN, RHW> H;
+    double x0, x1;          // the pivot column at this lane's rows (zero up to the pivot)
+    double xl, nwl;         // x and -w of the last step at row p1
+};
+
+// Steps whose pivot row lies in chunk B0, then the later chunks.
+template <int B0>
+__device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lane, const int wave,
+                                          const HhSelect<HhBlock<BN, RHW>::NA> &sel, RedState &R,
+                                          float *__restrict__ V, float *__restrict__ tau)
 {
-    constexpr bool est = sizeof(H) == 8;  // hardware estimate, one Newton step
-    const bool z = (sig == H(0));
-    const H s2 = fma(x0, x0, sig);
-    H rmu;
-    if constexpr (est) rmu = d_rsqrt_nr(s2);
-    else rmu = f_rsqrt(s2);
-    const H mu = s2 * rmu;
-    const H ax = f_abs(x0);
-    const H sg = (x0 < H(0)) ? H(-1) : H(1);
-    H rs;
-    if constexpr (est) rs = d_rcp_nr(ax + mu);
-    else rs = f_rcp(ax + mu);
-    Refl<H> h;
-    h.alpha = z ? x0 : -sg * mu;
-    h.rv0 = z ? H(1) : sg * rs;
-    h.tau = z ? H(0) : fma(ax, rmu, H(1));
-    return h;
+    using B = HhBlock<BN, RHW>;
+    constexpr int A0 = 8 * B0 / B::GI;
+    constexpr int ST = HhLds<BN>::ST;
+    const int pad = BN - n;
+    const RedRow row(lane);
+    const int i = 8 * wave + hh_row_of(lane), j = hh_col_of(lane);
+    double *W = S.u.s.w[wave];
+    const int yslot = hh_out_row(lane) * ST + wave + RHW * hh_own<B::NA>(lane);
+    hh_chunk<BN>(B0, pad, [&](const int kp, const int i0) {
+        const int k = kp - pad, par = kp & 1;
+        const int sp = i0 * ST + B0;
+        const double *X = S.u.s.x[par][wave];
+        double *Xn = S.u.s.x[par ^ 1][wave];  // the last step's x, then the next one's
+        wave_sync();
+        const double x0 = X[sp];
+        const bool l0 = row.p0 > kp + 1, l1 = row.p1 > kp + 1;
+        const double sig = wave_sum_all(fma(l0 ? R.x0 : 0.0, R.x0, l1 ? R.x1 * R.x1 : 0.0));
+        double y[B::NA];
+        double q = R.H.template step<A0, B0>(X, W, Xn, S.u.s.c[par], i, j, i0, y);
+        const double yo = hh_reduce_scatter<B::NA, A0>(y, sel, lane);
+        q = wave_sum_all(q);
+        S.u.s.y[par][yslot] = yo;
+        S.u.s.q[par][wave] = q;
+        const HhRefl<float> h = hh_reflector<float>(x0, sig);
+        const double xt0 = x0 - h.alpha, hb = 0.5 * h.beta * h.beta;
+        __syncthreads();
+        const double *Y = S.u.s.y[par], *C = S.u.s.c[par];
+        const double y0 = Y[row.s0], y1 = Y[row.s0 + 8], c0 = C[row.s0], c1 = C[row.s0 + 8];
+        const double s1 = Y[sp], a00 = C[sp];
+        double qs = S.u.s.q[par][0];
+#pragma unroll
+        for (int w2 = 1; w2 < RHW; ++w2) qs += S.u.s.q[par][w2];
+        const HhStep o0 = hh_step(R.x0, y0, c0, s1, a00, qs, h.alpha, h.beta, hb, xt0);
+        const HhStep o1 = hh_step(R.x1, y1, c1, s1, a00, qs, h.alpha, h.beta, hb, xt0);
+        if (wave == (kp & (RHW - 1))) {  // the waves take the steps' outputs in turn
+            if (V) {
+                // reflector k, normalized to v_{k+1} = 1
+                const float v0 = float(row.p0 == kp + 1 ? 1.0 : R.x0 * h.rx0);
+                const float v1 = float(row.p1 == kp + 1 ? 1.0 : R.x1 * h.rx0);
+                if (row.p0 >= pad) V[(int64_t)k * n + row.p0 - pad] = v0;
+                V[(int64_t)k * n + row.p1 - pad] = v1;
+                if (lane == 0) tau[k] = float(h.beta * xt0 * xt0);
+            }
+            S.b[k] = float(h.alpha);
+            S.a[k + 1] = float(fma(-2.0 * xt0, o0.w0, a00));
+        }
+        R.xl = R.x1;
+        R.nwl = o1.nw;
+        R.x0 = l0 ? o0.xn : 0.0;
+        R.x1 = l1 ? o1.xn : 0.0;
+        W[row.s0] = o0.nw;
+        W[row.s0 + 8] = o1.nw;
+        Xn[row.s0] = R.x0;
+        Xn[row.s0 + 8] = R.x1;
+    });
+    if constexpr (B0 + 1 < BN / 8) red_steps<B0 + 1>(S, n, lane, wave, sel, R, V, tau);
 }
 
-// Arithmetic type H: binary64 when Q_H is formed (eigenvectors), binary32
-// for eigenvalues alone (as for n <= 64).  Lane (r, g) = (t % 128, t / 128)
-// keeps row r of the columns c = g + 4j (j < 32) in registers; the four column groups are whole waves, so
-// reads of v and w at a lane's columns are wave-wide broadcasts.  Step k:
-// the owner group of column k publishes it with the partial of ||x||^2 (one
-// barrier), every lane forms the reflector (Golub-Van Loan 8.3, as for n <=
-// 64), its partial of p = tau A v and of v^T A v (second barrier), p and w
-// (third barrier), then the rank-2 update A -= v w^T + w v^T of its entries.
-// With eigenvectors the reflectors (rounded to binary32) and their tau go to
-// the workspace for k_big_qh.  Two teams per CU: at most 128 VGPRs.
-template <typename H>
-__global__ void __launch_bounds__(BT, 4)
+// Householder tridiagonalization in binary64 as for n <= 64 (hh_product), on
+// four waves that all form the norm and the reflector: a control wave would
+// share a SIMD with a product wave, whose issue bounds the step (about 270
+// instructions a wave and step at the start, two waves per SIMD with two teams
+// per CU).  One barrier per step instead of three, and each lane's 4 x 16 block
+// shrinks in both directions.  With eigenvectors the reflectors (rounded to
+// binary32) and their tau go to the workspace for k_big_qh.
+__global__ void __launch_bounds__(RT_, 2)
 k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
 {
-    __shared__ RedSmem<H> S;
+    __shared__ RedSmem S;
     const int64_t bi = blockIdx.x;
     if (bi >= batch) return;
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    const int r = t & (BN - 1), g = t >> 7;
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
     const int s = n / 2, n1 = s, n2 = n - s;
     const float *Ab = A + bi * n * n;
-
-    // load (coalesced, staged in LDS as binary32 over the reflector buffer)
-    float *St = S.u.st;
-    constexpr int SLD = RedSmem<H>::SLD;
-    {
-        // lane (j, i0) = (t % BN, t / BN) reads rows i0, i0 + 4, ... at column
-        // j: every load is issued before the first LDS write
-        const int j = t & (BN - 1), i0 = t / BN;
-        float ld[BN * BN / BT];
-#pragma unroll
-        for (int q = 0; q < BN * BN / BT; ++q) {
-            const int i = i0 + (BT / BN) * q;
-            const bool in = i < n && j < n;
-            const float v = Ab[in ? i * n + j : 0];  // clamped address: no branch
-            ld[q] = in ? v : 0.f;
-        }
-#pragma unroll
-        for (int q = 0; q < BN * BN / BT; ++q) St[(i0 + (BT / BN) * q) * SLD + j] = ld[q];
-    }
-    __syncthreads();
-    H ar[CPL];
+    constexpr int SLD = RedSmem::SLD;
     bool bad = false;
     float amax = 0.f;
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) {
-        const int c = g + 4 * j;
-        float v = 0.f;
-        if (r < n && c < n) {
-            v = (c <= r) ? St[r * SLD + c] : St[c * SLD + r];  // lower triangle
-            bad = bad || !f_finite(v);
-            amax = f_max(amax, f_abs(v));
-        }
-        ar[j] = H(v);
-    }
     {
+        // lane (j, i0) = (t % BN, t / BN) stages rows i0, i0 + 2, ... at column j,
+        // sixteen loads issued before the first LDS write
+        constexpr int RS = RT_ / BN, RPL = BN / RS, LB = 16;
+        const int j = t & (BN - 1), i0 = t / BN;
+#pragma unroll 1
+        for (int q0 = 0; q0 < RPL; q0 += LB) {
+            float ld[LB];
+#pragma unroll
+            for (int q = 0; q < LB; ++q) {
+                const int i = i0 + RS * (q0 + q);
+                ld[q] = Ab[(i < n && j <= i) ? i * n + j : 0];  // lower triangle, clamped
+            }
+#pragma unroll
+            for (int q = 0; q < LB; ++q) {
+                const int i = i0 + RS * (q0 + q);
+                const bool in = i < n && j <= i;
+                bad = bad || (in && !f_finite(ld[q]));
+                amax = in ? f_max(amax, f_abs(ld[q])) : amax;
+                S.u.st[i * SLD + j] = ld[q];
+            }
+        }
         const bool wb = __ballot(bad) != 0;
         const int we = group_max<64>(exp_field(amax), lane);
         if (lane == 0) {
@@ -178,7 +217,7 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
     __syncthreads();
     int anybad = 0, emax = 0;
 #pragma unroll
-    for (int w = 0; w < BT / 64; ++w) {
+    for (int w = 0; w < RHW; ++w) {
         anybad |= S.badw[w];
         emax = max(emax, S.expw[w]);
     }
@@ -186,111 +225,50 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
     int sh = (emax == 0) ? 0 : fexp<float>::BIAS - 1 - emax;
     sh = min(max(sh, -fexp<float>::SMAX), fexp<float>::SMAX);
     if (anybad) {
-        for (int e = t; e < 2 * n1; e += BT) ws.c1[bi * 2 * n1 + e] = 0.f;
-        for (int e = t; e < 2 * n2; e += BT) ws.c2[bi * 2 * n2 + e] = 0.f;
+        for (int e = t; e < 2 * n1; e += RT_) ws.c1[bi * 2 * n1 + e] = 0.f;
+        for (int e = t; e < 2 * n2; e += RT_) ws.c2[bi * 2 * n2 + e] = 0.f;
         if (t == 0) ws.meta[bi] = Meta{0.f, 0, 1, 0};
         return;
     }
-    const H hs = H(fexp<float>::pow2(sh));
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) ar[j] *= hs;
-    __syncthreads();  // the staging buffer becomes the reflector store
-
-    const int gs = __builtin_amdgcn_readfirstlane(g);
-    const int rhi = __builtin_amdgcn_readfirstlane((wave & 1) * 64 + 63);  // the wave's last row
-    auto wlive = [&](const int k) { return rhi > k; };
-    for (int k = 0; k < n - 2; ++k) {
-        const int gk = k & 3, jk = k >> 2;
-        typedef H H2 __attribute__((ext_vector_type(2)));
-        H2 *xe = reinterpret_cast<H2 *>(S.u.s.xe[k & 1]);
-        if (g == gk) {
-            const H x = pick<CPL>(ar, jk);
-            const bool below = r > k + 1 && r < n;
-            xe[r] = H2{below ? x : H(0), (r == k + 1) ? H(1) : H(0)};
-            if (r == k + 1) S.u.s.red[2] = x;
-            if (r == k) S.a[k] = float(x);
-            const H s2 = wave_sum_all(below ? x * x : H(0));
-            if (lane == 0) S.u.s.red[__builtin_amdgcn_readfirstlane(wave & 1)] = s2;
-        }
-        __syncthreads();
-        const H x0 = S.u.s.red[2];
-        const H sig = S.u.s.red[0] + S.u.s.red[1];
-        const Refl<H> h = reflector<H>(x0, sig);
-        // v = (1, x_{k+2..} rv0) = x' rv0 + e_{k+1} with x' the pivot column
-        // zeroed at rows <= k + 1 (exact: the products are as before, and the
-        // pivot entry is exactly 1 without a per-column select); x is zero
-        // past k + 1 too when sig = 0
-        const H2 xr2 = xe[r];
-        const H vr = fma(xr2.x, h.rv0, xr2.y);
-        // Dead work is skipped by wave-uniform branches: chunks of eight of a
-        // lane's columns that lie at or left of column k (v is zero there and
-        // the columns are never read again), and whole waves whose rows are
-        // all <= k (their p and w are not used).
-        // v at this wave's columns c = g + 4j, the same for all its lanes: lane
-        // j forms column j's entry from one pivot pair and the values are
-        // broadcast into scalar registers (one LDS read per lane instead of
-        // one per column), where they stay for the update
-        const H2 xl = xe[g + 4 * (lane & (CPL - 1))];
-        const H vl = fma(xl.x, h.rv0, xl.y);
-        H vc[CPL];
-        H pp = H(0);
-        if (wlive(k)) {
-            // independent chains against the FMA latency
-            constexpr int NC = 4;
-            H pq[NC];
-#pragma unroll
-            for (int i = 0; i < NC; ++i) pq[i] = H(0);
-#pragma unroll
-            for (int q = 0; q < CPL / 8; ++q) {
-                if (gs + 32 * q + 28 <= k) continue;
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                    const int j = 8 * q + jj;
-                    vc[j] = bcast(vl, j);
-                    pq[jj % NC] = fma(ar[j], vc[j], pq[jj % NC]);
-                }
-            }
-            pp = (pq[0] + pq[1]) + (pq[2] + pq[3]);
-            S.u.s.part[g][r] = pp;
-        }
-        const H pv = wave_sum_all(vr * pp);  // partial of v^T A v
-        if (lane == 0) S.u.s.red2[wave] = pv;
-        if constexpr (std::is_same<H, double>::value) {
-            if (g == 0 && r < n) ws.v[(bi * (n - 2) + k) * n + r] = float(vr);
-            if (t == 0) ws.tau[bi * n + k] = float(h.tau);
-        }
-        if (t == 0) S.b[k] = float(h.alpha);
-        __syncthreads();
-        const H p = h.tau * (S.u.s.part[0][r] + S.u.s.part[1][r] + S.u.s.part[2][r] + S.u.s.part[3][r]);
-        H vav = H(0);
-#pragma unroll
-        for (int w = 0; w < BT / 64; ++w) vav += S.u.s.red2[w];
-        const H ptv = h.tau * vav;  // p^T v = tau v^T A v
-        const H wr = (r > k) ? p - H(0.5) * h.tau * ptv * vr : H(0);
-        if (g == 0) S.u.s.w[r] = wr;
-        __syncthreads();
-        if (wlive(k)) {
-#pragma unroll
-            for (int q = 0; q < CPL / 8; ++q) {
-                if (gs + 32 * q + 28 <= k) continue;
-#pragma unroll
-                for (int jj = 0; jj < 8; ++jj) {
-                    const int j = 8 * q + jj;
-                    const int c = g + 4 * j;
-                    ar[j] = fma(-vr, S.u.s.w[c], fma(-wr, vc[j], ar[j]));
-                }
-            }
-        }
-    }
-    // last 2 x 2 block
+    const double hs = double(fexp<float>::pow2(sh));
+    const int pad = BN - n;
+    using B = HhBlock<BN, RHW>;
+    RedState R;
+    const RedRow row(lane);
     {
-        const int c0 = n - 2, c1 = n - 1;
-        if (g == (c0 & 3)) {
-            const H x = pick<CPL>(ar, c0 >> 2);
-            if (r == c0) S.a[c0] = float(x);
-            if (r == c1) S.b[c0] = float(x);
+        auto entry = [&](const int pr, const int pc) {  // lower triangle, zero in the padding
+            const int hi = max(pr, pc) - pad, lo = min(pr, pc) - pad;
+            const float v = S.u.st[lo >= 0 ? hi * SLD + lo : 0];
+            return lo >= 0 ? hs * double(v) : 0.0;
+        };
+        const int i = 8 * wave + hh_row_of(lane), j = hh_col_of(lane);
+#pragma unroll
+        for (int a = 0; a < B::NA; ++a) {
+#pragma unroll
+            for (int b = 0; b < B::NB; ++b) R.H.a[a][b] = entry(i + B::GI * a, j + 8 * b);
         }
-        if (g == (c1 & 3) && r == c1) S.a[c1] = float(pick<CPL>(ar, c1 >> 2));
+        const double e0 = entry(row.p0, pad), e1 = entry(row.p1, pad);
+        R.x0 = row.p0 > pad ? e0 : 0.0;
+        R.x1 = e1;  // p1 >= 64 > pad
+        if (t == 0) S.a[0] = float(hs * double(S.u.st[0]));
+    }
+    R.xl = R.nwl = 0.0;
+    __syncthreads();  // the staging buffer becomes the step buffers
+    S.u.s.w[wave][row.s0] = S.u.s.w[wave][row.s0 + 8] = 0.0;
+    {
+        const int par = pad & 1;
+        S.u.s.x[par][wave][row.s0] = R.x0;
+        S.u.s.x[par][wave][row.s0 + 8] = R.x1;
+        S.u.s.x[par ^ 1][wave][row.s0] = S.u.s.x[par ^ 1][wave][row.s0 + 8] = 0.0;
+    }
+    const HhSelect<B::NA> sel(lane);
+    red_steps<0>(S, n, lane, wave, sel, R, ws.v ? ws.v + bi * (n - 2) * n : nullptr,
+                 ws.tau ? ws.tau + bi * n : nullptr);
+    // b_{n-2} is the pivot column's last value, a_{n-1} the last diagonal entry
+    // after the last update (position BN - 1: lane 63 of the last wave)
+    if (wave == RHW - 1 && lane == 63) {
+        S.b[n - 2] = float(R.x1);
+        S.a[n - 1] = float(fma(2.0 * R.xl, R.nwl, R.H.a[B::NA - 1][B::NB - 1]));
     }
     __syncthreads();
 
@@ -300,9 +278,9 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
         const float rho = f_abs(beta);
         float *C1 = ws.c1 + bi * 2 * n1;
         float *C2 = ws.c2 + bi * 2 * n2;
-        for (int e = t; e < 2 * n1 - 1; e += BT)
+        for (int e = t; e < 2 * n1 - 1; e += RT_)
             C1[e] = (e < n1) ? S.a[e] - (e == s - 1 ? rho : 0.f) : S.b[e - n1];
-        for (int e = t; e < 2 * n2 - 1; e += BT)
+        for (int e = t; e < 2 * n2 - 1; e += RT_)
             C2[e] = (e < n2) ? S.a[s + e] - (e == 0 ? rho : 0.f) : S.b[s + e - n2];
         if (t == 0) ws.meta[bi] = Meta{beta, sh, 0, 0};
     }
@@ -948,12 +926,8 @@ bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *la
     ws.e1 = Q ? nullptr : ws.q1;
     ws.e2 = Q ? nullptr : ws.q1 + B * 2 * n1;
 
-    if (Q)
-        hipLaunchKernelGGL(k_big_reduce<double>, dim3((unsigned)batch), dim3(BT), 0, s,
-                           (const float *)A, n, (int64_t)batch, ws);
-    else
-        hipLaunchKernelGGL(k_big_reduce<float>, dim3((unsigned)batch), dim3(BT), 0, s,
-                           (const float *)A, n, (int64_t)batch, ws);
+    hipLaunchKernelGGL(k_big_reduce, dim3((unsigned)batch), dim3(RT_), 0, s, (const float *)A, n,
+                       (int64_t)batch, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_big_reduce launch");
     if (Q) {

@@ -57,14 +57,12 @@
 namespace bed {
 
 // Waves per SIMD that the resident teams of a shape need (four SIMDs per CU);
-// register allocation is capped accordingly.  n > 32: the reducing wave keeps
-// 64 binary64 entries and its operands per lane (over 200 registers), which
-// leaves two waves per SIMD: two teams of 256 threads per CU, one of 512.
+// register allocation is capped accordingly (n > 32: two teams, 256 registers
+// at 256 threads, 128 at 512).
 template <int NMAX, int NT> struct Occ {
     static constexpr int teams_per_cu = NMAX >= 64 ? 2 : (NMAX >= 32 ? 4 : 8);
     static constexpr int v = (teams_per_cu * NT / 64 + 3) / 4;
-    static constexpr int most = NMAX >= 64 ? 2 : 8;
-    static constexpr int wpe = v < 1 ? 1 : (v > most ? most : v);
+    static constexpr int wpe = v < 1 ? 1 : (v > 8 ? 8 : v);
 };
 #define BED_OCC(NMAX, NT) __attribute__((amdgpu_waves_per_eu(Occ<NMAX, NT>::wpe)))
 
@@ -988,74 +986,109 @@ __device__ __forceinline__ HhStep hh_step(const double x, const double yr, const
     return o;
 }
 
-// Entries, vectors and the product of one product wave at the chunk level.
+// Entries of one product wave, with its update and product at the chunk level.
 template <int NMAX, int HW> struct HhBlock {
     static constexpr int GI = 8 * HW;
     static constexpr int NA = NMAX / GI, NB = NMAX / 8, ST = HhLds<NMAX>::ST;
-    double a[NA][NB];       // A(i + GI a, j + 8 b) after the updates of all steps but the last
-    double xr[NA], xc[NB];  // x of the last step at this lane's rows and columns
+    // Large blocks leave no registers for the vectors' operands: they read the
+    // last x again and take the columns one at a time.
+    static constexpr bool LARGE = NMAX > 64;
+    double a[NA][NB];  // A(i + GI a, j + 8 b) after the updates of all steps but the last
+    double xr[LARGE ? 1 : NA], xc[LARGE ? 1 : NB];  // x of the last step at this lane's rows, columns
 
-    // Applies the update of the last step (-w in wl) and forms the products of
-    // this step with x in xl, for rows and columns from chunks A0, B0 on.  The
-    // column of position 8 B0 + j0 goes to cl.  Returns this lane's part of x^T A x.
+    // Applies the update of the last step (-w in wl; x of that step in xo, for
+    // LARGE blocks) and forms the products of this step with x in xl, for rows
+    // and columns from chunks A0, B0 on.  The column of position 8 B0 + j0 goes
+    // to cl.  Returns this lane's part of x^T A x.
     template <int A0, int B0>
-    __device__ __forceinline__ double step(const double* xl, const double* wl, double* cl,
-                                           const int i, const int j, const int j0, double (&y)[NA])
+    __device__ __forceinline__ double step(const double* xl, const double* wl, const double* xo,
+                                           double* cl, const int i, const int j, const int j0,
+                                           double (&y)[NA])
     {
-        double wr[NA], wc[NB], nr[NA], nc[NB];
         const int ri = (i & 7) * ST + (i >> 3);
+        auto column = [&] {
+            if (j == j0) {
 #pragma unroll
-        for (int c = A0; c < NA; ++c) {
-            wr[c] = wl[ri + HW * c];
-            nr[c] = xl[ri + HW * c];
-        }
-#pragma unroll
-        for (int b = B0 & ~1; b < NB; ++b) {
-            wc[b] = wl[j * ST + b];
-            nc[b] = xl[j * ST + b];
-        }
-#pragma unroll
-        for (int c = A0; c < NA; ++c)
-#pragma unroll
-            for (int b = B0; b < NB; ++b)
-                a[c][b] = fma(wr[c], xc[b], fma(xr[c], wc[b], a[c][b]));
-        if (j == j0) {
-#pragma unroll
-            for (int c = A0; c < NA; ++c) cl[ri + HW * c] = a[c][B0];
-        }
-        double q = 0.0;
-#pragma unroll
-        for (int c = 0; c < NA; ++c) {
-            y[c] = 0.0;
-            if (c < A0) continue;
-            double y1 = a[c][B0] * nc[B0], y2 = 0.0;
-#pragma unroll
-            for (int b = B0 + 1; b < NB; ++b) {
-                double& acc = ((b - B0) & 1) ? y2 : y1;
-                acc = (b == B0 + 1) ? a[c][b] * nc[b] : fma(a[c][b], nc[b], acc);
+                for (int c = A0; c < NA; ++c) cl[ri + HW * c] = a[c][B0];
             }
-            y[c] = (B0 + 1 < NB) ? y1 + y2 : y1;
-            q = (c == A0) ? nr[c] * y[c] : fma(nr[c], y[c], q);
+        };
+        double q = 0.0;
+        if constexpr (LARGE) {
+            double wr[NA], nr[NA];
+#pragma unroll
+            for (int c = A0; c < NA; ++c) {
+                wr[c] = wl[ri + HW * c];
+                nr[c] = xo[ri + HW * c];
+            }
+#pragma unroll
+            for (int b = B0; b < NB; ++b) {
+                const double wc = wl[j * ST + b], xc1 = xo[j * ST + b];
+#pragma unroll
+                for (int c = A0; c < NA; ++c)
+                    a[c][b] = fma(wr[c], xc1, fma(nr[c], wc, a[c][b]));
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            column();
+#pragma unroll
+            for (int c = 0; c < NA; ++c) y[c] = 0.0;
+#pragma unroll
+            for (int b = B0; b < NB; ++b) {
+                const double nc = xl[j * ST + b];
+#pragma unroll
+                for (int c = A0; c < NA; ++c) y[c] = fma(a[c][b], nc, y[c]);
+            }
+#pragma unroll
+            for (int c = A0; c < NA; ++c) q = fma(xl[ri + HW * c], y[c], q);
+        } else {
+            double wr[NA], wc[NB], nr[NA], nc[NB];
+#pragma unroll
+            for (int c = A0; c < NA; ++c) {
+                wr[c] = wl[ri + HW * c];
+                nr[c] = xl[ri + HW * c];
+            }
+#pragma unroll
+            for (int b = B0 & ~1; b < NB; ++b) {
+                wc[b] = wl[j * ST + b];
+                nc[b] = xl[j * ST + b];
+            }
+#pragma unroll
+            for (int c = A0; c < NA; ++c)
+#pragma unroll
+                for (int b = B0; b < NB; ++b)
+                    a[c][b] = fma(wr[c], xc[b], fma(xr[c], wc[b], a[c][b]));
+            column();
+#pragma unroll
+            for (int c = 0; c < NA; ++c) {
+                y[c] = 0.0;
+                if (c < A0) continue;
+                double y1 = a[c][B0] * nc[B0], y2 = 0.0;
+#pragma unroll
+                for (int b = B0 + 1; b < NB; ++b) {
+                    double& acc = ((b - B0) & 1) ? y2 : y1;
+                    acc = (b == B0 + 1) ? a[c][b] * nc[b] : fma(a[c][b], nc[b], acc);
+                }
+                y[c] = (B0 + 1 < NB) ? y1 + y2 : y1;
+                q = (c == A0) ? nr[c] * y[c] : fma(nr[c], y[c], q);
+            }
+#pragma unroll
+            for (int c = A0; c < NA; ++c) xr[c] = nr[c];
+#pragma unroll
+            for (int b = B0; b < NB; ++b) xc[b] = nc[b];
         }
-#pragma unroll
-        for (int c = A0; c < NA; ++c) xr[c] = nr[c];
-#pragma unroll
-        for (int b = B0; b < NB; ++b) xc[b] = nc[b];
         return q;
     }
 };
 
 // The steps kp (padded index) whose pivot row kp + 1 = 8 B0 + i0 lies in chunk
-// B0: f(parity constant, kp, i0), the parity of kp fixed per call.
+// B0: f(kp, i0).  (One copy of the body: unrolled by the parity that the
+// exchange buffers alternate with, it spends more on register copies than the
+// addresses cost.)
 template <int NMAX, typename F>
 __device__ __forceinline__ void hh_chunk(const int b0, const int pad, F&& f)
 {
+    const int kb = max(8 * b0 - 1, pad), ke = min(8 * b0 + 7, NMAX - 2);
 #pragma unroll 1
-    for (int i0 = 0; i0 < 8; i0 += 2) {
-        const int kp = 8 * b0 - 1 + i0;
-        if (kp >= pad && kp < NMAX - 2) f(std::integral_constant<int, 1>{}, kp, i0);
-        if (kp + 1 >= pad && kp + 1 < NMAX - 2) f(std::integral_constant<int, 0>{}, kp + 1, i0 + 1);
-    }
+    for (int kp = kb; kp < ke; ++kp) f(kp, (kp + 1) & 7);
 }
 
 // One wave alone, chunks B0, B0 + 1, ...  x: the pivot column at this lane's
@@ -1073,8 +1106,7 @@ __device__ __forceinline__ void hh_solo(Smem<T, NMAX, NT>& S, const int n, const
     const int pad = NMAX - n;
     const HhRow<NMAX> R(lane);
     const int vr = R.pos - pad + (R.pos < pad ? NMAX : 0);
-    if (8 * B0 + 7 > pad)
-    hh_chunk<NMAX>(B0, pad, [&](auto, const int kp, const int i0) {
+    hh_chunk<NMAX>(B0, pad, [&](const int kp, const int i0) {
         const int k = kp - pad;
         const int s0 = i0 * ST + B0;
         wave_sync();
@@ -1082,7 +1114,7 @@ __device__ __forceinline__ void hh_solo(Smem<T, NMAX, NT>& S, const int n, const
         const double x0 = S.u.h.x[0][s0];
         const double sig = HhRow<NMAX>::sum(R.pos > kp + 1 ? x * x : 0.0);
         double y[NB];
-        double q = H.template step<B0, B0>(S.u.h.x[0], S.u.h.w[0], S.u.h.c[0], hh_row_of(lane),
+        double q = H.template step<B0, B0>(S.u.h.x[0], S.u.h.w[0], nullptr, S.u.h.c[0], hh_row_of(lane),
                                            hh_col_of(lane), i0, y);
         BED_HSTEP(k, 1);
         const HhRefl<T> h = hh_reflector<T>(x0, sig);
@@ -1134,16 +1166,14 @@ __device__ __forceinline__ void hh_product(Smem<T, NMAX, NT>& S, const int n, co
     double* W = S.u.h.w[wave];
     // this lane's row after the reduction over the columns
     const int yslot = HhRow<NMAX>::slot_of(8 * wave + hh_out_row(lane) + B::GI * hh_own<B::NA>(lane));
-    if (8 * B0 + 7 > pad)
-    hh_chunk<NMAX>(B0, pad, [&](auto P, const int kp, const int i0) {
-        constexpr int par = decltype(P)::value;
-        const int k = kp - pad;
+    hh_chunk<NMAX>(B0, pad, [&](const int kp, const int i0) {
+        const int k = kp - pad, par = kp & 1;
         (void)k;
         const int s0 = i0 * ST + B0;
         wave_sync();
         BED_HSTEP(k, 0);
         double y[B::NA];
-        double q = H.template step<A0, B0>(X, W, S.u.h.c[par], i, j, i0, y);
+        double q = H.template step<A0, B0>(X, W, nullptr, S.u.h.c[par], i, j, i0, y);
         BED_HSTEP(k, 1);
         const double yo = hh_reduce_scatter<B::NA, A0>(y, sel, lane);
         q = wave_sum_all(q);
@@ -1185,9 +1215,8 @@ __device__ __forceinline__ void hh_control(Smem<T, NMAX, NT>& S, const int n, co
     const int vr = R.pos - pad + (R.pos < pad ? NMAX : 0);
 #pragma unroll 1
     for (int b0 = pad / 8; b0 < NMAX / 8; ++b0)
-        hh_chunk<NMAX>(b0, pad, [&](auto P, const int kp, const int i0) {
-            constexpr int par = decltype(P)::value;
-            const int k = kp - pad;
+        hh_chunk<NMAX>(b0, pad, [&](const int kp, const int i0) {
+            const int k = kp - pad, par = kp & 1;
             const int s0 = i0 * ST + b0;
             const double x0 = bcast(x, hh_lane_of<NMAX / 8>(i0, b0));
             const double sig = HhRow<NMAX>::sum(R.pos > kp + 1 ? x * x : 0.0);
