@@ -611,7 +611,7 @@ def main():
             main_res = (n, A_np, wall, ev, lam.cpu().numpy(), Q.cpu().numpy(), info.cpu().numpy())
 
     if not args.only_n and not args.no_big and not args.main_only:
-        # 64 < n <= 128: one more tearing step above the n <= 64 kernels
+        # 64 < n <= 128: kernels of their own
         nb = 128
         A_np_b, _, _ = workloads.paper_scale(nb)
         A_b = torch.from_numpy(A_np_b).to("cuda")
@@ -626,7 +626,7 @@ def main():
                           "launch_us_median": float(np.median(each_b) * 1e3),
                           "launch_us_p10": float(np.percentile(each_b, 10) * 1e3),
                           "launch_us_p90": float(np.percentile(each_b, 90) * 1e3),
-                          "kernels": "reduce + tear, Householder product, halves on the n <= 64 kernels, top merge",
+                          "kernels": "reduction, direct solve and back-transform; halves and top merge for what is left",
                           "parity": parity_sample(_orc, A_np_b, lam_b.cpu().numpy(),
                                                   Q_b.cpu().numpy(), info_b.cpu().numpy())}
         print(f"[bench] n={nb}: {per_n[str(nb)]['eigendecomps_per_s']:.4g} matrices/s, "
@@ -682,7 +682,7 @@ def main():
                      "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_TFLOPS,
                      "traffic": profiled_traffic(f"k_syevd_uniform_f32_n{n}_b{BATCH}"),
                      "kernel": (f"k_syevd_uniform<float, {nmax_of(n)}, {threads_of(n)}>" if n <= 64
-                                else "k_big_reduce, k_big_qh, k_syevd_tri, k_big_merge (one solve)"),
+                                else "k_big_reduce, k_big_direct, k_syevd_tri, k_big_merge (one solve)"),
                      "flops_per_launch": BATCH * F, "kernel_ms": ev},
         "latency": None if "one_team_per_cu" not in per_n.get(str(n), {}) else {
             "one_matrix_chain_us": per_n[str(n)]["one_team_per_cu"]["kernel_ms"] * 1e3,

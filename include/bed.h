@@ -24,9 +24,9 @@
  *              each column sign-canonical (largest-magnitude entry positive,
  *              lowest index on exact ties).
  *   Sizes      1 <= n_b <= 64 everywhere.  bed_syevd and bed_syevals also
- *              take uniform binary32 batches of 64 < n <= 128 (one more
- *              tearing step above the n <= 64 kernels, Sec. 2.1); other uses
- *              of n > 64 return BED_ERR_UNSUPPORTED.
+ *              take uniform binary32 batches of 64 < n <= 128 (kernels of
+ *              their own, in four launches); other uses of n > 64 return
+ *              BED_ERR_UNSUPPORTED.
  *   Memory     A, lambda, Q, info, dlambda, dQ, dA are DEVICE pointers owned
  *              by the caller.  n arrays are HOST pointers, read during the
  *              call only.  FP32 data needs 4-byte, FP64 8-byte alignment.
@@ -105,10 +105,10 @@ typedef struct bed_plan bed_plan;
  * a stored persistent schedule) use a plan from an internal cache keyed by
  * (dtype, n[], stream); the first call for a new key allocates its descriptor
  * (refused under capture, BED_ERR_CAPTURE).  A uniform binary32 batch of
- * 64 < n <= 128 runs in steps (reduction and tearing, the Householder
- * product when eigenvectors are wanted, the two halves on the n <= 64
- * kernels, the top merge) with a workspace kept per stream (about
- * 8 (n/2)^2 + 12n + 24 bytes per matrix, plus 4n(n - 1) with eigenvectors,
+ * 64 < n <= 128 runs in steps (reduction, direct solve and back-transform; for
+ * matrices left over, the two halves on the n <= 64 kernels and the top
+ * merge) with a workspace kept per stream (about 8 (n/2)^2 + 12n + 2100
+ * bytes per matrix, plus 4n(n - 1) with eigenvectors,
  * grown on demand; growing it synchronizes the stream and is refused under
  * capture).  A workspace that a HIP graph captured is kept until the process
  * ends (a larger one replaces it for later calls); the graph's replays share
@@ -138,13 +138,12 @@ bed_status bed_syevd_noalloc(bed_dtype dt, int64_t batch, const int32_t *n, cons
                              void *lambda, void *Q, int32_t *info, void *stream);
 
 /* Eigenvalues only (the note forms eigenvectors only when they are required,
- * Sec. 2.3.5): Q is not produced.  The merges carry only the first and last
- * row of each node's eigenvector block -- all that the next z (Eq. (5))
- * reads -- instead of the block product, and there is no back-transform.
- * For n <= 64 the reduction is bed_syevd's (binary64 arithmetic); for 64 < n it
- * runs in the data's own precision: an eigenvalue moves by at most the
- * reduction's backward error, with no eigenvalue-gap factor, so the results
- * keep bed_syevd's eigenvalue bound but are not bitwise equal to its lambda. */
+ * Sec. 2.3.5): Q is not produced.  There are no factorizations and no
+ * back-transform; where the divide step is used, the merges carry only the first
+ * and last row of each node's eigenvector block -- all that the next z (Eq. (5))
+ * reads -- instead of the block product.  The reduction is bed_syevd's (binary64
+ * arithmetic).  The results keep bed_syevd's eigenvalue bound but need not be
+ * bitwise equal to its lambda. */
 bed_status bed_syevals(bed_dtype dt, int64_t batch, const int32_t *n, const void *A,
                        void *lambda, int32_t *info, void *stream);
 

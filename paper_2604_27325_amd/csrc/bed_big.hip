@@ -1,23 +1,26 @@
-// bed_big.hip -- symmetric matrices of order 64 < n <= 128 in binary32.  The
-// divide step of the note applies at any size (Sec. 2.1): one tearing step
-// above the n <= 64 solver, whose halves then fit a single team, and the top
-// merge (Sec. 2.3) on one 512-thread team per matrix, with the merge code of
-// the n <= 64 solver laid out for 128 elements.
+// bed_big.hip -- symmetric matrices of order 64 < n <= 128 in binary32: the
+// reduction and the direct solver of n <= 64 laid out for 128 elements.  For
+// a spectrum that the direct solver does not take, the divide step of the note
+// applies at any size (Sec. 2.1): one tearing step above the n <= 64 solver, whose
+// halves then fit a single team, and the top merge (Sec. 2.3) on one 512-thread
+// team per matrix.
 //
 //   k_big_reduce  Householder tridiagonalization T = Q_H^T A Q_H with binary64
-//                 arithmetic; T torn at s = floor(n/2) (Eq. (3)) into T1 (s x s) and T2
-//                 ((n-s) x (n-s)), written as their diagonals; with
-//                 eigenvectors the reflectors go to the workspace
-//   k_big_qh      Q_H = H_0 ... H_{n-3} from the reflectors in compact-WY
-//                 blocks on binary64 MFMA tiles, staged in the Q output
+//                 arithmetic; with eigenvectors the reflectors go to the workspace
+//   k_big_direct  eigenvalues and eigenvectors of T and the back-transform; or
+//                 T torn at s = floor(n/2) (Eq. (3)) into T1 (s x s) and T2
+//                 ((n-s) x (n-s)), written as their diagonals
+//
+// and, where a matrix of the batch was torn (the others are passed over; both
+// launches are always there, about 4 us each, as the host does not wait to know):
+//
 //   children      the n <= 64 solver on tridiagonal input (no reduction, no
 //                 back-transform) solves T1 and T2; for eigenvalues alone it
 //                 returns only the end rows of their eigenvector matrices
 //   k_big_merge   z = [sgn(beta) Q1(s-1, :), Q2(0, :)] (Eq. (5)), deflation,
 //                 secular roots, Loewner vectors and the merge matrix M;
-//                 Q = Q_H (diag(Q1, Q2) M) on 16x16x4 MFMA tiles, sign rule
-// Every kernel fits two 512-thread teams per CU (at most 128 VGPRs and 80 KB
-// of LDS each).
+//                 E = diag(Q1, Q2) M on 16x16x4 MFMA tiles, back-transform of E
+// Every kernel fits two teams per CU (at most 80 KB of LDS each).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -56,6 +59,8 @@ struct Ws {
     Meta *meta;
     float *v;    // with eigenvectors: reflectors v_0 .. v_{n-3} (binary32 rows of n)
     float *tau;  // their tau (zero for a skipped step), n per matrix
+    double *t;       // T: diagonal, off-diagonal (BN values each)
+    int32_t *done;   // per matrix: no divide step (solved by k_big_direct, or non-finite)
     float *e1, *e2;  // eigenvalues only: the children's first and last eigenvector
                      // rows (2 n1 and 2 n2 values apart), in the q1 space
 };
@@ -80,7 +85,6 @@ struct RedSmem {
             alignas(16) double q[2][RHW];
         } s;
     } u;
-    float a[BN], b[BN];
     int badw[RHW];
     int expw[RHW];
 };
@@ -106,7 +110,8 @@ struct RedState {
 template <int B0>
 __device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lane, const int wave,
                                           const HhSelect<HhBlock<BN, RHW>::NA> &sel, RedState &R,
-                                          float *__restrict__ V, float *__restrict__ tau)
+                                          float *__restrict__ V, float *__restrict__ tau,
+                                          double *__restrict__ T)
 {
     using B = HhBlock<BN, RHW>;
     constexpr int A0 = 8 * B0 / B::GI;
@@ -151,8 +156,10 @@ __device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lan
                 V[(int64_t)k * n + row.p1 - pad] = v1;
                 if (lane == 0) tau[k] = float(h.beta * xt0 * xt0);
             }
-            S.b[k] = float(h.alpha);
-            S.a[k + 1] = float(fma(-2.0 * xt0, o0.w0, a00));
+            if (lane == 0) {
+                T[BN + k] = h.alpha;
+                T[k + 1] = fma(-2.0 * xt0, o0.w0, a00);
+            }
         }
         R.xl = R.x1;
         R.nwl = o1.nw;
@@ -163,7 +170,7 @@ __device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lan
         Xn[row.s0] = R.x0;
         Xn[row.s0 + 8] = R.x1;
     });
-    if constexpr (B0 + 1 < BN / 8) red_steps<B0 + 1>(S, n, lane, wave, sel, R, V, tau);
+    if constexpr (B0 + 1 < BN / 8) red_steps<B0 + 1>(S, n, lane, wave, sel, R, V, tau, T);
 }
 
 // Householder tridiagonalization in binary64 as for n <= 64 (hh_product), on
@@ -172,7 +179,7 @@ __device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lan
 // instructions a wave and step at the start, two waves per SIMD with two teams
 // per CU).  One barrier per step instead of three, and each lane's 4 x 16 block
 // shrinks in both directions.  With eigenvectors the reflectors (rounded to
-// binary32) and their tau go to the workspace for k_big_qh.
+// binary32) and their tau go to the workspace for the back-transform.
 __global__ void __launch_bounds__(RT_, 2)
 k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
 {
@@ -180,7 +187,6 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
     const int64_t bi = blockIdx.x;
     if (bi >= batch) return;
     const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
-    const int s = n / 2, n1 = s, n2 = n - s;
     const float *Ab = A + bi * n * n;
     constexpr int SLD = RedSmem::SLD;
     bool bad = false;
@@ -225,9 +231,10 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
     int sh = (emax == 0) ? 0 : fexp<float>::BIAS - 1 - emax;
     sh = min(max(sh, -fexp<float>::SMAX), fexp<float>::SMAX);
     if (anybad) {
-        for (int e = t; e < 2 * n1; e += RT_) ws.c1[bi * 2 * n1 + e] = 0.f;
-        for (int e = t; e < 2 * n2; e += RT_) ws.c2[bi * 2 * n2 + e] = 0.f;
-        if (t == 0) ws.meta[bi] = Meta{0.f, 0, 1, 0};
+        if (t == 0) {
+            ws.meta[bi] = Meta{0.f, 0, 1, 0};
+            ws.done[bi] = 1;
+        }
         return;
     }
     const double hs = double(fexp<float>::pow2(sh));
@@ -250,7 +257,7 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
         const double e0 = entry(row.p0, pad), e1 = entry(row.p1, pad);
         R.x0 = row.p0 > pad ? e0 : 0.0;
         R.x1 = e1;  // p1 >= 64 > pad
-        if (t == 0) S.a[0] = float(hs * double(S.u.st[0]));
+        if (t == 0) ws.t[bi * 2 * BN] = hs * double(S.u.st[0]);
     }
     R.xl = R.nwl = 0.0;
     __syncthreads();  // the staging buffer becomes the step buffers
@@ -263,86 +270,102 @@ k_big_reduce(const float *__restrict__ A, int n, int64_t batch, Ws ws)
     }
     const HhSelect<B::NA> sel(lane);
     red_steps<0>(S, n, lane, wave, sel, R, ws.v ? ws.v + bi * (n - 2) * n : nullptr,
-                 ws.tau ? ws.tau + bi * n : nullptr);
+                 ws.tau ? ws.tau + bi * n : nullptr, ws.t + bi * 2 * BN);
     // b_{n-2} is the pivot column's last value, a_{n-1} the last diagonal entry
     // after the last update (position BN - 1: lane 63 of the last wave)
     if (wave == RHW - 1 && lane == 63) {
-        S.b[n - 2] = float(R.x1);
-        S.a[n - 1] = float(fma(2.0 * R.xl, R.nwl, R.H.a[B::NA - 1][B::NB - 1]));
-    }
-    __syncthreads();
-
-    // tear (Eq. (3)): the two children's diagonals and off-diagonals
-    {
-        const float beta = S.b[s - 1];
-        const float rho = f_abs(beta);
-        float *C1 = ws.c1 + bi * 2 * n1;
-        float *C2 = ws.c2 + bi * 2 * n2;
-        for (int e = t; e < 2 * n1 - 1; e += RT_)
-            C1[e] = (e < n1) ? S.a[e] - (e == s - 1 ? rho : 0.f) : S.b[e - n1];
-        for (int e = t; e < 2 * n2 - 1; e += RT_)
-            C2[e] = (e < n2) ? S.a[s + e] - (e == 0 ? rho : 0.f) : S.b[s + e - n2];
-        if (t == 0) ws.meta[bi] = Meta{beta, sh, 0, 0};
+        double *T = ws.t + bi * 2 * BN;
+        T[BN + n - 2] = R.x1;
+        T[n - 1] = fma(2.0 * R.xl, R.nwl, R.H.a[B::NA - 1][B::NB - 1]);
+        ws.meta[bi] = Meta{0.f, sh, 0, 0};
     }
 }
 
-// ------------------------------------------------------------------ Q_H
-// Q_H = H_0 H_1 ... H_{n-3} in compact-WY blocks of 16 reflectors,
-// H_{16b} ... H_{16b+15} = I - V_b T_b V_b^T (T_b upper triangular), applied to
-// the identity for b = last .. 0 on 16x16x4 binary64 MFMA tiles.  The
+// ------------------------------------------------------------------ back-transform
+// Q = H_0 H_1 ... H_{n-3} V in compact-WY blocks of 16 reflectors,
+// H_{16b} ... H_{16b+15} = I - V_b T_b V_b^T (T_b upper triangular), applied
+// for b = last .. 0 on 16x16x4 binary64 MFMA tiles; Q_H is never formed.  The
 // reflectors come rounded to binary32 (exact to convert back) and are staged
 // in LDS at odd stride; the binary64 Gram matrices G_b = V_b^T V_b of the
 // rounded reflectors and then the T factors sit in packed upper triangles
 // (element (i, j) at j (j + 1) / 2 + i).  T is formed with tau_j = 2 / G(j, j),
 // so each block is exactly orthogonal for the reflectors as stored, up to
-// binary64 rounding; only the final binary32 rounding of Q_H remains
+// binary64 rounding; only the final binary32 rounding of Q remains
 // (binary32 products here would add a few 1e-6 to ||Q^T Q - I||_F at n = 128).
-// One wave per block forms G_b and T_b; after one barrier each wave keeps a
-// 16-column tile of Q in accumulators through all blocks.
-struct QhSmem {
+// One wave per block forms G_b and T_b; after one barrier each wave keeps its
+// 16 columns in accumulators through all blocks, so the sign rule needs no
+// other wave.  Bound by the binary64 matrix rate: 320 products of 16x16x4 a
+// wave at n = 128, 20 us a team.  (Q_H formed first and multiplied in binary32 took
+// the same matrix time, 53 us more for Q_H's kernel, and twice the error.)
+struct BackSmem {
     static constexpr int VLD = BN + 1;
     static constexpr int TP = 136;  // packed 16 x 16 upper triangle
+    static constexpr int TF = (BN / 16) * TP;
     float V[BN * VLD];
-    double tf[(BN / 16) * TP];  // G_b, then T_b
+    double tf[TF];  // G_b, then T_b
 };
 
-__global__ void __launch_bounds__(BT, 4)  // two teams per CU
-k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
+// This wave's 16 columns of the eigenvectors of T; at(i, j) is entry i of vector j.
+template <typename At>
+__device__ __forceinline__ void back_load(Mf<double>::acc (&qa)[BN / 16], const int n, const int t,
+                                          const At &at)
 {
-    __shared__ QhSmem S;
+    const int lane = t & 63, c = 16 * (t >> 6) + (lane & 15);
+#pragma unroll
+    for (int rt = 0; rt < BN / 16; ++rt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int r = 16 * rt + Mf<double>::crow(lane, v);
+            const bool in = r < n && c < n;
+            const double q = at(in ? r : 0, in ? c : 0);
+            qa[rt][v] = in ? q : 0.0;
+        }
+}
+
+// The nb x n reflector block, loaded ahead of the space that it is staged in: lane
+// (j, i0) = (t % BN, t / BN) takes rows i0, i0 + 4, ... at column j.
+constexpr int BACK_RPL = BN * BN / BT, BACK_RS = BT / BN;
+__device__ __forceinline__ void back_fetch(float (&ld)[BACK_RPL], const float *__restrict__ Vb,
+                                           const int n, const int t)
+{
+    const int j = t & (BN - 1), i0 = t / BN;
+#pragma unroll
+    for (int q = 0; q < BACK_RPL; ++q) {
+        const int i = i0 + BACK_RS * q;
+        ld[q] = Vb[(i < n - 2 && j < n) ? i * n + j : 0];
+    }
+}
+__device__ __forceinline__ void back_stage(float *V, const float (&ld)[BACK_RPL], const int n,
+                                           const int t)
+{
+    const int j = t & (BN - 1), i0 = t / BN;
+#pragma unroll
+    for (int q = 0; q < BACK_RPL; ++q) {
+        const int i = i0 + BACK_RS * q;
+        V[i * BackSmem::VLD + j] = (i < n - 2 && j < n) ? ld[q] : 0.f;
+    }
+}
+
+// V, tf: as in BackSmem (the caller has put a barrier behind the last use of the
+// space); ld, tau: the matrix's reflectors.
+__device__ __forceinline__ void back_transform(float *V, double *tf, Mf<double>::acc (&qa)[BN / 16],
+                                               const float (&ld)[BACK_RPL],
+                                               const float *__restrict__ tau, const int n,
+                                               const int t, float *__restrict__ Qb)
+{
     using MF = Mf<double>;
-    constexpr int VLD = QhSmem::VLD;
-    constexpr int TP = QhSmem::TP;
-    const int64_t bi = blockIdx.x;
-    if (bi >= batch) return;
-    if (ws.meta[bi].bad) return;  // the merge writes NaN
-    const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    constexpr int VLD = BackSmem::VLD;
+    constexpr int TP = BackSmem::TP;
+    const int lane = t & 63, wave = t >> 6;
     const int nb = n - 2;  // reflectors
     const int NB = (nb + 15) / 16;
-    {
-        // lane (j, i0) = (t % BN, t / BN) stages rows i0, i0 + 4, ... at column
-        // j (zero outside the nb x n reflector block), loads first
-        constexpr int RPL = BN * BN / BT, RS = BT / BN;
-        const int j = t & (BN - 1), i0 = t / BN;
-        const float *Vb = ws.v + bi * nb * n;
-        float ld[RPL];
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int i = i0 + RS * q;
-            ld[q] = Vb[(i < nb && j < n) ? i * n + j : 0];
-        }
-#pragma unroll
-        for (int q = 0; q < RPL; ++q) {
-            const int i = i0 + RS * q;
-            S.V[i * VLD + j] = (i < nb && j < n) ? ld[q] : 0.f;
-        }
-    }
+    back_stage(V, ld, n, t);
     __syncthreads();
     auto tix = [](int i, int j) { return ((j * (j + 1)) >> 1) + i; };  // i <= j
     const int i16 = lane & 15;
     for (int bk = wave; bk < NB; bk += BT / 64) {
         const int k0 = 16 * bk;
-        double *tb = S.tf + bk * TP;
+        double *tb = tf + bk * TP;
         // G_b: one MFMA chain per row tile at or below the block (rows <= k0 of
         // its reflectors are zero), summed
         MF::acc g = MF::zero();
@@ -352,7 +375,7 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
             MF::acc gt = MF::zero();
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
-                const double vv = S.V[(k0 + i16) * VLD + 16 * rt + MF::crow(lane, s4)];
+                const double vv = V[(k0 + i16) * VLD + 16 * rt + MF::crow(lane, s4)];
                 gt = MF::mma(vv, vv, gt);
             }
             g += gt;
@@ -368,7 +391,7 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
         // tau_j = 2 / G(j, j) on lane j (zero marks a skipped step: v = e_{k+1}
         // stored, no reflection), then broadcast
         double tl = 0.0;
-        if (lane < 16 && k0 + lane < nb && ws.tau[bi * n + k0 + lane] != 0.f)
+        if (lane < 16 && k0 + lane < nb && tau[k0 + lane] != 0.f)
             tl = 2.0 / tb[tix(lane, lane)];
         if (lane < 16) {
             double trow[16];
@@ -391,19 +414,8 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
         }
     }
     __syncthreads();
-    // One 16-column tile per wave.  Block b leaves a column c < 16 b of the
-    // identity unchanged (v_k is zero at rows <= k), so tile ct takes only
-    // the blocks b <= ct; waves w and w + 4 (one SIMD when waves are placed
-    // round robin) take tiles w and 7 - w, which balances the work.
-    const int ct = (wave < 4) ? wave : 11 - wave;
-    if (16 * ct >= n) return;
-    const int c = 16 * ct + i16;
-    MF::acc qa[BN / 16];
-#pragma unroll
-    for (int rt = 0; rt < BN / 16; ++rt)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) qa[rt][v] = (16 * rt + MF::crow(lane, v) == c) ? 1.0 : 0.0;
-    for (int bk = min(NB - 1, ct); bk >= 0; --bk) {
+    if (16 * wave >= n) return;
+    for (int bk = NB - 1; bk >= 0; --bk) {
         const int k0 = 16 * bk;
         // X = V_b^T Q (16 x 16 tile of this column block); staged rows past the
         // last reflector are zero
@@ -413,7 +425,7 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
             if (rt < bk || 16 * rt >= n) continue;
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
-                const double va = S.V[(k0 + i16) * VLD + 16 * rt + MF::crow(lane, s4)];
+                const double va = V[(k0 + i16) * VLD + 16 * rt + MF::crow(lane, s4)];
                 xp[rt & 1] = MF::mma(va, qa[rt][s4], xp[rt & 1]);
             }
         }
@@ -425,7 +437,7 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
 #pragma unroll
         for (int s4 = 0; s4 < 4; ++s4) {
             const int kk = MF::crow(lane, s4);
-            const double ta = (kk >= i16) ? S.tf[bk * TP + tix(i16, kk)] : 0.0;
+            const double ta = (kk >= i16) ? tf[bk * TP + tix(i16, kk)] : 0.0;
             y = MF::mma(ta, x[s4], y);
         }
         // Q -= V_b Y (its operand loads are not hoisted above X: the register
@@ -436,42 +448,174 @@ k_big_qh(int n, int64_t batch, float *__restrict__ Qh, Ws ws)
             if (rt < bk || 16 * rt >= n) continue;
 #pragma unroll
             for (int s4 = 0; s4 < 4; ++s4) {
-                const double vb = -double(S.V[(k0 + MF::crow(lane, s4)) * VLD + 16 * rt + i16]);
+                const double vb = -double(V[(k0 + MF::crow(lane, s4)) * VLD + 16 * rt + i16]);
                 qa[rt] = MF::mma(vb, y[s4], qa[rt]);
             }
         }
     }
-    float *Qb = Qh + bi * n * n;
+    // sign rule: the entry of largest magnitude (lowest row on ties) is positive
+    const int c = 16 * wave + i16;
+    float best = -1.f, bval = 0.f;
+    int brow = 1 << 20;
 #pragma unroll
     for (int rt = 0; rt < BN / 16; ++rt)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * rt + MF::crow(lane, v);
-            if (row < n && c < n) Qb[row * n + c] = float(qa[rt][v]);
+            const float q = float(qa[rt][v]), av = f_abs(q);
+            const bool take = row < n && av > best;
+            best = take ? av : best;
+            brow = take ? row : brow;
+            bval = take ? q : bval;
         }
+    auto least = [&](const float ob, const int orow, const float oval) {
+        const bool take = ob > best || (ob == best && orow < brow);
+        best = take ? ob : best;
+        brow = take ? orow : brow;
+        bval = take ? oval : bval;
+    };
+    least(xmove<16>(best, lane), xmove<16>(brow, lane), xmove<16>(bval, lane));
+    least(xmove<32>(best, lane), xmove<32>(brow, lane), xmove<32>(bval, lane));
+    const float sgn = bval < 0.f ? -1.f : 1.f;
+#pragma unroll
+    for (int rt = 0; rt < BN / 16; ++rt)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = 16 * rt + MF::crow(lane, v);
+            if (row < n && c < n) Qb[row * n + c] = sgn * float(qa[rt][v]);
+        }
+}
+
+// ------------------------------------------------------------------ direct solve
+struct DirSmem {
+    static constexpr int LD = BN / 2 + 1;
+    union {
+        struct {
+            union {
+                // factors from the top and from the bottom of half the
+                // eigenvectors, then the eigenvectors of T, a half each
+                float L[2][BN * LD];
+                struct {
+                    double a[BN], b[BN];
+                } t;               // T, until it is set up
+                DirectGrid<BT> g;  // during the first grid
+            } u;
+            DirectArrays<BN> t;
+        } d;
+        BackSmem q;
+    } u;
+    float lout[BN];
+};
+
+// The spectrum of T directly, as for n <= 64 (direct_solve), and the back-transform;
+// a matrix that it does not take is torn at s = floor(n/2) (Eq. (3)) for
+// the children and the top merge.  The eigenvectors are formed in two halves of
+// 64 columns, whose factors leave room (75 KB) for two teams per CU: one team's
+// serial factorizations run beside the other's matrix products and sections.
+// Batch 512, n = 128: 140 us for the 241 that forming Q_H, the children and the top
+// merge took; 38 without eigenvectors, for 186.  The binary64 pipe bounds it: the sections
+// (about 35 us) and the back-transform's matrix products (40) both fill it.
+__global__ void __launch_bounds__(BT, 4)  // two teams per CU
+k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q,
+             int32_t *__restrict__ info, Ws ws)
+{
+    __shared__ DirSmem S;
+    const int64_t bi = blockIdx.x;
+    if (bi >= batch) return;
+    if (ws.meta[bi].bad) return;  // the merge writes NaN
+    const int t = threadIdx.x, lane = t & 63, wave = __builtin_amdgcn_readfirstlane(t >> 6);
+    constexpr int LD = DirSmem::LD;
+    auto &L = S.u.d.u.L;
+    DirectArrays<BN> &D = S.u.d.t;
+    const double *T = ws.t + bi * 2 * BN;
+    if (t < n) {
+        S.u.d.u.t.a[t] = T[t];
+        S.u.d.u.t.b[t] = t + 1 < n ? T[BN + t] : 0.0;
+    }
+    __syncthreads();
+    if (wave == 0) direct_setup<BN, BT / BN>(D, S.u.d.u.t.a, S.u.d.u.t.b, n, lane);
+    __syncthreads();
+    if (!direct_eigenvalues<BN, BT>(D, S.u.d.u.g, n, t, Q != nullptr, S.lout)) {
+        const int n1 = n / 2, n2 = n - n1;
+        const float beta = float(T[BN + n1 - 1]);
+        const float rho = f_abs(beta);
+        float *C1 = ws.c1 + bi * 2 * n1;
+        float *C2 = ws.c2 + bi * 2 * n2;
+        for (int e = t; e < 2 * n1 - 1; e += BT)
+            C1[e] = (e < n1) ? float(T[e]) - (e == n1 - 1 ? rho : 0.f) : float(T[BN + e - n1]);
+        for (int e = t; e < 2 * n2 - 1; e += BT)
+            C2[e] = (e < n2) ? float(T[n1 + e]) - (e == 0 ? rho : 0.f)
+                             : float(T[BN + n1 + e - n2]);
+        if (t == 0) {
+            ws.meta[bi].beta = beta;
+            ws.done[bi] = 0;
+        }
+        return;
+    }
+    const float unscale = fexp<float>::pow2(-ws.meta[bi].shift);
+    if (t < n) lam[bi * n + t] = unscale * S.lout[t];
+    if (t == 0) {
+        ws.done[bi] = 1;
+        if (info) info[bi] = 0;
+    }
+    if (!Q) return;
+    constexpr int HC = BN / 2, LPR = BT / HC, SG = BN / LPR;
+    const int j = t / LPR, i0 = (t % LPR) * SG;
+    // the factors' two waves: the second team of a CU (its first 256 workgroups are
+    // dealt out one to a CU) takes the two SIMDs that the first one leaves idle
+    const int tf = t ^ ((bi >> 8 & 1) * 128);
+    float z0[SG], z[SG] = {};  // the first and the second half's entries
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int s = 0; s < SG; ++s) z0[s] = z[s];
+        // a serial chain: ahead of the other team's matrix products (25 us behind
+        // them, 10 so)
+        __builtin_amdgcn_s_setprio(3);
+        direct_factors<BN, HC, BT / BN, LD>(D, L[0], L[1], n, tf, HC * h);
+        __builtin_amdgcn_s_setprio(0);
+        __syncthreads();
+        // opaque: rows and bounds are formed here, not kept through the factors
+        int th = t, nh = n;
+        asm volatile("" : "+v"(th), "+s"(nh));
+        const bool act = HC * h + th / LPR < nh;
+        const int e = act ? th / LPR : 0;
+        direct_vector<BN, LPR, LD>(D, L[0] + e, L[1] + e, D.lam[HC * h + e], act, nh, th, z);
+        __syncthreads();
+    }
+#pragma unroll
+    for (int s = 0; s < SG; ++s) {
+        L[0][(i0 + s) * LD + j] = z0[s];
+        L[1][(i0 + s) * LD + j] = z[s];
+    }
+    __syncthreads();
+    auto at = [&](const int i, const int j) -> float & { return L[j >= HC][i * LD + (j & (HC - 1))]; };
+    if (direct_close(D)) {
+        if (wave == 0) direct_orthogonal(D, n, lane, at);
+        __syncthreads();
+    }
+    float ld[BACK_RPL];
+    back_fetch(ld, ws.v + bi * (n - 2) * n, n, t);
+    Mf<double>::acc qa[BN / 16];
+    back_load(qa, n, t, at);
+    __syncthreads();
+    back_transform(S.u.q.V, S.u.q.tf, qa, ld, ws.tau + bi * n, n, t, Q + bi * n * n);
 }
 
 // ------------------------------------------------------------------ top merge
 struct MrgSmem {
     static constexpr int LD = BN + 1;  // odd stride; column BN is the padding column of M
     // rows 0 and 1 first hold the children's eigenvalues and z; then the
-    // merge matrix M; then E = diag(Q1, Q2) M
+    // merge matrix M; then E = diag(Q1, Q2) M; then the reflectors
     float M[BN * LD];
-    // merge state; after the secular solve, the sign candidates of Q
-    struct {
+    union {
         MergeArrays<float, BN> m;
+        double tf[BackSmem::TF];
     } u;
     float lout[BN];  // eigenvalues, ascending
     float red[4][2];
     uint64_t live[2], dead[2], cmask[2];
     int capped, anyrot;
-};
-
-// Per wave and column: the entry of largest magnitude of the wave's rows of Q
-// (lowest row on ties), signed.
-struct SignCand {
-    float val;
-    int row;
 };
 
 __global__ void __launch_bounds__(BT, 4)  // two teams per CU
@@ -493,6 +637,7 @@ k_big_merge(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q
         if (t == 0 && info) info[bi] = -1;
         return;
     }
+    if (ws.done[bi]) return;
     const float *Q1 = ws.q1 + bi * n1 * n1;
     const float *Q2 = ws.q2 + bi * n2 * n2;
     const float rho = f_abs(md.beta);
@@ -694,11 +839,11 @@ k_big_merge(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q
     roots_vectors<float, BN, BT, BN / (BT / BN)>(S, n, 0, t, S.lout, BN / 2);
 
     // ---- Q = Q_H (diag(Q1, Q2) M) with the sign rule ------------------------
-    // Wave w takes row tile w of both products on 16x16x4 MFMA tiles, its A
-    // rows (diag(Q1, Q2), then Q_H) loaded from HBM into registers, B from
-    // LDS; E = diag(Q1, Q2) M replaces M.  Each wave then leaves, per column,
-    // its entry of largest magnitude (lowest row on ties), a barrier later
-    // the column's sign is known, and each wave stores its rows.
+    const float unscale = fexp<float>::pow2(-md.shift);
+    for (int e = t; e < n; e += BT) lam[bi * n + e] = unscale * S.lout[e];
+    if (t == 0 && info) info[bi] = S.capped + ws.i1[bi] + ws.i2[bi];
+    // Wave w takes row tile w of E = diag(Q1, Q2) M on 16x16x4 MFMA tiles, its A
+    // rows loaded from HBM into registers, B from LDS; E replaces M.
     if (Qb) {
         using MF = Mf<float>;
         constexpr int KS = BN / 4;  // k steps
@@ -740,97 +885,15 @@ k_big_merge(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q
 #pragma unroll
                 for (int v = 0; v < 4; ++v)
                     S.M[(16 * wave + MF::crow(lane, v)) * LD + 16 * ct + i16] = acc[ct][v];
-            // Q_H rows of this tile (held in the Q output; only this wave
-            // reads or writes them)
-#pragma unroll
-            for (int s4 = 0; s4 < KS; ++s4) {
-                const int k = 4 * s4 + kk;
-                a[s4] = Qb[(r < n && k < n) ? r * n + k : 0];
-            }
-#pragma unroll
-            for (int s4 = 0; s4 < KS; ++s4) {
-                const int k = 4 * s4 + kk;
-                a[s4] = (r < n && k < n) ? a[s4] : 0.f;
-            }
         }
         __syncthreads();  // E complete
-        SignCand *cand = reinterpret_cast<SignCand *>(&S.u);  // [wave][column]
-        float *csign = reinterpret_cast<float *>(cand + (BT / 64) * BN);
-        static_assert(sizeof(S.u) >= sizeof(SignCand) * (BT / 64) * BN + sizeof(float) * BN,
-                      "sign candidates");
-        if (rows) {
-#pragma unroll
-            for (int ct = 0; ct < BN / 16; ++ct) acc[ct] = MF::zero();
-#pragma unroll
-            for (int s4 = 0; s4 < KS; ++s4) {
-                const float *erow = S.M + (4 * s4 + kk) * LD + i16;
-#pragma unroll
-                for (int ct = 0; ct < BN / 16; ++ct) acc[ct] = MF::mma(a[s4], erow[16 * ct], acc[ct]);
-            }
-#pragma unroll
-            for (int ct = 0; ct < BN / 16; ++ct) {
-                float best = -1.f, bval = 0.f;
-                int brow = 1 << 20;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = 16 * wave + MF::crow(lane, v);
-                    const float av = f_abs(acc[ct][v]);
-                    const bool take = row < n && (av > best || (av == best && row < brow));
-                    best = take ? av : best;
-                    brow = take ? row : brow;
-                    bval = take ? acc[ct][v] : bval;
-                }
-                {
-                    const float ob = xmove<16>(best, lane);
-                    const int orow = xmove<16>(brow, lane);
-                    const float oval = xmove<16>(bval, lane);
-                    const bool take = ob > best || (ob == best && orow < brow);
-                    best = take ? ob : best;
-                    brow = take ? orow : brow;
-                    bval = take ? oval : bval;
-                }
-                {
-                    const float ob = xmove<32>(best, lane);
-                    const int orow = xmove<32>(brow, lane);
-                    const float oval = xmove<32>(bval, lane);
-                    const bool take = ob > best || (ob == best && orow < brow);
-                    brow = take ? orow : brow;
-                    bval = take ? oval : bval;
-                }
-                if (kk == 0) cand[wave * BN + 16 * ct + i16] = SignCand{bval, brow};
-            }
-        }
+        float ld[BACK_RPL];
+        back_fetch(ld, ws.v + bi * (n - 2) * n, n, t);
+        Mf<double>::acc qa[BN / 16];
+        back_load(qa, n, t, [&](const int i, const int j) { return S.M[i * LD + j]; });
         __syncthreads();
-        if (t < n) {
-            float best = -1.f, bval = 0.f;
-            int brow = 1 << 20;
-            for (int w = 0; w < BT / 64 && 16 * w < n; ++w) {
-                const SignCand cw = cand[w * BN + t];
-                const float av = f_abs(cw.val);
-                const bool take = cw.row < n && (av > best || (av == best && cw.row < brow));
-                best = take ? av : best;
-                brow = take ? cw.row : brow;
-                bval = take ? cw.val : bval;
-            }
-            csign[t] = (bval < 0.f) ? -1.f : 1.f;
-        }
-        __syncthreads();
-        if (rows) {
-#pragma unroll
-            for (int ct = 0; ct < BN / 16; ++ct) {
-                const int c = 16 * ct + i16;
-                const float sgn = (c < n) ? csign[c] : 1.f;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const int row = 16 * wave + MF::crow(lane, v);
-                    if (row < n && c < n) Qb[row * n + c] = sgn * acc[ct][v];
-                }
-            }
-        }
+        back_transform(S.M, S.u.tf, qa, ld, ws.tau + bi * n, n, t, Qb);
     }
-    const float unscale = fexp<float>::pow2(-md.shift);
-    for (int e = t; e < n; e += BT) lam[bi * n + e] = unscale * S.lout[e];
-    if (t == 0 && info) info[bi] = S.capped + ws.i1[bi] + ws.i2[bi];
 }
 
 // ------------------------------------------------------------------ host
@@ -868,7 +931,10 @@ bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *la
     const size_t m_bytes = align_up(B * sizeof(Meta));
     const size_t v_bytes = Q ? align_up(B * (n - 2) * n * sizeof(float)) : 0;
     const size_t t_bytes = Q ? align_up(B * n * sizeof(float)) : 0;
-    const size_t need = c_bytes + q_bytes + l_bytes + i_bytes + m_bytes + v_bytes + t_bytes;
+    const size_t d_bytes = align_up(B * 2 * BN * sizeof(double));
+    const size_t f_bytes = align_up(B * sizeof(int32_t));
+    const size_t need =
+        c_bytes + q_bytes + l_bytes + i_bytes + m_bytes + d_bytes + f_bytes + v_bytes + t_bytes;
     const bool capturing = stream_capturing(s);
     char *base = nullptr;
     {
@@ -911,18 +977,24 @@ bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *la
         base = (char *)b->ptr;
     }
     Ws ws;
-    ws.c1 = (float *)base;
+    auto take = [&](const size_t bytes) {
+        char *p = base;
+        base += bytes;
+        return p;
+    };
+    ws.c1 = (float *)take(c_bytes);
     ws.c2 = ws.c1 + B * 2 * n1;
-    ws.q1 = (float *)(base + c_bytes);
+    ws.q1 = (float *)take(q_bytes);
     ws.q2 = ws.q1 + B * n1 * n1;
-    ws.l1 = (float *)(base + c_bytes + q_bytes);
+    ws.l1 = (float *)take(l_bytes);
     ws.l2 = ws.l1 + B * n1;
-    ws.i1 = (int32_t *)(base + c_bytes + q_bytes + l_bytes);
+    ws.i1 = (int32_t *)take(i_bytes);
     ws.i2 = ws.i1 + B;
-    ws.meta = (Meta *)(base + c_bytes + q_bytes + l_bytes + i_bytes);
-    ws.v = Q ? (float *)(base + c_bytes + q_bytes + l_bytes + i_bytes + m_bytes) : nullptr;
-    ws.tau = Q ? (float *)(base + c_bytes + q_bytes + l_bytes + i_bytes + m_bytes + v_bytes)
-               : nullptr;
+    ws.meta = (Meta *)take(m_bytes);
+    ws.t = (double *)take(d_bytes);
+    ws.done = (int32_t *)take(f_bytes);
+    ws.v = Q ? (float *)take(v_bytes) : nullptr;
+    ws.tau = Q ? (float *)take(t_bytes) : nullptr;
     ws.e1 = Q ? nullptr : ws.q1;
     ws.e2 = Q ? nullptr : ws.q1 + B * 2 * n1;
 
@@ -930,24 +1002,22 @@ bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *la
                        (int64_t)batch, ws);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_big_reduce launch");
-    if (Q) {
-        hipLaunchKernelGGL(k_big_qh, dim3((unsigned)batch), dim3(BT), 0, s, n, (int64_t)batch,
-                           (float *)Q, ws);
-        e = hipGetLastError();
-        if (e != hipSuccess) return hip_fail(e, "k_big_qh launch");
-    }
+    hipLaunchKernelGGL(k_big_direct, dim3((unsigned)batch), dim3(BT), 0, s, n, (int64_t)batch,
+                       (float *)lam, (float *)Q, info, ws);
+    e = hipGetLastError();
+    if (e != hipSuccess) return hip_fail(e, "k_big_direct launch");
     const bed_tune dflt = default_tune();
-    // the halves: eigenvectors, or (eigenvalues only) just the end rows z needs
+    // the halves of what is left: eigenvectors, or (eigenvalues only) just the end rows z needs
     float *q1 = Q ? ws.q1 : nullptr, *q2 = Q ? ws.q2 : nullptr;
     if (n1 == n2) {
         e = launch_tri(class_shape(size_class(n1), dflt), ws.c1, n1, 2 * batch, ws.l1, q1,
-                       ws.i1, ws.e1, s);
+                       ws.i1, ws.e1, ws.done, batch, s);
     } else {
         e = launch_tri(class_shape(size_class(n1), dflt), ws.c1, n1, batch, ws.l1, q1, ws.i1,
-                       ws.e1, s);
+                       ws.e1, ws.done, batch, s);
         if (e == hipSuccess)
             e = launch_tri(class_shape(size_class(n2), dflt), ws.c2, n2, batch, ws.l2, q2,
-                           ws.i2, ws.e2, s);
+                           ws.i2, ws.e2, ws.done, batch, s);
     }
     if (e != hipSuccess) return hip_fail(e, "child solve launch");
     hipLaunchKernelGGL(k_big_merge, dim3((unsigned)batch), dim3(BT), 0, s, n, (int64_t)batch,

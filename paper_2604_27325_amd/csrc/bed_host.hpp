@@ -34,8 +34,9 @@ bed_tune tuned_or_default_uniform(bed_dtype dt, int64_t batch, int32_t n);
 bed_status plan_run_impl(const bed_plan *p, const void *A, void *lam, void *Q, int32_t *info,
                          hipStream_t s);
 
-// Uniform batch of order 64 < n <= NMAX_BIG (binary32): reduction and tearing
-// kernel, the two halves on the n <= 64 kernels, top-merge kernel.  Q may be
+// Uniform batch of order 64 < n <= NMAX_BIG (binary32): reduction, direct
+// solve; for what that leaves the two halves on the n <= 64 kernels and the top
+// merge.  Q may be
 // NULL (eigenvalues only).
 bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *lam, void *Q,
                      int32_t *info, hipStream_t s);

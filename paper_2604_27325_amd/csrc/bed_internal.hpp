@@ -57,9 +57,11 @@ hipError_t launch_small(bed_dtype dt, const void *A, int n, int64_t batch, void 
 // Uniform batch of binary32 tridiagonal matrices (diagonal then off-diagonal,
 // 2n values apart); team shapes (32, 128), (32, 256) and (64, 256).  With Q == nullptr
 // (eigenvalues only) ends, if not null, receives each matrix's first and last
-// eigenvector rows (2n values apart).
+// eigenvector rows (2n values apart).  skip: one entry per matrix or, with
+// batch = 2 skip_count, per pair (b, b + skip_count); set entries are left alone.
 hipError_t launch_tri(TeamShape ts, const float *tri, int n, int64_t batch, float *lam, float *Q,
-                      int32_t *info, float *ends, hipStream_t s);
+                      int32_t *info, float *ends, const int32_t *skip, int64_t skip_count,
+                      hipStream_t s);
 
 // Work-list launch.  counter == nullptr: workgroup i handles items i, i+grid,
 // ... (static).  counter != nullptr: persistent workgroups pull items from

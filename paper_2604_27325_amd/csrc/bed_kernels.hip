@@ -17,14 +17,16 @@ bool team_supported(bed_dtype dt, TeamShape ts)
 }
 
 hipError_t launch_tri(TeamShape ts, const float *tri, int n, int64_t batch, float *lam, float *Q,
-                      int32_t *info, float *ends, hipStream_t s)
+                      int32_t *info, float *ends, const int32_t *skip, int64_t skip_count,
+                      hipStream_t s)
 {
     if (batch <= 0) return hipSuccess;
-    if (!leaf_supported(ts.leaf)) return hipErrorInvalidValue;
+    if (!leaf_supported(ts.leaf) || batch > 2 * skip_count) return hipErrorInvalidValue;
 #define X(NM, NTT)                                                                          \
     if (ts.nmax == NM && ts.nt == NTT) {                                                    \
         hipLaunchKernelGGL((k_syevd_tri<float, NM, NTT>), dim3((unsigned)batch), dim3(NTT), \
-                           0, s, tri, n, batch, lam, Q, info, ends, ts.leaf);               \
+                           0, s, tri, n, batch, lam, Q, info, ends, skip, skip_count,       \
+                           ts.leaf);                                                        \
         return hipGetLastError();                                                           \
     }
     X(32, 128)

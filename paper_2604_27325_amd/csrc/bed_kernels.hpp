@@ -24,15 +24,16 @@ k_syevd_uniform(const T *__restrict__ A, int n, int64_t batch, T *__restrict__ l
 // Uniform batch of tridiagonal matrices: matrix b is the diagonal (n values)
 // then the off-diagonal (n - 1 values) at tri + 2 n b.  Without Q, ends
 // (nullable) receives the first and last rows of each eigenvector matrix at
-// ends + 2 n b.
+// ends + 2 n b.  Matrix b is left alone where skip[b modulo skip_count] is set.
 template <typename T, int NMAX, int NT>
 __global__ void __launch_bounds__(NT) BED_OCC(NMAX, NT)
 k_syevd_tri(const T *__restrict__ tri, int n, int64_t batch, T *__restrict__ lam,
-            T *__restrict__ Q, int32_t *__restrict__ info, T *__restrict__ ends, int leaf)
+            T *__restrict__ Q, int32_t *__restrict__ info, T *__restrict__ ends,
+            const int32_t *__restrict__ skip, int64_t skip_count, int leaf)
 {
     __shared__ Smem<T, NMAX, NT> S;
     const int64_t b = blockIdx.x;
-    if (b >= batch) return;
+    if (b >= batch || skip[b < skip_count ? b : b - skip_count]) return;
     const int64_t n2 = (int64_t)n * n;
     syevd_team<T, NMAX, NT, true>(tri + b * 2 * n, n, lam + b * n, Q ? Q + b * n2 : nullptr,
                                   info ? info + b : nullptr, S, threadIdx.x, leaf,

@@ -138,6 +138,25 @@ struct MergeArrays {
     T nrho[NMAX], nzz[NMAX], nfro[NMAX];
 };
 
+// Direct solver: det and counts on the first grid.
+template <int NT>
+struct DirectGrid {
+    double f[NT];
+    int c[NT];
+};
+// Rows {a_i, b_{i-1}^2} from the top and {a_i, b_i^2} from the bottom, b_i in
+// both orders, eigenvalues.
+template <int NMAX>
+struct DirectArrays {
+    alignas(16) double ab[2][NMAX][2];
+    double b[2][NMAX];
+    double lam[NMAX];
+    double lo, hi, unscale;
+    int cell[NMAX];
+    uint64_t close[(NMAX + 63) / 64];  // bit j: eigenvalues j and j + 1 are close
+    int ok;
+};
+
 template <typename T, int NMAX, int NT>
 struct Smem {
     static constexpr int LD = NMAX + 1;  // odd row stride: column walks hit distinct banks
@@ -167,18 +186,10 @@ struct Smem {
             alignas(16) double sc[2][4];
         } h;
         MergeArrays<T, NMAX> m;
-        struct {  // direct solver: rows {a_i, b_{i-1}^2} from the top and {a_i, b_i^2} from
-                  // the bottom, b_i in both orders, eigenvalues, first grid
-            alignas(16) double ab[2][NMAX][2];
-            double b[2][NMAX];
-            double lam[NMAX];
-            double lo, hi, unscale;
-            double gf[NT];
-            int gc[NT];
-            int cell[NMAX];
-            uint64_t close;  // j: eigenvalues j and j + 1 are close
-            int ok;
-        } t;
+        struct {  // direct solver
+            DirectArrays<NMAX> t;
+            DirectGrid<NT> g;
+        } d;
         struct {  // back-transform: per block of 16 reflectors, Gram matrix and T factor
             // 16 x 16 tiles with row stride 17 (bank-conflict free column reads)
             T gram[((NMAX + 13) / 16) * 272];
@@ -1399,16 +1410,24 @@ template <int LPR> __device__ __forceinline__ int direct_order(const int n)
 {
     return LPR == 8 ? (n + 15) & ~15 : (n + 7) & ~7;
 }
-template <typename T, int NMAX, int NT>
-__device__ __forceinline__ void direct_setup(Smem<T, NMAX, NT>& S, const int n, const int lane)
+template <int NMAX, int LPR>
+__device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double* ta,
+                                             const double* tb, const int n, const int lane)
 {
-    const int e = lane;
-    const bool in = e < n;
-    const double a = S.ta[in ? e : 0];
-    const double bl = (in && e > 0) ? S.tb[e - 1] : 0.0;
-    const double br = (e + 1 < n) ? S.tb[e] : 0.0;
-    const double r = f_abs(bl) + f_abs(br);
-    float hi = in ? float(a + r) : -3e38f, nlo = in ? float(r - a) : -3e38f;
+    constexpr int R = NMAX > 64 ? NMAX / 64 : 1;  // rows per lane
+    double a[R], bl[R], br[R];
+    float hi = -3e38f, nlo = -3e38f;
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int e = lane + 64 * k;
+        const bool in = e < n;
+        a[k] = ta[in ? e : 0];
+        bl[k] = (in && e > 0) ? tb[e - 1] : 0.0;
+        br[k] = (e + 1 < n) ? tb[e] : 0.0;
+        const double r = f_abs(bl[k]) + f_abs(br[k]);
+        hi = in ? f_max(hi, float(a[k] + r)) : hi;
+        nlo = in ? f_max(nlo, float(r - a[k])) : nlo;
+    }
 #define BED_MAX_STAGE(ST) hi = f_max(hi, xmove<ST>(hi, lane)), nlo = f_max(nlo, xmove<ST>(nlo, lane))
     BED_MAX_STAGE(1);
     BED_MAX_STAGE(2);
@@ -1420,28 +1439,33 @@ __device__ __forceinline__ void direct_setup(Smem<T, NMAX, NT>& S, const int n, 
     const int ex = exp_field(f_max(hi, nlo));
     const int sh = min(max(fexp<float>::BIAS - 1 - ex, -fexp<float>::SMAX), fexp<float>::SMAX);
     const double sc = double(fexp<float>::pow2(sh));
-    const int m = direct_order<NT / NMAX>(n);
-    if (e < m) {
-        const double as = in ? a * sc : 4.0, bs = bl * sc, bt = br * sc;
-        S.u.t.ab[0][e][0] = as;
-        S.u.t.ab[0][e][1] = bs * bs;
-        S.u.t.ab[1][m - 1 - e][0] = as;
-        S.u.t.ab[1][m - 1 - e][1] = bt * bt;
-        S.u.t.b[0][e] = bt;
-        S.u.t.b[1][in ? n - 1 - e : e] = in ? bs : 0.0;  // coupling of row e to the row above
-        S.u.t.cell[e] = -2;
+    const int m = direct_order<LPR>(n);
+#pragma unroll
+    for (int k = 0; k < R; ++k) {
+        const int e = lane + 64 * k;
+        const bool in = e < n;
+        if (e < m) {
+            const double as = in ? a[k] * sc : 4.0, bs = bl[k] * sc, bt = br[k] * sc;
+            D.ab[0][e][0] = as;
+            D.ab[0][e][1] = bs * bs;
+            D.ab[1][m - 1 - e][0] = as;
+            D.ab[1][m - 1 - e][1] = bt * bt;
+            D.b[0][e] = bt;
+            D.b[1][in ? n - 1 - e : e] = in ? bs : 0.0;  // coupling of row e to the row above
+            D.cell[e] = -2;
+        }
     }
-    if (e == 0) {
-        S.u.t.lo = -double(nlo) * sc - 1e-6;
-        S.u.t.hi = double(hi) * sc + 1e-6;
-        S.u.t.unscale = double(fexp<float>::pow2(-sh));
-        S.u.t.ok = (n >= 2 && ex > fexp<float>::BIAS - 64) ? 1 : 0;
+    if (lane == 0) {
+        D.lo = -double(nlo) * sc - 1e-6;
+        D.hi = double(hi) * sc + 1e-6;
+        D.unscale = double(fexp<float>::pow2(-sh));
+        D.ok = (n >= 2 && ex > fexp<float>::BIAS - 64) ? 1 : 0;
     }
 }
 
 // Minors of T - x I over `blocks` blocks of eight rows of a table {a, b^2}, p_i =
 // (a_i - x) p_{i-1} - b^2 p_{i-2}: the last two (p1, p0) and the number of sign
-// changes.  |a_i - x| <= 2, so n <= 64 minors stay within 2^64.
+// changes.  |a_i - x| <= 2, so n <= 128 minors stay within 2^192.
 __device__ __forceinline__ int direct_minors(const double* rows, const int blocks, const double x,
                                              double& p1, double& p0)
 {
@@ -1516,21 +1540,21 @@ __device__ __forceinline__ double direct_det(const double (*ab)[NMAX][2], const 
 // 2^-44 of the interval and the points enclose this eigenvalue alone (the
 // cubic's own error is then at rounding level).  About four rounds after the grid.
 // With vectors: every gap at least DIRECT_GAP.  Returns whether solved.
-template <typename T, int NMAX, int NT>
-__device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, const int t,
-                                             const bool want_q, T* __restrict__ Lc)
+template <int NMAX, int NT>
+__device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, DirectGrid<NT>& G,
+                                                   const int n, const int t, const bool want_q,
+                                                   float* __restrict__ Lc)
 {
     constexpr int LPR = NT / NMAX;
-    constexpr int LD = Smem<T, NMAX, NT>::LD;
     static_assert(LPR == 4 || LPR == 8, "lanes per eigenvalue");
     const int lane = t & 63;
     const int m = direct_order<LPR>(n);
-    if (!S.u.t.ok) return false;
+    if (!D.ok) return false;
     const int j = t / LPR, sub = t % LPR;
     const bool act = j < n;
     bool bad = false;
     {
-        const double glo = S.u.t.lo, ghi = S.u.t.hi;
+        const double glo = D.lo, ghi = D.hi;
         // grid points: lane pairs of LPR = 8 share one
         constexpr int NG = LPR == 8 ? NT / 2 : NT;
         const int gi = LPR == 8 ? (t >> 3) * 4 + (t & 3) : t;
@@ -1544,34 +1568,34 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
         {
             int c;
             bool tiny;
-            const double f = direct_det<LPR, NMAX>(S.u.t.ab, m, sub, grid(gi), c, tiny);
+            const double f = direct_det<LPR, NMAX>(D.ab, m, sub, grid(gi), c, tiny);
             bad = tiny;
             if (LPR == 4 || sub < 4) {
-                S.u.t.gf[gi] = f;
-                S.u.t.gc[gi] = c;
+                G.f[gi] = f;
+                G.c[gi] = c;
             }
             team_sync<NT>();
             if (LPR == 4 || sub < 4) {
                 // eigenvalues between this point and the next (before the first)
-                const int cn = (gi + 1 < NG) ? S.u.t.gc[gi + 1] : n;
-                for (int q = max(c, 0); q < min(cn, n); ++q) S.u.t.cell[q] = gi;
+                const int cn = (gi + 1 < NG) ? G.c[gi + 1] : n;
+                for (int q = max(c, 0); q < min(cn, n); ++q) D.cell[q] = gi;
                 if (gi == 0)
-                    for (int q = 0; q < min(c, n); ++q) S.u.t.cell[q] = -1;
+                    for (int q = 0; q < min(c, n); ++q) D.cell[q] = -1;
             }
             team_sync<NT>();
-            const int cell = act ? S.u.t.cell[j] : -2;
-            if (cell >= 0) lo = grid(cell), clo = S.u.t.gc[cell];
-            if (cell >= -1 && cell + 1 < NG) hi = grid(cell + 1), chi = S.u.t.gc[cell + 1];
+            const int cell = act ? D.cell[j] : -2;
+            if (cell >= 0) lo = grid(cell), clo = G.c[cell];
+            if (cell >= -1 && cell + 1 < NG) hi = grid(cell + 1), chi = G.c[cell + 1];
             const int k0 = min(max(cell - 1, 0), NG - 4);
             have = cell >= -1;
             {
-                const int ca = S.u.t.gc[k0], cb = S.u.t.gc[k0 + 3];
+                const int ca = G.c[k0], cb = G.c[k0 + 3];
                 strict = ca == j && cb == j + 1;
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 X[q] = grid(k0 + q);
-                F[q] = S.u.t.gf[k0 + q];
+                F[q] = G.f[k0 + q];
             }
         }
         const int pt = sub & 3;
@@ -1615,7 +1639,7 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
             const double x = err < 0.25 * w ? xn : fma(w, even, lo);
             int c;
             bool tiny;
-            const double f = direct_det<LPR, NMAX>(S.u.t.ab, m, sub, x, c, tiny);
+            const double f = direct_det<LPR, NMAX>(D.ab, m, sub, x, c, tiny);
             bad = bad || (tiny && !done);
             int C[4];
             bool Bl[4];
@@ -1642,185 +1666,254 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
             ++rounds;
         }
         if (act && sub == 0) {
-            S.u.t.lam[j] = lam;
-            Lc[j] = T(lam * S.u.t.unscale);
+            D.lam[j] = lam;
+            Lc[j] = float(lam * D.unscale);
         }
     }
-    if (__ballot(bad) && lane == 0) S.u.t.ok = 0;
+    if (__ballot(bad) && lane == 0) D.ok = 0;
     team_sync<NT>();
     BED_PHASE(3);
-    if (want_q && t < 64) {
-        const double gap = t + 1 < n ? S.u.t.lam[t + 1 < n ? t + 1 : 0] - S.u.t.lam[t < n ? t : 0] : 1.0;
+    constexpr int CW = (NMAX + 63) / 64;  // words of the mask of close pairs
+    if (want_q && t < 64 * CW) {
+        const double gap = t + 1 < n ? D.lam[t + 1 < n ? t + 1 : 0] - D.lam[t < n ? t : 0] : 1.0;
         const uint64_t close = __ballot(!(gap >= DIRECT_CLOSE));
-        if (lane == 0) S.u.t.close = close;
-        if (__ballot(!(gap >= DIRECT_GAP)) != 0 || __popcll(close) > DIRECT_MOST) S.u.t.ok = 0;
+        if (lane == 0) D.close[t >> 6] = close;
+        if (__ballot(!(gap >= DIRECT_GAP)) != 0 || __popcll(close) > DIRECT_MOST) D.ok = 0;
     }
     team_sync<NT>();
-    if (!S.u.t.ok) return false;
-    if (!want_q) return true;
+    return D.ok != 0;
+}
 
-    // Factors of T - lambda I from the top (L D L^T) and from the bottom (U D
-    // U^T), one lane each per eigenvalue: l_i = b / D_i toward the next row,
-    // rounded to T (a relative perturbation of the vector's entries).  A zero
-    // pivot becomes 1e-25, far below the rounding of T.
-    if (t < 2 * NMAX) {
-        const int e = t % NMAX;
-        const bool up = t / NMAX != 0;
-        if (e < n) {
-            const double x = S.u.t.lam[e];
-            const double* ar = &S.u.t.ab[up ? 1 : 0][up ? m - n : 0][0];
-            const double* br = &S.u.t.b[up ? 1 : 0][0];
-            T* L = up ? S.Q1 + (n - 1) * LD + e : S.Q0 + e;
-            const int dL = up ? -LD : LD;
-            double bp = 0.0, l = 0.0;
+// Factors of T - lambda I from the top (L D L^T) and from the bottom (U D U^T)
+// for the NC eigenvalues from c0 on, one lane each per eigenvalue: l_i = b / D_i
+// toward the next row, rounded to binary32 (a relative perturbation of the
+// vector's entries).  A zero pivot becomes 1e-25, far below the rounding of T.
+template <int NMAX, int NC, int LPR, int LD>
+__device__ __forceinline__ void direct_factors(const DirectArrays<NMAX>& D, float* Lp, float* Lm,
+                                               const int n, const int t, const int c0)
+{
+    if (t >= 2 * NC) return;
+    const int j = t % NC, e = c0 + j;
+    const bool up = t / NC != 0;
+    if (e >= n) return;
+    const double x = D.lam[e];
+    const double* ar = &D.ab[up ? 1 : 0][up ? direct_order<LPR>(n) - n : 0][0];
+    const double* bk = &D.b[up ? 1 : 0][0];
+    if (up && n < NMAX) Lm[n * LD + j] = 0.f;  // below the last row (its coupling is zero)
+    float* L = up ? Lm + (n - 1) * LD + j : Lp + j;
+    const int dL = up ? -LD : LD;
+    double bp = 0.0, l = 0.0;
 #pragma unroll 4
-            for (int k = 0; k < n; ++k) {
-                const double bn = br[k];
-                double D = fma(-bp, l, ar[2 * k] - x);
-                D = f_abs(D) < 1e-25 ? 1e-25 : D;
-                double r = __builtin_amdgcn_rcp(D);
-                r = fma(r, fma(-D, r, 1.0), r);
-                r = fma(r, fma(-D, r, 1.0), r);
-                l = bn * r;
-                *L = T(l);
-                L += dL;
-                bp = bn;
-            }
-        }
+    for (int k = 0; k < n; ++k) {
+        const double bn = bk[k];
+        double d = fma(-bp, l, ar[2 * k] - x);
+        d = f_abs(d) < 1e-25 ? 1e-25 : d;
+        // b / d: one third-order step from the hardware's estimate
+        const double r = __builtin_amdgcn_rcp(d), br = bn * r, er = fma(-d, r, 1.0);
+        l = fma(br, fma(er, er, er), br);
+        *L = float(l);
+        L += dL;
+        bp = bn;
     }
-    team_sync<NT>();
-    BED_PHASE(6);
-    // Twist at the row of smallest |gamma_i| = |e_i^T (T - lambda)^{-1} e_i|^{-1},
-    // z = 1 there, and products of -l outward; rows of a group's lane are
-    // consecutive, its products are finished by a scan over the group.
+}
+
+// Entries i0 = SG (t % LPR), i0 + 1, ... of the eigenvector of eigenvalue x (Lp, Lm:
+// its columns of the factors), of norm one.  Twist at the row of smallest
+// |gamma_i| = |e_i^T (T - x)^{-1} e_i|^{-1}, z = 1 there, and products of -l
+// outward; rows of a group's lane are consecutive, its products are finished by
+// a scan over the group.  act: lanes that hold an eigenvalue (the others compute
+// on a valid column).  Rows past n hold anything: none becomes the twist, and the
+// products stop at n.
+template <int NMAX, int LPR, int LD>
+__device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const float* Lp,
+                                              const float* Lm, const double x, const bool act,
+                                              const int n, const int t, float (&out)[NMAX / LPR])
+{
+    using T = float;
+    constexpr int SG = NMAX / LPR;
+    const int lane = t & 63, sub = t % LPR;
+    const int i0 = sub * SG;
+    T lp[SG], lm[SG];
+#pragma unroll
+    for (int s = 0; s < SG; ++s) {
+        lp[s] = Lp[(i0 + s) * LD];
+        lm[s] = Lm[(i0 + s) * LD];
+    }
+    T best = T(3e38);
+    int r = 0;
     {
-        constexpr int SG = NMAX / LPR;
-        const int e = act ? j : 0;
-        const double x = S.u.t.lam[e];
-        const T* Lp = S.Q0 + e;  // toward the row below
-        const T* Lm = S.Q1 + e;  // toward the row above
-        const int i0 = sub * SG;
-        T lp[SG], lm[SG];
+        const int ia = max(i0 - 1, 0);
+        T lprev = Lp[ia * LD];  // of the row before
+        T bprev = i0 > 0 ? T(D.b[0][ia]) : T(0);
+        const T lafter = Lm[min(i0 + SG, NMAX - 1) * LD];
 #pragma unroll
         for (int s = 0; s < SG; ++s) {
-            const int i = min(i0 + s, n - 1);
-            lp[s] = Lp[i * LD];
-            lm[s] = Lm[i * LD];
+            const int i = i0 + s;
+            const T bn = T(D.b[0][i]);  // zero at the last row
+            const T d = T(D.ab[0][i][0] - x);
+            const T ln = s + 1 < SG ? lm[s + 1 < SG ? s + 1 : 0] : lafter;
+            const T ag = f_abs(fma(-bprev, lprev, fma(-bn, ln, d)));
+            const bool take = i < n && ag < best;
+            r = take ? i : r;
+            best = take ? ag : best;
+            lprev = lp[s];
+            bprev = bn;
         }
-        T best = T(3e38);
-        int r = 0;
-        {
-            const int ia = min(max(i0 - 1, 0), n - 1);
-            T lprev = Lp[ia * LD];  // of the row before
-            T bprev = i0 > 0 ? T(S.u.t.b[0][ia]) : T(0);
-            const T lafter = Lm[min(i0 + SG, n - 1) * LD];
+    }
+    auto least = [&](const T ob, const int orr) {
+        const bool take = ob < best || (ob == best && orr < r);
+        best = take ? ob : best;
+        r = take ? orr : r;
+    };
+    least(xmove<1>(best, lane), xmove<1>(r, lane));
+    least(xmove<2>(best, lane), xmove<2>(r, lane));
+    if constexpr (LPR == 8) least(xmove<4>(best, lane), xmove<4>(r, lane));
+    double z[SG];
+    double n2 = 0.0;
+    // second pass: from the largest entry, where the first twist row was
+    // much smaller (gamma is only known to binary32 rounding)
+    for (int pass = 0; pass < 2; ++pass) {
+        // opaque, or the compiler widens all of them once, ahead of the loop,
+        // into registers that it has not got
 #pragma unroll
-            for (int s = 0; s < SG; ++s) {
-                const int i = i0 + s;
-                const int ic = min(i, n - 1);
-                const T bn = T(S.u.t.b[0][ic]);  // zero at the last row
-                const T d = T(S.u.t.ab[0][ic][0] - x);
-                const T ln = s + 1 < SG ? lm[s + 1 < SG ? s + 1 : 0] : lafter;
-                const T ag = f_abs(fma(-bprev, lprev, fma(-bn, ln, d)));
-                const bool take = i < n && ag < best;
-                r = take ? i : r;
-                best = take ? ag : best;
-                lprev = lp[s];
-                bprev = bn;
-            }
+        for (int s = 0; s < SG; ++s) asm volatile("" : "+v"(lp[s]), "+v"(lm[s]));
+        // products within the lane, from its last row up to the twist and
+        // from its first row down, one where the twist does not lie beyond
+        double up = 1.0, dn = 1.0;
+#pragma unroll
+        for (int s = SG - 1; s >= 0; --s) {
+            const bool above = i0 + s < r;
+            up = above ? -up * double(lp[s]) : 1.0;
+            z[s] = up;
         }
-        auto least = [&](const T ob, const int orr) {
-            const bool take = ob < best || (ob == best && orr < r);
-            best = take ? ob : best;
-            r = take ? orr : r;
+#pragma unroll
+        for (int s = 0; s < SG; ++s) {
+            const int i = i0 + s;
+            dn = i > r ? -dn * double(i < n ? lm[s] : T(0)) : 1.0;
+            z[s] = i > r ? dn : z[s];
+        }
+        // products of the lanes below (up) and above (dn) in the group
+        double cu = 1.0, cd = 1.0;
+#pragma unroll
+        for (int q = 1; q < LPR; ++q) {
+            const double ou = __shfl(up, lane + q), od = __shfl(dn, lane - q);
+            cu *= sub + q < LPR ? ou : 1.0;
+            cd *= sub - q >= 0 ? od : 1.0;
+        }
+        n2 = 0.0;
+        double zb = 0.0;
+        int ri = 0;
+#pragma unroll
+        for (int s = 0; s < SG; ++s) {
+            const int i = i0 + s;
+            z[s] *= i < r ? cu : (i > r ? cd : 1.0);
+            n2 = fma(z[s], z[s], n2);
+            const double az = f_abs(z[s]);
+            ri = az > zb ? i : ri;
+            zb = f_max(zb, az);
+        }
+        n2 = group_sum<LPR>(n2, lane);
+        const bool far = act && zb > 8.0;
+        if (!__ballot(far)) break;
+        auto most = [&](const double ob, const int orr) {
+            const bool take = ob > zb || (ob == zb && orr < ri);
+            zb = take ? ob : zb;
+            ri = take ? orr : ri;
         };
-        least(xmove<1>(best, lane), xmove<1>(r, lane));
-        least(xmove<2>(best, lane), xmove<2>(r, lane));
-        if constexpr (LPR == 8) least(xmove<4>(best, lane), xmove<4>(r, lane));
-        double z[SG];
-        double n2 = 0.0;
-        // second pass: from the largest entry, where the first twist row was
-        // much smaller (gamma is only known to binary32 rounding)
-        for (int pass = 0; pass < 2; ++pass) {
-            // products within the lane, from its last row up to the twist and
-            // from its first row down, one where the twist does not lie beyond
-            double up = 1.0, dn = 1.0;
+        most(xmove<1>(zb, lane), xmove<1>(ri, lane));
+        most(xmove<2>(zb, lane), xmove<2>(ri, lane));
+        if constexpr (LPR == 8) most(xmove<4>(zb, lane), xmove<4>(ri, lane));
+        r = zb > 8.0 ? ri : r;
+    }
+    const double sc = d_rsqrt_nr(n2);
 #pragma unroll
-            for (int s = SG - 1; s >= 0; --s) {
-                const bool above = i0 + s < r;
-                up = above ? -up * double(lp[s]) : 1.0;
-                z[s] = up;
-            }
+    for (int s = 0; s < SG; ++s) out[s] = T(z[s] * sc);
+}
+
+// One wave: Gram-Schmidt along each run of close eigenvalues, in order; at(i, j)
+// is entry i of vector j.
+template <int NMAX, typename At>
+__device__ __forceinline__ void direct_orthogonal(const DirectArrays<NMAX>& D, const int n,
+                                                  const int lane, const At& at)
+{
+    constexpr int R = (NMAX + 63) / 64;  // rows lane + 64 k
+    int first = 0, last = -2;  // of the current run
+#pragma unroll 1
+    for (int w = 0; w < R; ++w) {
+        uint64_t todo = D.close[w];
+        while (todo) {
+            const int j = 64 * w + __builtin_ctzll(todo);
+            todo &= todo - 1;
+            first = j == last + 1 ? first : j;
+            last = j;
+            double v[R];
 #pragma unroll
-            for (int s = 0; s < SG; ++s) {
-                const int i = i0 + s;
-                dn = i > r ? -dn * double(i < n ? lm[s] : T(0)) : 1.0;
-                z[s] = i > r ? dn : z[s];
-            }
-            // products of the lanes below (up) and above (dn) in the group
-            double cu = 1.0, cd = 1.0;
+            for (int k = 0; k < R; ++k)
+                v[k] = lane + 64 * k < n ? double(at(lane + 64 * k, j + 1)) : 0.0;
+            for (int q = first; q <= j; ++q) {
+                double u[R], d = 0.0;
 #pragma unroll
-            for (int q = 1; q < LPR; ++q) {
-                const double ou = __shfl(up, lane + q), od = __shfl(dn, lane - q);
-                cu *= sub + q < LPR ? ou : 1.0;
-                cd *= sub - q >= 0 ? od : 1.0;
-            }
-            n2 = 0.0;
-            double zb = 0.0;
-            int ri = 0;
+                for (int k = 0; k < R; ++k) {
+                    u[k] = lane + 64 * k < n ? double(at(lane + 64 * k, q)) : 0.0;
+                    d = fma(u[k], v[k], d);
+                }
+                d = wave_sum_all(d);
 #pragma unroll
-            for (int s = 0; s < SG; ++s) {
-                const int i = i0 + s;
-                z[s] *= i < r ? cu : (i > r ? cd : 1.0);
-                n2 = fma(z[s], z[s], n2);
-                const double az = f_abs(z[s]);
-                ri = az > zb ? i : ri;
-                zb = f_max(zb, az);
+                for (int k = 0; k < R; ++k) v[k] = fma(-d, u[k], v[k]);
             }
-            n2 = group_sum<LPR>(n2, lane);
-            const bool far = act && zb > 8.0;
-            if (!__ballot(far)) break;
-            auto most = [&](const double ob, const int orr) {
-                const bool take = ob > zb || (ob == zb && orr < ri);
-                zb = take ? ob : zb;
-                ri = take ? orr : ri;
-            };
-            most(xmove<1>(zb, lane), xmove<1>(ri, lane));
-            most(xmove<2>(zb, lane), xmove<2>(ri, lane));
-            if constexpr (LPR == 8) most(xmove<4>(zb, lane), xmove<4>(ri, lane));
-            r = zb > 8.0 ? ri : r;
+            double d = 0.0;
+#pragma unroll
+            for (int k = 0; k < R; ++k) d = fma(v[k], v[k], d);
+            d = d_rsqrt_nr(wave_sum_all(d));
+#pragma unroll
+            for (int k = 0; k < R; ++k)
+                if (lane + 64 * k < n) at(lane + 64 * k, j + 1) = float(v[k] * d);
+            wave_sync();
         }
-        const double sc = d_rsqrt_nr(n2);
+    }
+}
+
+template <int NMAX>
+__device__ __forceinline__ bool direct_close(const DirectArrays<NMAX>& D)
+{
+    uint64_t any = 0;
+#pragma unroll
+    for (int k = 0; k < (NMAX + 63) / 64; ++k) any |= D.close[k];
+    return any != 0;
+}
+
+// The spectrum of T (S.ta, S.tb, set up); eigenvectors into Q0.  Returns whether
+// solved.
+template <typename T, int NMAX, int NT>
+__device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, const int t,
+                                             const bool want_q, T* __restrict__ Lc)
+{
+    constexpr int LPR = NT / NMAX;
+    constexpr int LD = Smem<T, NMAX, NT>::LD;
+    DirectArrays<NMAX>& D = S.u.d.t;
+    if (!direct_eigenvalues<NMAX, NT>(D, S.u.d.g, n, t, want_q, Lc)) return false;
+    if (!want_q) return true;
+    direct_factors<NMAX, NMAX, LPR, LD>(D, S.Q0, S.Q1, n, t, 0);
+    team_sync<NT>();
+    BED_PHASE(6);
+    {
+        constexpr int SG = NMAX / LPR;
+        const int j = t / LPR, i0 = (t % LPR) * SG;
+        const bool act = j < n;
+        const int e = act ? j : 0;
+        float z[SG];
+        direct_vector<NMAX, LPR, LD>(D, S.Q0 + e, S.Q1 + e, D.lam[e], act, n, t, z);
         wave_sync();
         if (act) {
 #pragma unroll
             for (int s = 0; s < SG; ++s)
-                if (i0 + s < n) S.Q0[(i0 + s) * LD + e] = T(z[s] * sc);
+                if (i0 + s < n) S.Q0[(i0 + s) * LD + e] = z[s];
         }
     }
     team_sync<NT>();
-    if (S.u.t.close) {
-        // Gram-Schmidt along each run of close eigenvalues (one row per lane)
-        if (t < 64) {
-            T* row = S.Q0 + (lane < n ? lane : 0) * LD;
-            int first = 0;  // of the current run
-            uint64_t todo = S.u.t.close;
-            int last = -2;
-            while (todo) {
-                const int j = __builtin_ctzll(todo);
-                todo &= todo - 1;
-                first = j == last + 1 ? first : j;
-                last = j;
-                double v = lane < n ? double(row[j + 1]) : 0.0;
-                for (int q = first; q <= j; ++q) {
-                    const double u = lane < n ? double(row[q]) : 0.0;
-                    v = fma(-wave_sum_all(u * v), u, v);
-                }
-                v *= d_rsqrt_nr(wave_sum_all(v * v));
-                if (lane < n) row[j + 1] = T(v);
-                wave_sync();
-            }
-        }
+    if (direct_close(D)) {
+        if (t < 64)
+            direct_orthogonal(D, n, t, [&](const int i, const int j) -> T& { return S.Q0[i * LD + j]; });
         team_sync<NT>();
     }
     BED_PHASE(7);
@@ -1944,7 +2037,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
     constexpr bool DIRECT = std::is_same<T, float>::value && !TRI && LPR >= 4;
     const bool direct = DIRECT && leaf_arg == 0;
     if constexpr (DIRECT) {
-        if (direct && wave == 0) direct_setup(S, n, lane);
+        if (direct && wave == 0) direct_setup<NMAX, NT / NMAX>(S.u.d.t, S.ta, S.tb, n, lane);
     }
     team_sync<NT>();
     if constexpr (AW > 0 && !TRI) {

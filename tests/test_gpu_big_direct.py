@@ -1,0 +1,83 @@
+"""Orders 64 < n <= 128 whose spectrum is solved directly after the reduction,
+beside matrices of the same batch that go through the halves and the top merge
+(eigenvalues closer than 1e-10 of the interval, split and degenerate
+spectra), against the binary64 oracle."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_2604_27325_amd import workloads
+from tests.parity import compare_batch
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+import paper_2604_27325_amd as bed  # noqa: E402
+
+
+def check(A_np, label):
+    A_np = np.ascontiguousarray(A_np, dtype=np.float32)
+    b, n = A_np.shape[0], A_np.shape[1]
+    print(f"[{label}] batch {b} n={n}", flush=True)
+    A = torch.from_numpy(A_np).cuda()
+    lam, Q, info = bed.syevd_packed([n] * b, A.view(-1))
+    vals = bed.syevals(A)
+    torch.cuda.synchronize()
+    lam_o, Q_o, _ = oracle.syevd(A_np.astype(np.float64))
+    for i in range(b):  # LAPACK where the oracle's vectors are not orthonormal
+        if np.linalg.norm(Q_o[i].T @ Q_o[i] - np.eye(n)) > 1e-10:
+            lam_o[i], Q_o[i] = np.linalg.eigh(A_np[i].astype(np.float64))
+    worst, fails = compare_batch(A_np, lam.view(b, n).cpu().numpy(),
+                                 Q.view(b, n, n).cpu().numpy(), lam_o, Q_o, np.float32,
+                                 info=info.cpu().numpy())
+    print(f"  worst {worst}", flush=True)
+    assert not fails, f"{label}: {len(fails)} failing, first {fails[:2]}"
+    nrm = np.abs(lam_o).max(axis=1).clip(1e-300)
+    err = np.abs(vals.cpu().numpy() - lam_o).max(axis=1) / nrm
+    assert err.max() <= 1e-5, f"{label}: eigenvalues only {err.max()}"
+
+
+def rotated(rng, w):
+    V, _ = np.linalg.qr(rng.standard_normal((len(w), len(w))))
+    return (V * w) @ V.T
+
+
+@pytest.mark.parametrize("n", [65, 72, 73, 112, 113, 127, 128])
+def test_spectra_of_one_batch(n):
+    """Separated, paired at several distances (also across the two halves of the
+    columns), graded, split and degenerate spectra in turn."""
+    rng = np.random.default_rng(9400 + n)
+    base = np.linspace(-1.0, 1.0, n)
+    mats = list(workloads.gaussian_sym(rng, 3, n))
+    for d in (1e-3, 1e-5, 1e-7, 0.0):
+        w = base.copy()
+        w[[64, 6]] = w[[63, 5]] + d
+        mats.append(rotated(rng, np.sort(w)))
+    off = np.ones(n - 1)
+    blk = workloads.gaussian_sym(rng, 1, n)[0]
+    blk[:n // 2, n // 2:] = blk[n // 2:, :n // 2] = 0.0
+    u = rng.standard_normal((n, 2))
+    mats += [rotated(rng, 10.0 ** -np.linspace(0, 6, n)), blk, u @ u.T, np.ones((n, n)),
+             np.diag(np.arange(n) - 2.0), np.zeros((n, n)), np.eye(n) * 3.0,
+             2 * np.eye(n) + 0.5 * (np.diag(off, 1) + np.diag(off, -1)),
+             np.diag(np.abs(np.arange(n) - (n - 1) / 2.0)) + np.diag(off, 1) + np.diag(off, -1)]
+    mats += list(workloads.covariance(rng, 3, n))
+    A = np.stack(mats)
+    check(0.5 * (A + A.transpose(0, 2, 1)), f"spectra n={n}")
+
+
+def test_non_finite_matrix_beside_the_others():
+    rng = np.random.default_rng(9500)
+    A = workloads.gaussian_sym(rng, 4, 96).astype(np.float32)
+    A[1, 3, 5] = A[1, 5, 3] = np.nan
+    A[2] = np.eye(96)
+    lam, Q, info = bed.syevd_packed([96] * 4, torch.from_numpy(A).cuda().view(-1))
+    lam, Q = lam.view(4, 96).cpu().numpy(), Q.view(4, 96, 96).cpu().numpy()
+    assert info.cpu().tolist() == [0, -1, 0, 0]
+    assert np.isnan(lam[1]).all() and np.isnan(Q[1]).all()
+    for i in (0, 2, 3):
+        assert np.isfinite(Q[i]).all()
+        r = A[i].astype(np.float64) @ Q[i] - Q[i].astype(np.float64) * lam[i]
+        assert np.linalg.norm(r) <= 96 * 2.0 ** -23 * np.linalg.norm(A[i])
