@@ -5,11 +5,11 @@
 // the configured limits (bed_admit.hpp).  At admission an event is recorded on
 // the caller's stream, so the step that reads a request's A first waits for
 // the work the caller enqueued before submitting (the kernel or copy that
-// produced A).  A scheduler thread packs every admitted, not-yet-launched
-// request into one step on a free stream (up to max_step matrices), uploads
-// the step's pointer work list from pinned host memory into a device buffer
-// owned by that stream slot, launches one kernel per size class and records
-// an event.  Steps on different streams overlap on the
+// produced A).  A scheduler thread packs admitted, not-yet-launched requests into a
+// step on a free stream (up to max_step matrices): a pointer work list in pinned
+// host memory that the step's kernels read in place, one launch per size class and
+// one event.  While several streams are free a step takes the oldest request's data
+// type and size class only.  Steps on different streams overlap on the
 // device; completion is observed by polling the events.  The per-matrix
 // kernel configuration depends only on (n, dtype), so each request's result is
 // bitwise the same alone or in any mix.
@@ -50,8 +50,9 @@ struct Request {
 struct Slot {
     hipStream_t stream = nullptr;
     hipEvent_t done_ev = nullptr;
-    PtrItem *h_items = nullptr;  // pinned staging
-    PtrItem *d_items = nullptr;  // device work list
+    // work list of the step in flight, in pinned memory that its kernels read: 48
+    // bytes a matrix, once, are not worth a copy ahead of each step
+    PtrItem *items = nullptr;
     bool busy = false;
     std::vector<uint64_t> tickets;
 };
@@ -102,36 +103,60 @@ static void server_loop(bed_server *s)
             }
         }
         if (progressed) s->cv_done.notify_all();
-        // launches: every pending request goes into the next step on a free slot
+        // launches: pending requests go into the next step on a free slot
         Slot *free_slot = nullptr;
+        int nfree = 0;
         for (auto &sl : s->slots)
             if (!sl.busy) {
-                free_slot = &sl;
-                break;
+                if (!free_slot) free_slot = &sl;
+                ++nfree;
             }
         if (free_slot && !s->pending.empty()) {
             Slot &sl = *free_slot;
-            int nitems = 0;
-            std::vector<PtrItem> cls_items[2][3];  // [dtype][size class]
-            while (!s->pending.empty()) {
-                const uint64_t tk = s->pending.front();
-                Request &r = s->reqs[tk];
-                if (nitems > 0 && nitems + r.count > s->opts.max_step) break;
-                s->pending.pop_front();
-                const size_t es = dtype_size(r.dt);
-                for (int32_t i = 0; i < r.count; ++i) {
-                    PtrItem it;
-                    it.A = (const char *)r.A + (size_t)i * r.n * r.n * es;
-                    it.lam = (char *)r.lam + (size_t)i * r.n * es;
-                    it.Q = (char *)r.Q + (size_t)i * r.n * r.n * es;
-                    it.info = r.info ? r.info + i : nullptr;
-                    it.n = r.n;
-                    cls_items[r.dt == BED_F64][size_class(r.n)].push_back(it);
+            // One type and size class a step, so that classes run side by side on the
+            // streams (one after the other on one stream they took 100 us for the last
+            // step of a burst, 65 so); everything on the last free stream, where the
+            // rest would wait for a step's end.
+            int count = 0;
+            const bed_dtype dt0 = s->reqs[s->pending.front()].dt;
+            const int cls0 = size_class(s->reqs[s->pending.front()].n);
+            for (auto p = s->pending.begin(); p != s->pending.end();) {
+                Request &r = s->reqs[*p];
+                if (nfree > 1 && (r.dt != dt0 || size_class(r.n) != cls0)) {
+                    ++p;
+                    continue;
                 }
-                nitems += r.count;
+                if (count > 0 && count + r.count > s->opts.max_step) break;
+                count += r.count;
                 r.launched = true;
-                sl.tickets.push_back(tk);
+                sl.tickets.push_back(*p);
+                p = s->pending.erase(p);
             }
+            // the list in pinned memory grouped by (dtype, class)
+            struct Launch {
+                bed_dtype dt;
+                int cls, off, count;
+            };
+            std::vector<Launch> launches;
+            int off = 0;
+            for (const bed_dtype dt : {BED_F32, BED_F64})
+                for (int c = 2; c >= 0; --c) {
+                    const int first = off;
+                    const size_t es = dtype_size(dt);
+                    for (uint64_t tk : sl.tickets) {
+                        const Request &r = s->reqs[tk];
+                        if (r.dt != dt || size_class(r.n) != c) continue;
+                        for (int32_t i = 0; i < r.count; ++i) {
+                            PtrItem &it = sl.items[off++];
+                            it.A = (const char *)r.A + (size_t)i * r.n * r.n * es;
+                            it.lam = (char *)r.lam + (size_t)i * r.n * es;
+                            it.Q = (char *)r.Q + (size_t)i * r.n * r.n * es;
+                            it.info = r.info ? r.info + i : nullptr;
+                            it.n = r.n;
+                        }
+                    }
+                    if (off > first) launches.push_back(Launch{dt, c, first, off - first});
+                }
             // every request's input is complete on its producer stream first:
             // per producer stream, the event of its latest request covers the
             // earlier ones (work on one stream completes in order)
@@ -141,32 +166,22 @@ static void server_loop(bed_server *s)
                 auto &v = latest[s->reqs[tk].producer];
                 v = std::max(v, tk);
             }
-            for (const auto &kv : latest)
-                if (e == hipSuccess) e = hipStreamWaitEvent(sl.stream, s->reqs[kv.second].ready, 0);
-            // stage the list in pinned memory grouped by (dtype, class)
-            int off = 0;
-            struct Launch {
-                bed_dtype dt;
-                int cls, off, count;
-            };
-            std::vector<Launch> launches;
-            for (int d = 0; d < 2; ++d)
-                for (int c = 2; c >= 0; --c) {
-                    auto &v = cls_items[d][c];
-                    if (v.empty()) continue;
-                    std::copy(v.begin(), v.end(), sl.h_items + off);
-                    launches.push_back(Launch{d ? BED_F64 : BED_F32, c, off, (int)v.size()});
-                    off += (int)v.size();
-                }
-            if (e == hipSuccess)
-                e = hipMemcpyAsync(sl.d_items, sl.h_items, sizeof(PtrItem) * off,
-                                   hipMemcpyHostToDevice, sl.stream);
+            std::vector<hipEvent_t> waits;
+            for (const auto &kv : latest) waits.push_back(s->reqs[kv.second].ready);
+            // The calls below take longer than a submission: the lock is free meanwhile,
+            // and what is submitted joins the next step.  Nobody else touches the slot,
+            // and the requests' events are recycled only when this thread has seen the
+            // step's end.
+            lk.unlock();
+            for (hipEvent_t ev : waits)
+                if (e == hipSuccess) e = hipStreamWaitEvent(sl.stream, ev, 0);
             const bed_tune dflt = default_tune();
             for (const Launch &L : launches)
                 if (e == hipSuccess)
-                    e = launch_ptrlist(L.dt, class_shape(L.cls, dflt), sl.d_items + L.off, L.count,
+                    e = launch_ptrlist(L.dt, class_shape(L.cls, dflt), sl.items + L.off, L.count,
                                        sl.stream);
             if (e == hipSuccess) e = hipEventRecord(sl.done_ev, sl.stream);
+            lk.lock();
             if (e != hipSuccess) s->error = hipGetErrorString(e);
             sl.busy = true;
             continue;
@@ -210,8 +225,7 @@ extern "C" bed_status bed_server_create(bed_server **out, const bed_server_opts 
         hipError_t e = hipStreamCreateWithFlags(&sl.stream, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&sl.done_ev, hipEventDisableTiming);
         if (e == hipSuccess)
-            e = hipHostMalloc((void **)&sl.h_items, sizeof(PtrItem) * opts.max_step * 2, 0);
-        if (e == hipSuccess) e = hipMalloc(&sl.d_items, sizeof(PtrItem) * opts.max_step * 2);
+            e = hipHostMalloc((void **)&sl.items, sizeof(PtrItem) * opts.max_step, 0);
         if (e != hipSuccess) {
             bed_server_destroy(s);
             return hip_fail(e, "server resources");
@@ -319,8 +333,7 @@ extern "C" void bed_server_destroy(bed_server *s)
     for (auto &sl : s->slots) {
         if (sl.stream) (void)hipStreamSynchronize(sl.stream);
         if (sl.done_ev) (void)hipEventDestroy(sl.done_ev);
-        if (sl.h_items) (void)hipHostFree(sl.h_items);
-        if (sl.d_items) (void)hipFree(sl.d_items);
+        if (sl.items) (void)hipHostFree(sl.items);
         if (sl.stream) (void)hipStreamDestroy(sl.stream);
     }
     delete s;
