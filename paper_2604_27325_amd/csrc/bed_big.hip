@@ -154,7 +154,7 @@ __device__ __forceinline__ void red_steps(RedSmem &S, const int n, const int lan
                 const float v1 = float(row.p1 == kp + 1 ? 1.0 : R.x1 * h.rx0);
                 if (row.p0 >= pad) V[(int64_t)k * n + row.p0 - pad] = v0;
                 V[(int64_t)k * n + row.p1 - pad] = v1;
-                if (lane == 0) tau[k] = float(h.beta * xt0 * xt0);
+                if (lane == 0) tau[k] = float(h.tau);
             }
             if (lane == 0) {
                 T[BN + k] = h.alpha;

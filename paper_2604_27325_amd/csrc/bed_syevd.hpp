@@ -871,6 +871,7 @@ __device__ __forceinline__ void backmul_rowtile(Smem<T, NMAX, NT>& S, const T* _
 // row per lane, and hands them to its own lanes through its own LDS copies.
 template <typename T> struct HhRefl {
     double alpha, beta, rx0;  // rx0 = 1 / (x_0 - alpha)
+    double tau;               // beta (x_0 - alpha)^2 = 1 + |x_0| / mu
 };
 template <typename T>
 __device__ __forceinline__ HhRefl<T> hh_reflector(const double x0, const double sig)
@@ -878,18 +879,25 @@ __device__ __forceinline__ HhRefl<T> hh_reflector(const double x0, const double 
     // sig = ||x||^2 - x_0^2.  A sub-column below 1e-75 (of a matrix scaled to
     // magnitude one) counts as zero: beta = 0, alpha = x_0; beta^2 stays finite.
     // 1/mu and 1/(|x_0| + mu) are hardware estimates refined by Newton steps:
-    // one for binary32 storage (below 1e-12), two for binary64.
+    // one for binary32 storage (below 1e-12); two for binary64, where mu, beta and
+    // tau are also formed to about their rounding: H is as orthogonal as they are.
     const bool z = sig < 1e-150;
     const double s2 = fma(x0, x0, sig);
     double rmu = d_rsqrt_nr(s2);
     if constexpr (sizeof(T) == 8) rmu = fma(rmu, 0.5 * fma(-s2 * rmu, rmu, 1.0), rmu);
-    const double mu = s2 * rmu;
+    double mu = s2 * rmu;
+    if constexpr (sizeof(T) == 8) mu = fma(0.5 * fma(-mu, mu, s2), rmu, mu);
     const double ax = f_abs(x0);
     double rs = d_rcp_nr(ax + mu);
     if constexpr (sizeof(T) == 8) rs = fma(rs, fma(-(ax + mu), rs, 1.0), rs);
     HhRefl<T> h;
     h.alpha = z ? x0 : -f_copysign(mu, x0);
     h.beta = z ? 0.0 : rmu * rs;
+    h.tau = z ? 0.0 : fma(ax, rmu, 1.0);
+    if constexpr (sizeof(T) == 8) {
+        const double d = mu * (ax + mu);
+        h.beta = z ? 0.0 : fma(h.beta, fma(-d, h.beta, 1.0), h.beta);
+    }
     h.rx0 = z ? 0.0 : f_copysign(rs, x0);
     return h;
 }
@@ -1148,7 +1156,7 @@ __device__ __forceinline__ void hh_solo(Smem<T, NMAX, NT>& S, const int n, const
         BED_HSTEP(k, 3);
         S.Vt[k * VLD + vr] = T(v);
         // (every lane writes the same values)
-        S.tau[k] = T(h.beta * xt0 * xt0);
+        S.tau[k] = T(h.tau);
         S.tb[k] = h.alpha;
         S.ta[k + 1] = fma(-2.0 * xt0, o.w0, a00);
         BED_HSTEP(k, 8);
@@ -1240,7 +1248,7 @@ __device__ __forceinline__ void hh_control(Smem<T, NMAX, NT>& S, const int n, co
             // normalized to v_{k+1} = 1, at index r of the original matrix
             // (padding positions hold zeros at indices >= n)
             S.Vt[k * VLD + vr] = T((R.pos == kp + 1) ? 1.0 : x * h.rx0);
-            S.tau[k] = T(h.beta * xt0 * xt0);
+            S.tau[k] = T(h.tau);
             S.tb[k] = h.alpha;
             team_sync<NT>();
             const double yr = S.u.h.y[par][R.slot], ce = S.u.h.c[par][R.slot];
