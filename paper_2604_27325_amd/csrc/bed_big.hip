@@ -533,7 +533,7 @@ k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ 
         S.u.d.u.t.b[t] = t + 1 < n ? T[BN + t] : 0.0;
     }
     __syncthreads();
-    if (wave == 0) direct_setup<BN, BT / BN>(D, S.u.d.u.t.a, S.u.d.u.t.b, n, lane);
+    if (wave == 0) direct_setup<BN, BT / BN>(D, S.u.d.u.t.a, S.u.d.u.t.b, n, lane, Q != nullptr);
     __syncthreads();
     if (!direct_eigenvalues<BN, BT>(D, S.u.d.u.g, n, t, Q != nullptr, S.lout)) {
         const int n1 = n / 2, n2 = n - n1;

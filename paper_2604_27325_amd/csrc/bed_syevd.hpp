@@ -1409,6 +1409,12 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
 constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 1e-10;
 constexpr int DIRECT_MOST = 4;
 constexpr int DIRECT_CAP = 64;       // rounds per eigenvalue
+// A T with this many couplings below DIRECT_CLOSE has low rank or comes apart and
+// goes to the divide step at once, which deflates it; the direct solver found out
+// after all its rounds (half rank, batch 512: n = 32 60 us so, 44 at once; n = 64
+// 114 and 100).  Eigenvalues alone have no gap to keep: only where most minors vanish
+// (half rank, n = 128: 358 and 288).
+constexpr int DIRECT_SPLIT = 3;
 
 // Wave 0: T scaled by a power of two to |T| in [1/2, 1) (Gershgorin), as rows
 // {a_i, b_{i-1}^2} from the top and, for the bottom half's minors, {a_i, b_i^2}
@@ -1420,7 +1426,8 @@ template <int LPR> __device__ __forceinline__ int direct_order(const int n)
 }
 template <int NMAX, int LPR>
 __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double* ta,
-                                             const double* tb, const int n, const int lane)
+                                             const double* tb, const int n, const int lane,
+                                             const bool want_q)
 {
     constexpr int R = NMAX > 64 ? NMAX / 64 : 1;  // rows per lane
     double a[R], bl[R], br[R];
@@ -1448,6 +1455,10 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
     const int sh = min(max(fexp<float>::BIAS - 1 - ex, -fexp<float>::SMAX), fexp<float>::SMAX);
     const double sc = double(fexp<float>::pow2(sh));
     const int m = direct_order<LPR>(n);
+    int split = 0;  // couplings that are close to none
+#pragma unroll
+    for (int k = 0; k < R; ++k)
+        split += __popcll(__ballot(lane + 64 * k + 1 < n && f_abs(br[k]) * sc < DIRECT_CLOSE));
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int e = lane + 64 * k;
@@ -1467,7 +1478,8 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
         D.lo = -double(nlo) * sc - 1e-6;
         D.hi = double(hi) * sc + 1e-6;
         D.unscale = double(fexp<float>::pow2(-sh));
-        D.ok = (n >= 2 && ex > fexp<float>::BIAS - 64) ? 1 : 0;
+        const bool several = want_q ? split >= DIRECT_SPLIT : (NMAX > 64 && 4 * split >= n);
+        D.ok = (n >= 2 && ex > fexp<float>::BIAS - 64 && !several) ? 1 : 0;
     }
 }
 
@@ -2045,7 +2057,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
     constexpr bool DIRECT = std::is_same<T, float>::value && !TRI && LPR >= 4;
     const bool direct = DIRECT && leaf_arg == 0;
     if constexpr (DIRECT) {
-        if (direct && wave == 0) direct_setup<NMAX, NT / NMAX>(S.u.d.t, S.ta, S.tb, n, lane);
+        if (direct && wave == 0) direct_setup<NMAX, NT / NMAX>(S.u.d.t, S.ta, S.tb, n, lane, Q_out != nullptr);
     }
     team_sync<NT>();
     if constexpr (AW > 0 && !TRI) {
