@@ -83,9 +83,8 @@ k_small(const T *__restrict__ A, int64_t batch, T *__restrict__ lam, T *__restri
         int32_t *__restrict__ info)
 {
     const int64_t b = (int64_t)blockIdx.x * THREADS + threadIdx.x;
-    const bool act = b < batch;
-    const int64_t bi = act ? b : 0;
-    const T *Ab = A + bi * (N * N);
+    if (b >= batch) return;  // (reads no other matrix: with Q == A one may be written by now)
+    const T *Ab = A + b * (N * N);
     const bool wide_in = (reinterpret_cast<uintptr_t>(A) & 15) == 0;
     T in[N * N];
     load<T, N>(Ab, wide_in, in);
@@ -176,7 +175,6 @@ k_small(const T *__restrict__ A, int64_t batch, T *__restrict__ lam, T *__restri
                 v[k][p + 1] = sw ? x0 : x1;
             }
         }
-    if (!act) return;
     const double us = sizeof(T) == 8 ? fexp<double>::pow2(-sh) : 1.0;
 #pragma unroll
     for (int i = 0; i < N; ++i) lam[b * N + i] = bad ? f_nan<T>() : T(us * a[i][i]);

@@ -75,3 +75,19 @@ def test_small_nonfinite(dtype, n):
     keep = np.ones(70, bool)
     keep[[5, 66]] = False
     assert bool(torch.isfinite(Q[torch.from_numpy(keep).cuda()]).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n", [2, 3, 4])
+def test_small_in_place_over_many_workgroups(dtype, n):
+    """Q == A with a partly filled last wave: its idle lanes stay off the matrices
+    that other workgroups overwrite, so every run gives the out-of-place bits."""
+    batch = 64 * 300 + 5
+    A_np = workloads.gaussian_sym(np.random.default_rng(720 + n), batch, n).astype(NP[dtype])
+    A = torch.from_numpy(A_np).cuda().view(-1)
+    lam = torch.empty(batch * n, dtype=dtype, device="cuda")
+    lam0, Q0, _ = bed.syevd_packed([n] * batch, A)
+    for _ in range(20):
+        inplace = A.clone()
+        bed.syevd_packed([n] * batch, inplace, lam=lam, Q=inplace)
+        assert torch.equal(inplace, Q0) and torch.equal(lam, lam0)
