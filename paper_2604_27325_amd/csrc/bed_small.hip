@@ -117,9 +117,10 @@ k_small(const T *__restrict__ A, int64_t batch, T *__restrict__ lam, T *__restri
             a[i][j] = bad ? 0.0 : sc * double(in[i * N + j]);
             f2 = fma(j < i ? 2.0 * a[i][j] : a[i][j], a[i][j], f2);
         }
-    // Sweeps until every off-diagonal entry of the wave's matrices is below
-    // rounding (binary32 storage: 2^-44 of the norm, which the eigenvectors of
-    // eigenvalues 2^-20 apart turn into 2^-24).
+    // Sweeps until every off-diagonal entry is below rounding (binary32 storage:
+    // 2^-44 of the norm, which the eigenvectors of eigenvalues 2^-20 apart turn
+    // into 2^-24).  Each lane stops by itself, so that a matrix's result does not
+    // depend on its neighbours; the wave goes on until its last lane has stopped.
     const double thr2 = f2 * (sizeof(T) == 8 ? 0x1p-108 : 0x1p-88);
     for (int sweep = 0; sweep < SWEEPS; ++sweep) {
         double off = 0.0;
@@ -127,7 +128,7 @@ k_small(const T *__restrict__ A, int64_t batch, T *__restrict__ lam, T *__restri
         for (int p = 0; p < N; ++p)
 #pragma unroll
             for (int q = p + 1; q < N; ++q) off = f_max(off, a[q][p] * a[q][p]);
-        if (!__ballot(off > thr2)) break;
+        if (!(off > thr2)) break;
 #pragma unroll
         for (int p = 0; p < N; ++p)
 #pragma unroll

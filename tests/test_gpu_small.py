@@ -91,3 +91,21 @@ def test_small_in_place_over_many_workgroups(dtype, n):
         inplace = A.clone()
         bed.syevd_packed([n] * batch, inplace, lam=lam, Q=inplace)
         assert torch.equal(inplace, Q0) and torch.equal(lam, lam0)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n", [2, 3, 4])
+def test_small_results_do_not_depend_on_the_batch(dtype, n):
+    """Each matrix of a wave gives the same bits alone, beside others that take
+    fewer or more Jacobi sweeps, and in another place."""
+    rng = np.random.default_rng(730 + n)
+    A_np = workloads.gaussian_sym(rng, 256, n)
+    A_np[::3] = 1e-5 * A_np[::3] + np.diag(np.arange(n) + 1.0)  # one or two sweeps
+    A = torch.from_numpy(A_np).to("cuda", dtype)
+    lam, Q = bed.syevd(A)
+    perm = torch.from_numpy(rng.permutation(256)).cuda()
+    lam_p, Q_p = bed.syevd(A[perm].contiguous())
+    assert torch.equal(lam_p, lam[perm]) and torch.equal(Q_p, Q[perm])
+    for i in range(0, 256, 5):
+        lam_1, Q_1 = bed.syevd(A[i:i + 1])
+        assert torch.equal(lam_1[0], lam[i]) and torch.equal(Q_1[0], Q[i]), i
