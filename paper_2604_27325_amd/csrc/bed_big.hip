@@ -572,7 +572,7 @@ k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ 
         // a serial chain: ahead of the other team's matrix products (25 us behind
         // them, 10 so)
         __builtin_amdgcn_s_setprio(3);
-        direct_factors<BN, HC, BT / BN, LD>(D, L[0], L[1], n, tf, HC * h);
+        direct_factors<BN, BT, HC, BT / BN, LD>(D, L[0], L[1], n, tf, HC * h);
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         // opaque: rows and bounds are formed here, not kept through the factors
@@ -580,7 +580,7 @@ k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ 
         asm volatile("" : "+v"(th), "+s"(nh));
         const bool act = HC * h + th / LPR < nh;
         const int e = act ? th / LPR : 0;
-        direct_vector<BN, LPR, LD>(D, L[0] + e, L[1] + e, D.lam[HC * h + e], act, nh, th, z);
+        direct_vector<BN, LPR, LD>(D, L[0] + e, L[1] + e, HC * h + e, act, nh, th, z);
         __syncthreads();
     }
 #pragma unroll

@@ -153,6 +153,7 @@ struct DirectArrays {
     double lam[NMAX];
     double lo, hi, unscale;
     int cell[NMAX];
+    uint32_t twist[2][NMAX];  // per half of the rows: float bits of gamma (upper 25), row
     uint64_t close[(NMAX + 63) / 64];  // bit j: eigenvalues j and j + 1 are close
     int ok;
 };
@@ -1400,9 +1401,9 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
 // each other, where the divide step is three or four dependent merges of five
 // to seven phases each: batch 512, n = 64: 36 -> 20 us after the reduction, n =
 // 32: 21 -> 11 us.  A vector's error is about 3e-14 / gap (eigenvalue rounding
-// times the vector's length over its twist entry), inside the space of its
-// close neighbours: vectors of eigenvalues closer than DIRECT_CLOSE are made
-// orthogonal in order.  A matrix with a pair closer than DIRECT_GAP, with more
+// times the vector's length over its twist entry; the twist is found in binary64,
+// see direct_factors), inside the space of its close neighbours: vectors of
+// eigenvalues closer than DIRECT_CLOSE are made orthogonal in order.  A matrix with a pair closer than DIRECT_GAP, with more
 // than DIRECT_MOST close pairs, or whose determinants leave the exponent range,
 // goes through the divide step, which does not depend on gaps.
 // Distances are of the Gershgorin interval's scale (|T| in [1/2, 1)).
@@ -1708,45 +1709,91 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
 // for the NC eigenvalues from c0 on, one lane each per eigenvalue: l_i = b / D_i
 // toward the next row, rounded to binary32 (a relative perturbation of the
 // vector's entries).  A zero pivot becomes 1e-25, far below the rounding of T.
-template <int NMAX, int NC, int LPR, int LD>
-__device__ __forceinline__ void direct_factors(const DirectArrays<NMAX>& D, float* Lp, float* Lm,
+//
+// The lanes of an eigenvalue meet in the middle, and each forms on its second
+// half gamma_i = D_i - b l', its own pivot in binary64 and the other one's l' of
+// the row ahead: as two binary32 parts, the low one kept where the lane itself
+// will write that row.  The twist has to come from there: gamma from the rounded
+// factors is known to about 5e-8 of T, and where T comes apart (a vanishing
+// coupling, which no product of factors crosses) such noise chose between the
+// parts' rows for eigenvalues that the parts share to less than that.  The row of
+// smallest |gamma_i| + 2^-46 |D_i| (2^-46: the parts' rounding) goes to D.twist,
+// one entry per lane.  (Batch 512, a solve with gamma of the rounded factors, formed
+// in direct_vector, and so: n = 32 32.4 and 33.0 us, n = 64 72.8 and 74.2, n = 128
+// 314.8 and 313.2.)
+template <int NMAX, int NT, int NC, int LPR, int LD>
+__device__ __forceinline__ void direct_factors(DirectArrays<NMAX>& D, float* Lp, float* Lm,
                                                const int n, const int t, const int c0)
 {
-    if (t >= 2 * NC) return;
     const int j = t % NC, e = c0 + j;
     const bool up = t / NC != 0;
-    if (e >= n) return;
-    const double x = D.lam[e];
+    const bool act = t < 2 * NC && e < n;
+    const double x = D.lam[act ? e : 0];
     const double* ar = &D.ab[up ? 1 : 0][up ? direct_order<LPR>(n) - n : 0][0];
     const double* bk = &D.b[up ? 1 : 0][0];
-    if (up && n < NMAX) Lm[n * LD + j] = 0.f;  // below the last row (its coupling is zero)
-    float* L = up ? Lm + (n - 1) * LD + j : Lp + j;
-    const int dL = up ? -LD : LD;
+    if (act && up && n < NMAX) Lm[n * LD + j] = 0.f;  // below the last row (its coupling is zero)
+    const int dL = up ? -LD : LD, first = up ? (n - 1) * LD + j : j;
+    float* L = (up ? Lm : Lp) + first;  // this lane's factors, at row k
+    float* O = (up ? Lp : Lm) + first;  // the other lane's
+    const int h = up ? n - n / 2 : n / 2;
     double bp = 0.0, l = 0.0;
-#pragma unroll 4
-    for (int k = 0; k < n; ++k) {
-        const double bn = bk[k];
-        double d = fma(-bp, l, ar[2 * k] - x);
+    auto pivot = [&](const int k) { return fma(-bp, l, ar[2 * k] - x); };
+    auto next = [&](double d, const double bn, float* at) {
         d = f_abs(d) < 1e-25 ? 1e-25 : d;
         // b / d: one third-order step from the hardware's estimate
         const double r = __builtin_amdgcn_rcp(d), br = bn * r, er = fma(-d, r, 1.0);
         l = fma(br, fma(er, er, er), br);
-        *L = float(l);
-        L += dL;
         bp = bn;
+        *at = float(l);
+    };
+    if (act) {
+#pragma unroll 4
+        for (int k = 0; k < h; ++k) {
+            next(pivot(k), bk[k], L);
+            *O = float(l - double(*L));
+            L += dL;
+            O += dL;
+        }
+    }
+    if constexpr (2 * NC > 64) team_sync<NT>();  // the two lanes sit in different waves
+    else wave_sync();
+    if (act) {
+        uint32_t best = ~0u;
+        float oh = 0.f, ol = 0.f;  // the other lane's factor of the row ahead
+        auto ahead = [&] {
+            oh = O[dL];
+            ol = L[dL];
+        };
+        auto row = [&](const int k, auto another) {
+            const double bn = bk[k], d = pivot(k);
+            const double lx = double(oh) + double(ol);
+            L += dL;
+            O += dL;
+            if constexpr (decltype(another)::value) ahead();
+            const double g = fma(0x1p-46, f_abs(d), f_abs(fma(-bn, lx, d)));
+            const uint32_t key = (__float_as_uint(float(g)) & ~127u) | (uint32_t)k;
+            best = key < best ? key : best;
+            next(d, bn, L - dL);
+        };
+        if (h < n - 1) ahead();
+        int k = h;
+#pragma unroll 4
+        for (; k < n - 2; ++k) row(k, std::true_type{});
+        for (; k < n; ++k) row(k, std::false_type{});  // (at the last row b = 0)
+        if (up) best = (best & ~127u) | (uint32_t)(n - 1 - (int)(best & 127u));
+        D.twist[up ? 1 : 0][e] = best;
     }
 }
 
-// Entries i0 = SG (t % LPR), i0 + 1, ... of the eigenvector of eigenvalue x (Lp, Lm:
-// its columns of the factors), of norm one.  Twist at the row of smallest
-// |gamma_i| = |e_i^T (T - x)^{-1} e_i|^{-1}, z = 1 there, and products of -l
+// Entries i0 = SG (t % LPR), i0 + 1, ... of the eigenvector of eigenvalue e (Lp, Lm:
+// its columns of the factors), of norm one: z = 1 at the twist row, where
+// |gamma_i| = |e_i^T (T - x)^{-1} e_i|^{-1} is smallest, and products of -l
 // outward; rows of a group's lane are consecutive, its products are finished by
 // a scan over the group.  act: lanes that hold an eigenvalue (the others compute
-// on a valid column).  Rows past n hold anything: none becomes the twist, and the
-// products stop at n.
+// on a valid column).  Rows past n hold anything; the products stop at n.
 template <int NMAX, int LPR, int LD>
 __device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const float* Lp,
-                                              const float* Lm, const double x, const bool act,
+                                              const float* Lm, const int e, const bool act,
                                               const int n, const int t, float (&out)[NMAX / LPR])
 {
     using T = float;
@@ -1759,39 +1806,11 @@ __device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const
         lp[s] = Lp[(i0 + s) * LD];
         lm[s] = Lm[(i0 + s) * LD];
     }
-    T best = T(3e38);
-    int r = 0;
-    {
-        const int ia = max(i0 - 1, 0);
-        T lprev = Lp[ia * LD];  // of the row before
-        T bprev = i0 > 0 ? T(D.b[0][ia]) : T(0);
-        const T lafter = Lm[min(i0 + SG, NMAX - 1) * LD];
-#pragma unroll
-        for (int s = 0; s < SG; ++s) {
-            const int i = i0 + s;
-            const T bn = T(D.b[0][i]);  // zero at the last row
-            const T d = T(D.ab[0][i][0] - x);
-            const T ln = s + 1 < SG ? lm[s + 1 < SG ? s + 1 : 0] : lafter;
-            const T ag = f_abs(fma(-bprev, lprev, fma(-bn, ln, d)));
-            const bool take = i < n && ag < best;
-            r = take ? i : r;
-            best = take ? ag : best;
-            lprev = lp[s];
-            bprev = bn;
-        }
-    }
-    auto least = [&](const T ob, const int orr) {
-        const bool take = ob < best || (ob == best && orr < r);
-        best = take ? ob : best;
-        r = take ? orr : r;
-    };
-    least(xmove<1>(best, lane), xmove<1>(r, lane));
-    least(xmove<2>(best, lane), xmove<2>(r, lane));
-    if constexpr (LPR == 8) least(xmove<4>(best, lane), xmove<4>(r, lane));
+    int r = min(D.twist[0][e], D.twist[1][e]) & 127u;
     double z[SG];
     double n2 = 0.0;
     // second pass: from the largest entry, where the first twist row was
-    // much smaller (gamma is only known to binary32 rounding)
+    // much smaller (an eigenvalue exact to rounding leaves only noise in gamma)
     for (int pass = 0; pass < 2; ++pass) {
         // opaque, or the compiler widens all of them once, ahead of the loop,
         // into registers that it has not got
@@ -1913,7 +1932,7 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
     DirectArrays<NMAX>& D = S.u.d.t;
     if (!direct_eigenvalues<NMAX, NT>(D, S.u.d.g, n, t, want_q, Lc)) return false;
     if (!want_q) return true;
-    direct_factors<NMAX, NMAX, LPR, LD>(D, S.Q0, S.Q1, n, t, 0);
+    direct_factors<NMAX, NT, NMAX, LPR, LD>(D, S.Q0, S.Q1, n, t, 0);
     team_sync<NT>();
     BED_PHASE(6);
     {
@@ -1922,7 +1941,7 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
         const bool act = j < n;
         const int e = act ? j : 0;
         float z[SG];
-        direct_vector<NMAX, LPR, LD>(D, S.Q0 + e, S.Q1 + e, D.lam[e], act, n, t, z);
+        direct_vector<NMAX, LPR, LD>(D, S.Q0 + e, S.Q1 + e, e, act, n, t, z);
         wave_sync();
         if (act) {
 #pragma unroll

@@ -15,7 +15,7 @@ import numpy as np
 
 __all__ = [
     "gaussian_sym", "covariance", "plain_fp64", "paper_scale", "uneven",
-    "differentiation", "serving_trace", "serving_matrices", "pack",
+    "differentiation", "serving_trace", "serving_matrices", "pack", "decoupled_pairs",
 ]
 
 
@@ -114,6 +114,42 @@ def serving_matrices(seed, count, n):
     """Gaussian symmetric FP32 matrices of one serving request."""
     rng = np.random.default_rng(seed)
     return gaussian_sym(rng, count, n).astype(np.float32)
+
+
+def decoupled_pairs(rng, batch, n):
+    """Block-diagonal matrices of two blocks (random sizes) with common
+    eigenvalues, rows and columns permuted in every other one.  In turn: two
+    weighted graph Laplacians (both with eigenvalue zero); two rotated blocks that
+    share one to four eigenvalues; the same with the first block shifted by
+    10^U(-9.5, -7).  Values are meant to be rounded to binary32."""
+    out = []
+    for t in range(batch):
+        n1 = int(rng.integers(2, n - 1))
+        blocks = []
+        w = rng.uniform(-1.0, 1.0, n)
+        k = min(int(rng.integers(1, 5)), n1, n - n1)
+        w[n1:n1 + k] = w[:k]
+        for lo, hi in ((0, n1), (n1, n)):
+            m = hi - lo
+            if t % 3 == 0:
+                W = np.triu(rng.uniform(0.0, 1.0, (m, m)) * (rng.uniform(size=(m, m)) < 0.5), 2)
+                W += np.diag(rng.uniform(0.3, 1.0, m - 1), 1)  # a path: connected
+                W = (W + W.T).astype(np.float32).astype(np.float64)
+                B = np.diag(W.sum(axis=1)) - W
+            else:
+                V, _ = np.linalg.qr(rng.standard_normal((m, m)))
+                B = (V * w[lo:hi]) @ V.T
+                B = 0.5 * (B + B.T)
+                if t % 3 == 2 and lo == 0:
+                    B += np.eye(m) * 10.0 ** rng.uniform(-9.5, -7.0)
+            blocks.append(B)
+        A = np.zeros((n, n))
+        A[:n1, :n1], A[n1:, n1:] = blocks
+        if t % 2:
+            p = rng.permutation(n)
+            A = A[np.ix_(p, p)]
+        out.append(A)
+    return np.stack(out)
 
 
 def pack(mats):

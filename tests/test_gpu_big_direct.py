@@ -81,3 +81,9 @@ def test_non_finite_matrix_beside_the_others():
         assert np.isfinite(Q[i]).all()
         r = A[i].astype(np.float64) @ Q[i] - Q[i].astype(np.float64) * lam[i]
         assert np.linalg.norm(r) <= 96 * 2.0 ** -23 * np.linalg.norm(A[i])
+
+
+@pytest.mark.parametrize("n", [65, 97, 128])
+def test_decoupled_blocks_that_share_eigenvalues(n):
+    """As for n <= 64: two decoupled blocks with common eigenvalues."""
+    check(workloads.decoupled_pairs(np.random.default_rng(9600 + n), 24, n), f"decoupled n={n}")

@@ -95,3 +95,12 @@ def test_close_pairs(n, gap):
         M[p, p] = M[q, q] = 0.25
         M[p, q] = M[q, p] = gap
     check(A, f"pair {gap} n={n}")
+
+
+@pytest.mark.parametrize("n", [8, 16, 20, 32, 47, 64])
+@pytest.mark.parametrize("mid,big", [(256, 256), (128, 512)])
+def test_decoupled_blocks_that_share_eigenvalues(n, mid, big):
+    """Two decoupled blocks with common eigenvalues up to binary32 rounding or a
+    planted distance: each vector's twist has to lie in its own block."""
+    check(workloads.decoupled_pairs(np.random.default_rng(9300 + n), 48, n),
+          f"decoupled n={n}", tune={"threads_mid": mid, "threads_big": big})
