@@ -832,6 +832,7 @@ k_big_merge(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q
         S.u.m.nrho[0] = rho;
         S.u.m.nzz[0] = S.red[3][0] + S.red[3][1];
         S.u.m.nfro[0] = f_sqrt(f_max(fro2, 0.f));
+        S.u.m.nback[0] = 1.f;
     }
     __syncthreads();
 

@@ -136,6 +136,7 @@ struct MergeArrays {
     int tnlo[NMAX / 16], tnhi[NMAX / 16];  // per 16-row tile: span of its nodes
     int nk[NMAX];
     T nrho[NMAX], nzz[NMAX], nfro[NMAX];
+    T nback[NMAX];  // from the node's scale (of dk, nrho, nfro) back to T's
 };
 
 // Direct solver: det and counts on the first grid.
@@ -219,6 +220,12 @@ __device__ __forceinline__ int input_shift(const Smem<T, NMAX, NT>& S)
     const int sh = (emax == 0) ? 0 : fexp<T>::BIAS - 1 - emax;
     return min(max(sh, -fexp<T>::SMAX), fexp<T>::SMAX);
 }
+
+// Couplings of T below 2^-64 of the matrix's scale count as zero in binary32: the
+// reduction of a null block leaves its rounding there, and that one's rounding, 1e-17,
+// 1e-34, ... down to where binary32 has no reciprocals.
+__device__ __forceinline__ float coupling(const float b) { return f_abs(b) < 0x1p-64f ? 0.f : b; }
+__device__ __forceinline__ double coupling(const double b) { return b; }
 
 // Node of a dyadic tearing tree over [0, n): node j at depth d covers
 // [floor(j n / 2^d), floor((j+1) n / 2^d)); nodes of more than `leaf`
@@ -650,7 +657,7 @@ __device__ __forceinline__ void secular_roots(SM& S, const int n, const int d, c
         if (live && sub == 0) {
             S.u.m.rdo[q] = dorg;
             S.u.m.rtau[q] = h;
-            S.u.m.itv[q] = dorg + h;
+            S.u.m.itv[q] = S.u.m.nback[qlo] * (dorg + h);
             if (capped) atomicAdd(&S.capped, 1);
         }
     }
@@ -2060,7 +2067,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
         const T sc = fexp<T>::pow2(input_shift(S));
         for (int e = t; e < 2 * n - 1; e += NT) {
             if (e < n) S.a[e] *= sc;
-            else S.b[e - n] *= sc;
+            else S.b[e - n] = coupling(S.b[e - n] * sc);
         }
         qj = n - 2;
     } else {
@@ -2118,7 +2125,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
     if constexpr (!TRI) {  // T in the storage type
         for (int e = t; e < n; e += NT) {
             S.a[e] = T(S.ta[e]);
-            S.b[e] = T(e + 1 < n ? S.tb[e] : 0.0);
+            S.b[e] = coupling(T(e + 1 < n ? S.tb[e] : 0.0));
         }
     }
     team_sync<NT>();
@@ -2222,7 +2229,13 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
             const T d2 = __shfl(pd2, ihi) - (lo > 0 ? __shfl(pd2, ilo) : T(0));
             const T dmax = act ? f_max(f_abs(S.u.m.sd[lo]), f_abs(S.u.m.sd[hi - 1])) : T(0);
             BED_MARK(d, 11);
-            const T tol = T(8) * u * f_max(dmax, rho * zz0);
+            const T nmax = f_max(dmax, rho * zz0), tol = T(8) * u * nmax;
+            // A node below 2^-20 of the matrix's scale is merged as 2^s times itself
+            // (exact): the squares and reciprocals of its small differences would
+            // leave the range.
+            const int ns = fexp<T>::BIAS - exp_field(nmax);
+            const int nsh = ns > 20 ? min(ns, fexp<T>::SMAX) : 0;
+            const T nsc = fexp<T>::pow2(nsh);
             // Frobenius norm of the node (Eq. (10)), from D + rho z z^T
             const T fro2 = d2 + T(2) * rho * dz + rho * rho * zz0 * zz0;
             bool defl = act && (rho * f_abs(zp) <= tol);  // type 1
@@ -2318,7 +2331,7 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
                 const int row = S.u.m.sperm[e];
                 if (!defl) {
                     const int idx = __popcll(live2 & lane_range(lo, e));
-                    S.u.m.dk[lo + idx] = dp;
+                    S.u.m.dk[lo + idx] = nsc * dp;
                     S.u.m.zk[lo + idx] = zp;
                     S.u.m.ndrow[lo + idx] = row;
                 } else {
@@ -2332,9 +2345,10 @@ __device__ __forceinline__ void syevd_team(const T* __restrict__ Ain, const int 
             const T zz = __shfl(pzz, ihi) - (lo > 0 ? __shfl(pzz, ilo) : T(0));
             if (act && e == lo) {
                 S.u.m.nk[lo] = k;
-                S.u.m.nrho[lo] = rho;
+                S.u.m.nrho[lo] = nsc * rho;
                 S.u.m.nzz[lo] = zz;
-                S.u.m.nfro[lo] = f_sqrt(f_max(fro2, T(0)));
+                S.u.m.nfro[lo] = nsc * f_sqrt(f_max(fro2, T(0)));
+                S.u.m.nback[lo] = fexp<T>::pow2(-nsh);
                 S.u.m.nrot[lo] = my_nrot;
             }
             const bool anyrot = __ballot(hasrot) != 0;

@@ -175,3 +175,51 @@ def test_scaled_and_block_structured_matrices(dt):
     mats.append(W)
     for i, M in enumerate(mats):
         check(M[None].astype(dt), f"scaled/block {i} n={M.shape[0]} {dt.__name__}")
+
+
+def _null_blocks(rng, batch, n):
+    """Graph Laplacians (weighted or not) and 0/1/-1 matrices so sparse that many
+    rows are empty, zero but for a few rows and columns, and diagonal blocks with
+    scales 1, 1e-10, 1e-20 and 1e-30."""
+    out = []
+    for t in range(batch):
+        W = np.triu(rng.uniform(size=(n, n)) < rng.uniform(0.5, 3.0) / n, 1).astype(np.float64)
+        if t % 4 == 0:
+            W *= rng.uniform(0.0, 1.0, (n, n)).astype(np.float32)
+        if t % 4 < 2:
+            A = np.diag((W + W.T).sum(axis=1)) - W - W.T
+        elif t % 4 == 2:
+            W *= rng.integers(-1, 2, (n, n))
+            A = W + W.T + np.diag(rng.integers(-1, 2, n) * (rng.uniform(size=n) < 0.3))
+        else:
+            s = np.repeat(10.0 ** (-10.0 * np.arange(4)), (n + 3) // 4)[:n]
+            A = np.where(s[:, None] == s[None, :], workloads.gaussian_sym(rng, 1, n)[0] * s, 0.0)
+        out.append(A)
+    return np.stack(out)
+
+
+@pytest.mark.parametrize("dt", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [5, 11, 16, 17, 22, 32, 40, 64, 65, 96, 128])
+def test_null_blocks(dt, n):
+    """Matrices with empty rows: the reduction leaves rounding's rounding in the
+    null block, whose merges are as far below the matrix's scale."""
+    if dt == np.float64 and n > 64:
+        pytest.skip("binary32 only above 64")
+    A = _null_blocks(np.random.default_rng(7700 + n), 64, n).astype(dt)
+    At = torch.from_numpy(A).cuda()
+    lam, Q, info = bed.syevd(At, return_info=True)
+    vals = bed.syevals(At).cpu().numpy()
+    lam, Q = lam.cpu().numpy(), Q.double().cpu().numpy()
+    A = A.astype(np.float64)
+    ref = np.linalg.eigvalsh(A)
+    nrm = np.abs(ref).max(axis=1).clip(1e-30)
+    tol_lam, tol = (1e-5, 1e-5) if dt == np.float32 else (1e-12, 1e-13)
+    assert not info.cpu().numpy().any()
+    for got in (lam, vals):
+        assert np.isfinite(got).all() and (np.diff(got, axis=1) >= 0).all()
+        assert (np.abs(got - ref).max(axis=1) <= tol_lam * nrm).all()
+    assert np.isfinite(Q).all()
+    res = np.linalg.norm(A @ Q - Q * lam[:, None, :], axis=(1, 2)) / \
+        np.linalg.norm(A, axis=(1, 2)).clip(1e-30)
+    orth = np.linalg.norm(np.swapaxes(Q, 1, 2) @ Q - np.eye(n), axis=(1, 2))
+    assert res.max() <= tol and orth.max() <= tol, (res.max(), orth.max())
