@@ -70,10 +70,12 @@ typedef enum {
 
 /* Launch schedule of a plan.  Zero fields mean "autotuned / default".
  *   threads_big   threads per matrix for the n > 32 size class (64, 128,
- *                 256 or 512; default 256: two waves hold the matrix during
- *                 the Householder reduction, one forms the reflectors, one
- *                 the Householder product; 64 and 128 reduce on one wave and
- *                 apply the product in compact-WY form)
+ *                 256 or 512; default 256 in binary32, 512 in binary64.
+ *                 During the Householder reduction 256 have two waves hold
+ *                 the matrix, one form the reflectors and one (binary32) the
+ *                 Householder product, 512 four, one and two or more; the
+ *                 others reduce on one wave.  Where no wave forms the product
+ *                 it is applied in compact-WY form)
  *   threads_mid   threads per matrix for 16 < n <= 32 (64, 128 or 256; default
  *                 256: one wave holds the matrix, one forms the reflectors,
  *                 two the Householder product, all four merge)

@@ -110,10 +110,14 @@ TeamShape class_shape(int cls, const bed_tune &t)
     }
 }
 
-bed_tune default_tune()
+// threads_big: with 256 threads a binary32 team leaves room for a second one on the
+// CU (64 x 64 x 512: 75 us, 77 with 512).  A binary64 team fills the CU's LDS
+// whatever its size, and 512 threads hold Q_H beside the reduction and eight lanes a
+// root in the merges (64 x 64, batch 64 and 512: 91 and 183 us, 100 and 200 with 256).
+bed_tune default_tune(bed_dtype dt)
 {
     bed_tune t;
-    t.threads_big = 256;
+    t.threads_big = dt == BED_F64 ? 512 : 256;
     t.threads_mid = 256;
     t.waves_per_cu = 0;
     t.order = 0;
@@ -214,7 +218,7 @@ extern "C" bed_status bed_plan_create(bed_plan **plan, bed_dtype dt, int64_t bat
     if (stream_capturing((hipStream_t)stream))
         return fail(BED_ERR_CAPTURE, "bed_plan_create while its stream is being captured");
     bed_tune t = tune ? *tune : tuned_or_default(dt, batch, n);
-    const bed_tune dflt = default_tune();
+    const bed_tune dflt = default_tune(dt);
     if (t.threads_big == 0) t.threads_big = dflt.threads_big;
     if (t.threads_mid == 0) t.threads_mid = dflt.threads_mid;
     if (t.leaf != 0 && !leaf_supported(t.leaf))
@@ -398,7 +402,7 @@ extern "C" bed_status bedi_solve_uniform(bed_dtype dt, int64_t batch, int32_t n,
     hipStream_t s = (hipStream_t)stream;
     if (n > 64 && dt != BED_F32)
         return fail(BED_ERR_UNSUPPORTED, "n = %d > 64 is supported in binary32 only", n);
-    const bed_tune t = n > 64 ? default_tune() : tuned_or_default_uniform(dt, batch, n);
+    const bed_tune t = n > 64 ? default_tune(dt) : tuned_or_default_uniform(dt, batch, n);
     if (t.persistent) {  // a stored persistent schedule: through the plan cache
         const std::vector<int32_t> sizes(batch, n);
         return solve(dt, batch, sizes.data(), A, lambda, Q, info, stream, want_q != 0);

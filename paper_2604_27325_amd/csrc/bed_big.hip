@@ -1007,7 +1007,7 @@ bed_status big_solve(bed_dtype dt, int64_t batch, int n, const void *A, void *la
                        (float *)lam, (float *)Q, info, ws);
     e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e, "k_big_direct launch");
-    const bed_tune dflt = default_tune();
+    const bed_tune dflt = default_tune(dt);
     // the halves of what is left: eigenvectors, or (eigenvalues only) just the end rows z needs
     float *q1 = Q ? ws.q1 : nullptr, *q2 = Q ? ws.q2 : nullptr;
     if (n1 == n2) {

@@ -24,7 +24,7 @@ bool stream_capturing(hipStream_t s);
 int device_cu_count();
 int size_class(int n);
 TeamShape class_shape(int cls, const bed_tune &t);
-bed_tune default_tune();
+bed_tune default_tune(bed_dtype dt);
 
 // Autotuner cache lookup: the stored schedule for this (arch, dtype, size mix)
 // or the default one.  Never launches work.

@@ -141,7 +141,7 @@ extern "C" bed_status bed_syevd_noalloc(bed_dtype dt, int64_t batch, const int32
     if ((st = check_ptr(lambda, dt, "lambda", false)) != BED_OK) return st;
     if ((st = check_ptr(Q, dt, "Q", false)) != BED_OK) return st;
     hipStream_t s = (hipStream_t)stream;
-    const bed_tune dflt = default_tune();
+    const bed_tune dflt = default_tune(dt);
     bool uniform = true;
     int cnt[3] = {0, 0, 0};
     for (int64_t b = 0; b < batch; ++b) {

@@ -175,10 +175,9 @@ static void server_loop(bed_server *s)
             lk.unlock();
             for (hipEvent_t ev : waits)
                 if (e == hipSuccess) e = hipStreamWaitEvent(sl.stream, ev, 0);
-            const bed_tune dflt = default_tune();
             for (const Launch &L : launches)
                 if (e == hipSuccess)
-                    e = launch_ptrlist(L.dt, class_shape(L.cls, dflt), sl.items + L.off, L.count,
+                    e = launch_ptrlist(L.dt, class_shape(L.cls, default_tune(L.dt)), sl.items + L.off, L.count,
                                        sl.stream);
             if (e == hipSuccess) e = hipEventRecord(sl.done_ev, sl.stream);
             lk.lock();

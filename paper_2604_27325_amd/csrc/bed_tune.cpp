@@ -70,7 +70,7 @@ void load_file_locked()
     char line[512];
     while (fgets(line, sizeof line, f)) {
         char key[256];
-        bed_tune t = default_tune();
+        bed_tune t = default_tune(BED_F32);  // (a line names all but the cutoff)
         const int got = sscanf(line, " \"%255[^\"]\" : [ %d , %d , %d , %d , %d , %d ]", key,
                                &t.threads_big, &t.threads_mid, &t.waves_per_cu, &t.order,
                                &t.persistent, &t.leaf);
@@ -108,7 +108,7 @@ bed_tune tuned_or_default(bed_dtype dt, int64_t batch, const int32_t *n)
         auto it = g_tuned.find(tune_key(dt, batch, n));
         if (it != g_tuned.end()) return it->second;
     }
-    return default_tune();
+    return default_tune(dt);
 }
 
 bed_tune tuned_or_default_uniform(bed_dtype dt, int64_t batch, int32_t n)
@@ -121,7 +121,7 @@ bed_tune tuned_or_default_uniform(bed_dtype dt, int64_t batch, int32_t n)
         auto it = g_tuned.find(tune_key(dt, batch, hist));
         if (it != g_tuned.end()) return it->second;
     }
-    return default_tune();
+    return default_tune(dt);
 }
 }  // namespace bed
 
@@ -150,7 +150,7 @@ extern "C" bed_status bed_autotune(bed_dtype dt, int64_t batch, const int32_t *n
     if (hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess)
         return fail(BED_ERR_HIP, "hipEventCreate failed");
     float best_ms = 1e30f;
-    bed_tune best = default_tune();
+    bed_tune best = default_tune(dt);
     auto trial = [&](const bed_tune &t) {
         bed_plan *p = nullptr;
         if (bed_plan_create(&p, dt, batch, n, &t, stream) != BED_OK) return;
@@ -198,7 +198,7 @@ extern "C" bed_status bed_tune_set(bed_dtype dt, int64_t batch, const int32_t *n
     if (st != BED_OK) return st;
     if (!tune) return fail(BED_ERR_INVALID_ARG, "tune is NULL");
     bed_tune t = *tune;
-    const bed_tune dflt = default_tune();
+    const bed_tune dflt = default_tune(dt);
     if (t.threads_big == 0) t.threads_big = dflt.threads_big;
     if (t.threads_mid == 0) t.threads_mid = dflt.threads_mid;
     if (t.leaf != 0 && !leaf_supported(t.leaf))

@@ -116,3 +116,17 @@ def test_tune_rejects_unsupported_leaf_size(lib):
         t = Tune(threads_big=512, threads_mid=128, leaf=leaf)
         assert lib.bed_tune_set(0, 2, n, ctypes.byref(t)) == 1  # BED_ERR_INVALID_ARG
         assert b"leaf" in lib.bed_last_error()
+
+
+def test_default_team_sizes_by_type(lib):
+    """A plan without a schedule takes the type's default (a uniform plan makes
+    no allocation, so this needs no GPU)."""
+    from paper_2604_27325_amd import Tune
+    i32 = ctypes.c_int32
+    n = (i32 * 2)(40, 40)
+    for dtype, threads in ((0, 256), (1, 512)):
+        plan, t = ctypes.c_void_p(), Tune()
+        assert lib.bed_plan_create(ctypes.byref(plan), dtype, ctypes.c_int64(2), n, None, None) == 0
+        assert lib.bed_plan_get_tune(plan, ctypes.byref(t)) == 0
+        lib.bed_plan_destroy(plan)
+        assert (t.threads_big, t.threads_mid, t.leaf) == (threads, 256, 0)
