@@ -1410,19 +1410,29 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
 // 32: 21 -> 11 us.  A vector's error is about 3e-14 / gap (eigenvalue rounding
 // times the vector's length over its twist entry; the twist is found in binary64,
 // see direct_factors), inside the space of its close neighbours: vectors of
-// eigenvalues closer than DIRECT_CLOSE are made orthogonal in order.  A matrix with a pair closer than DIRECT_GAP, with more
-// than DIRECT_MOST close pairs, or whose determinants leave the exponent range,
-// goes through the divide step, which does not depend on gaps.
+// eigenvalues closer than DIRECT_CLOSE are made orthogonal in order.  A matrix with a
+// pair closer than DIRECT_GAP, with more than DIRECT_MOST close pairs, or whose
+// determinants leave the exponent range, goes through the divide step, which does not
+// depend on gaps.  (DIRECT_GAP: at 4e-12 the two vectors of a pair are still a few
+// hundredths from orthogonal at most before they are made so; an eigenvalue repeated
+// exactly in a dense binary32 matrix is 1e-9 apart in most and 1e-10 in some.)
 // Distances are of the Gershgorin interval's scale (|T| in [1/2, 1)).
-constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 1e-10;
+constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 4e-12;
 constexpr int DIRECT_MOST = 4;
 constexpr int DIRECT_CAP = 64;       // rounds per eigenvalue
-// A T with this many couplings below DIRECT_CLOSE has low rank or comes apart and
-// goes to the divide step at once, which deflates it; the direct solver found out
-// after all its rounds (half rank, batch 512: n = 32 60 us so, 44 at once; n = 64
-// 114 and 100).  Eigenvalues alone have no gap to keep: only where most minors vanish
-// (half rank, n = 128: 358 and 288).
+constexpr int DIRECT_LOOK = 6;       // rounds that separated spectra do with
+// With vectors, a matrix that will be refused is to be known early: the divide step
+// alone takes as long as it took without a direct solver, so the rounds ahead of it
+// were lost.  Three looks (us a solve at n = 32 and 64, batch 512, without and with it):
+//   at the couplings: DIRECT_SPLIT of them below DIRECT_CLOSE, T has low rank (half
+//   rank: 60 -> 45, 114 -> 99); one below DIRECT_APART, T comes apart, and its parts
+//   most often share eigenvalues (graph components, Kronecker products; one common
+//   eigenvalue: 61 -> 45, 126 -> 96; none: 37 -> 41, 78 -> 88);
+//   at the grid (fourfold eigenvalues: 63 -> 48, 132 -> 104; the divide step alone: 46
+//   and 100);
+//   after DIRECT_LOOK rounds at the brackets.
 constexpr int DIRECT_SPLIT = 3;
+constexpr double DIRECT_APART = 1e-13;
 
 // Wave 0: T scaled by a power of two to |T| in [1/2, 1) (Gershgorin), as rows
 // {a_i, b_{i-1}^2} from the top and, for the bottom half's minors, {a_i, b_i^2}
@@ -1463,10 +1473,18 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
     const int sh = min(max(fexp<float>::BIAS - 1 - ex, -fexp<float>::SMAX), fexp<float>::SMAX);
     const double sc = double(fexp<float>::pow2(sh));
     const int m = direct_order<LPR>(n);
-    int split = 0;  // couplings that are close to none
+    int split = 0;
+    bool apart = false;
 #pragma unroll
-    for (int k = 0; k < R; ++k)
-        split += __popcll(__ballot(lane + 64 * k + 1 < n && f_abs(br[k]) * sc < DIRECT_CLOSE));
+    for (int k = 0; k < R; ++k) {
+        const bool in = lane + 64 * k + 1 < n;
+        split += __popcll(__ballot(in && f_abs(br[k]) * sc < DIRECT_CLOSE));
+        apart = apart || (in && f_abs(br[k]) * sc < DIRECT_APART);
+    }
+    // Eigenvalues alone have no gap to keep: only where most minors vanish (half rank,
+    // n = 128: 358 and 288 us).
+    const bool several = want_q ? split >= DIRECT_SPLIT || __ballot(apart)
+                                : (NMAX > 64 && 4 * split >= n);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int e = lane + 64 * k;
@@ -1486,7 +1504,6 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
         D.lo = -double(nlo) * sc - 1e-6;
         D.hi = double(hi) * sc + 1e-6;
         D.unscale = double(fexp<float>::pow2(-sh));
-        const bool several = want_q ? split >= DIRECT_SPLIT : (NMAX > 64 && 4 * split >= n);
         D.ok = (n >= 2 && ex > fexp<float>::BIAS - 64 && !several) ? 1 : 0;
     }
 }
@@ -1626,6 +1643,17 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
                 F[q] = G.f[k0 + q];
             }
         }
+        // A wave none of whose (at least eight) eigenvalues is alone in its cell (a
+        // quarter of the mean spacing wide) and none in a crowd: multiple eigenvalues.
+        // (Graded spectra have the crowd at one end and lone ones at the other.)
+        if (want_q) {
+            if (__popcll(__ballot(act)) >= 8 * LPR &&
+                !__ballot(act && (chi - clo == 1 || 4 * (chi - clo) > n)))
+                bad = true;
+            if (__ballot(bad)) D.ok = 0;
+            team_sync<NT>();
+            if (!D.ok) return false;
+        }
         const int pt = sub & 3;
         const double spread = pt == 0 ? -8.0 : (pt == 1 ? -1.0 : (pt == 2 ? 1.0 : 8.0));
         const double even = double(pt + 1) * 0.2, fl = double(pt + 1) * 0x1p-9, fh = double(4 - pt) * -0x1p-9;
@@ -1657,9 +1685,12 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
             const bool stop = !(w > 0x1p-51) || (strict && err <= 0x1p-44);
             lam = done ? lam : est;
             done = done || stop;
-            if (rounds >= DIRECT_CAP) {
-                bad = bad || !done;
-                done = true;
+            if (rounds >= (want_q ? DIRECT_LOOK : DIRECT_CAP)) {
+                // what the checks below would refuse: no use in finding it exactly
+                const bool pair = want_q && act && j + 1 < chi;  // the next one is in here too
+                bad = bad || (pair && w < DIRECT_GAP) || (rounds >= DIRECT_CAP && !done);
+                if (__ballot(bad) || __popcll(__ballot(pair && w < DIRECT_CLOSE)) > LPR * DIRECT_MOST)
+                    bad = done = true;
             }
             if (!__ballot(!done)) break;  // Eq. (22): converged lanes idle till here
             // points in ascending order over the lanes

@@ -116,12 +116,13 @@ def serving_matrices(seed, count, n):
     return gaussian_sym(rng, count, n).astype(np.float32)
 
 
-def decoupled_pairs(rng, batch, n):
+def decoupled_pairs(rng, batch, n, link=None):
     """Block-diagonal matrices of two blocks (random sizes) with common
     eigenvalues, rows and columns permuted in every other one.  In turn: two
     weighted graph Laplacians (both with eigenvalue zero); two rotated blocks that
     share one to four eigenvalues; the same with the first block shifted by
-    10^U(-9.5, -7).  Values are meant to be rounded to binary32."""
+    10^U(-9.5, -7).  With link = (lo, hi) one entry of size 10^U(lo, hi) couples the
+    blocks.  Values are meant to be rounded to binary32."""
     out = []
     for t in range(batch):
         n1 = int(rng.integers(2, n - 1))
@@ -145,6 +146,8 @@ def decoupled_pairs(rng, batch, n):
             blocks.append(B)
         A = np.zeros((n, n))
         A[:n1, :n1], A[n1:, n1:] = blocks
+        if link:
+            A[n1, n1 - 1] = A[n1 - 1, n1] = 10.0 ** rng.uniform(*link)
         if t % 2:
             p = rng.permutation(n)
             A = A[np.ix_(p, p)]

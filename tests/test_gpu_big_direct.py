@@ -87,3 +87,10 @@ def test_non_finite_matrix_beside_the_others():
 def test_decoupled_blocks_that_share_eigenvalues(n):
     """As for n <= 64: two decoupled blocks with common eigenvalues."""
     check(workloads.decoupled_pairs(np.random.default_rng(9600 + n), 24, n), f"decoupled n={n}")
+
+
+@pytest.mark.parametrize("link", [(-13, -9), (-9, -5)])
+@pytest.mark.parametrize("n", [65, 128])
+def test_weakly_coupled_blocks_that_share_eigenvalues(n, link):
+    check(workloads.decoupled_pairs(np.random.default_rng(9610 + n), 24, n, link),
+          f"linked {link} n={n}")

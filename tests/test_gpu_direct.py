@@ -104,3 +104,41 @@ def test_decoupled_blocks_that_share_eigenvalues(n, mid, big):
     planted distance: each vector's twist has to lie in its own block."""
     check(workloads.decoupled_pairs(np.random.default_rng(9300 + n), 48, n),
           f"decoupled n={n}", tune={"threads_mid": mid, "threads_big": big})
+
+
+def _multiple(rng, n):
+    """Twofold and fourfold eigenvalues throughout, one eigenvalue repeated twice and
+    six times, cells of the first grid with two apart eigenvalues each, and a pair
+    in a decoupled 2 x 2 block, exact and 1e-11 apart."""
+    def rotated(w):
+        V, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        return (V * np.sort(w)) @ V.T
+
+    lin = np.linspace(-1.0, 1.0, n)
+    two, six = lin.copy(), lin.copy()
+    two[n // 2] = two[n // 2 - 1]
+    six[n // 3:n // 3 + 6] = six[n // 3]
+    mats = [rotated(np.repeat(lin, 2)[:n]), rotated(np.repeat(lin, 4)[:n]), rotated(two), rotated(six),
+            rotated(np.repeat(np.linspace(-1.0, 1.0, (n + 1) // 2), 2)[:n] + 1e-3 * (np.arange(n) % 2))]
+    for d in (0.0, 1e-11):
+        A = rotated(lin)
+        A[[0, n - 1], :] = 0.0
+        A[:, [0, n - 1]] = 0.0
+        A[0, 0] = A[n - 1, n - 1] = 0.25
+        A[0, n - 1] = A[n - 1, 0] = d
+        mats.append(A)
+    return np.stack(mats)
+
+
+@pytest.mark.parametrize("n", [8, 15, 16, 24, 31, 32, 33, 39, 40, 48, 64])
+@pytest.mark.parametrize("mid,big", [(256, 256), (128, 512)])
+def test_multiple_eigenvalues(n, mid, big):
+    check(_multiple(np.random.default_rng(9310 + n), n), f"multiple n={n}",
+          tune={"threads_mid": mid, "threads_big": big})
+
+
+@pytest.mark.parametrize("link", [(-13, -9), (-9, -5)])
+@pytest.mark.parametrize("n", [8, 16, 32, 47, 64])
+def test_weakly_coupled_blocks_that_share_eigenvalues(n, link):
+    check(workloads.decoupled_pairs(np.random.default_rng(9320 + n), 48, n, link),
+          f"linked {link} n={n}")
