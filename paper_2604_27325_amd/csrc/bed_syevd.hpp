@@ -1437,7 +1437,8 @@ constexpr double DIRECT_APART = 1e-13;
 // Wave 0: T scaled by a power of two to |T| in [1/2, 1) (Gershgorin), as rows
 // {a_i, b_{i-1}^2} from the top and, for the bottom half's minors, {a_i, b_i^2}
 // from the bottom of the padded order m; padding rows are {4, 0}, whose factors
-// 4 - x keep signs.
+// 4 - x keep signs.  Couplings count as 2^-52 at least for the minors: with a zero
+// one every minor below would be zero where x meets an eigenvalue above.
 template <int LPR> __device__ __forceinline__ int direct_order(const int n)
 {
     return LPR == 8 ? (n + 15) & ~15 : (n + 7) & ~7;
@@ -1473,18 +1474,31 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
     const int sh = min(max(fexp<float>::BIAS - 1 - ex, -fexp<float>::SMAX), fexp<float>::SMAX);
     const double sc = double(fexp<float>::pow2(sh));
     const int m = direct_order<LPR>(n);
-    int split = 0;
-    bool apart = false;
+    bool several;
+    if (want_q) {
+        int split = 0;
+        bool apart = false;
 #pragma unroll
-    for (int k = 0; k < R; ++k) {
-        const bool in = lane + 64 * k + 1 < n;
-        split += __popcll(__ballot(in && f_abs(br[k]) * sc < DIRECT_CLOSE));
-        apart = apart || (in && f_abs(br[k]) * sc < DIRECT_APART);
+        for (int k = 0; k < R; ++k) {
+            const bool in = lane + 64 * k + 1 < n;
+            split += __popcll(__ballot(in && f_abs(br[k]) * sc < DIRECT_CLOSE));
+            apart = apart || (in && f_abs(br[k]) * sc < DIRECT_APART);
+        }
+        several = split >= DIRECT_SPLIT || __ballot(apart);
+    } else {
+        // Eigenvalues alone have no gap to keep, but a determinant that must not vanish:
+        // near an eigenvalue of its null block each row without a coupling costs it up to
+        // 51 bits (the last rounds' distance), a halves' determinant those of its lower
+        // half.  More than start and end of the range hold: to the divide step at once
+        // (half rank, n = 128: 284 us, 358 after all rounds).
+        int lost = 0;
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int e = lane + 64 * k, bits = min(1022 - exp_field(bl[k] * sc), 51);
+            lost += (e > 0 && e < n && (LPR == 4 || e >= m / 2) && bits >= 20) ? bits : 0;
+        }
+        several = group_sum<64>(lost, lane) > (LPR == 4 ? 1580 : 840);
     }
-    // Eigenvalues alone have no gap to keep: only where most minors vanish (half rank,
-    // n = 128: 358 and 288 us).
-    const bool several = want_q ? split >= DIRECT_SPLIT || __ballot(apart)
-                                : (NMAX > 64 && 4 * split >= n);
 #pragma unroll
     for (int k = 0; k < R; ++k) {
         const int e = lane + 64 * k;
@@ -1492,9 +1506,9 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
         if (e < m) {
             const double as = in ? a[k] * sc : 4.0, bs = bl[k] * sc, bt = br[k] * sc;
             D.ab[0][e][0] = as;
-            D.ab[0][e][1] = bs * bs;
+            D.ab[0][e][1] = in && e > 0 ? fmax(bs * bs, 0x1p-104) : 0.0;
             D.ab[1][m - 1 - e][0] = as;
-            D.ab[1][m - 1 - e][1] = bt * bt;
+            D.ab[1][m - 1 - e][1] = e + 1 < n ? fmax(bt * bt, 0x1p-104) : 0.0;
             D.b[0][e] = bt;
             D.b[1][in ? n - 1 - e : e] = in ? bs : 0.0;  // coupling of row e to the row above
             D.cell[e] = -2;
@@ -1510,13 +1524,17 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
 
 // Minors of T - x I over `blocks` blocks of eight rows of a table {a, b^2}, p_i =
 // (a_i - x) p_{i-1} - b^2 p_{i-2}: the last two (p1, p0) and the number of sign
-// changes.  |a_i - x| <= 2, so n <= 128 minors stay within 2^192.
+// changes.  |a_i - x| <= 2, so n <= 128 minors stay within 2^192; they start at 2^800
+// (halves, whose products are formed: 2^400), which leaves the small ones that much
+// more room.  (Eigenvalues alone, us, without and with these two: half rank n = 64
+// 122 -> 73, six-fold n = 30 63 -> 40, which is what the divide step takes.)
+template <int LPR>
 __device__ __forceinline__ int direct_minors(const double* rows, const int blocks, const double x,
                                              double& p1, double& p0)
 {
     typedef double d2 __attribute__((ext_vector_type(2)));
     p0 = 0.0;
-    p1 = 1.0;
+    p1 = LPR == 8 ? 0x1p400 : 0x1p800;
     uint32_t m = 0;  // signs of the minors, the latest in bit 0
     int c = 0;
     const d2* row = reinterpret_cast<const d2*>(rows);
@@ -1556,12 +1574,12 @@ __device__ __forceinline__ double direct_det(const double (*ab)[NMAX][2], const 
     };
     double p1, p0;
     if constexpr (LPR == 4) {
-        count = direct_minors(&ab[0][0][0], m >> 3, x, p1, p0);
+        count = direct_minors<LPR>(&ab[0][0][0], m >> 3, x, p1, p0);
         tiny = vanished(p1, p0);
         return p1;
     } else {
         const bool low = sub >= 4;
-        int c = direct_minors(&ab[low ? 1 : 0][0][0], m >> 4, x, p1, p0);
+        int c = direct_minors<LPR>(&ab[low ? 1 : 0][0][0], m >> 4, x, p1, p0);
         const double bh = ab[0][m >> 1][1];
         const double q1 = lxor<4>(p1), q0 = lxor<4>(p0);
         const int oc = lxor<4>(c);

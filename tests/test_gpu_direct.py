@@ -142,3 +142,25 @@ def test_multiple_eigenvalues(n, mid, big):
 def test_weakly_coupled_blocks_that_share_eigenvalues(n, link):
     check(workloads.decoupled_pairs(np.random.default_rng(9320 + n), 48, n, link),
           f"linked {link} n={n}")
+
+
+@pytest.mark.parametrize("n", [8, 16, 24, 32, 48, 64, 96, 128])
+def test_eigenvalues_alone_of_null_and_repeated_blocks(n):
+    """Small determinants: null blocks of half, three quarters and all of the matrix
+    but one row, low rank, and exact copies of small blocks; ascending."""
+    rng = np.random.default_rng(9330 + n)
+    mats = []
+    for m in (n // 2, n // 4, 1):
+        A = np.zeros((n, n))
+        A[:m, :m] = workloads.gaussian_sym(rng, 1, m)[0]
+        mats.append(A)
+        X = rng.standard_normal((m, n))
+        mats.append(X.T @ X)
+    for k in (2, 4, 8):
+        L = 2.0 * np.eye(k) - np.eye(k, k=1) - np.eye(k, k=-1)
+        mats += [np.kron(L, np.eye(n // k)), np.kron(np.eye(n // k), L)]
+    A = np.stack(mats).astype(np.float32)
+    vals = bed.syevals(torch.from_numpy(A).cuda()).cpu().numpy()
+    ref = np.linalg.eigvalsh(A.astype(np.float64))
+    assert np.isfinite(vals).all() and (np.diff(vals, axis=1) >= 0).all()
+    assert (np.abs(vals - ref).max(axis=1) <= 1e-5 * np.abs(ref).max(axis=1)).all()
