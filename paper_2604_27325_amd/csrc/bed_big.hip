@@ -561,9 +561,6 @@ k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ 
     if (!Q) return;
     constexpr int HC = BN / 2, LPR = BT / HC, SG = BN / LPR;
     const int j = t / LPR, i0 = (t % LPR) * SG;
-    // the factors' two waves: the second team of a CU (its first 256 workgroups are
-    // dealt out one to a CU) takes the two SIMDs that the first one leaves idle
-    const int tf = t ^ ((bi >> 8 & 1) * 128);
     float z0[SG], z[SG] = {};  // the first and the second half's entries
 #pragma unroll 1
     for (int h = 0; h < 2; ++h) {
@@ -572,7 +569,7 @@ k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ 
         // a serial chain: ahead of the other team's matrix products (25 us behind
         // them, 10 so)
         __builtin_amdgcn_s_setprio(3);
-        direct_factors<BN, BT, HC, BT / BN, LD>(D, L[0], L[1], n, tf, HC * h);
+        direct_factors<BN, BT, HC, BT / BN, LD>(D, L[0], L[1], n, t, HC * h);
         __builtin_amdgcn_s_setprio(0);
         __syncthreads();
         // opaque: rows and bounds are formed here, not kept through the factors
