@@ -159,14 +159,29 @@ struct DirectArrays {
     int ok;
 };
 
+// Its factors: of the default teams for n <= 32 in binary64, one set of them beside its
+// other arrays, the other in Q1 and M; else in binary32 in Q0 and Q1.
+template <typename T, int NMAX, int NT> struct DirectWide {
+    static constexpr bool value = sizeof(T) == 4 && (NMAX == 16 || (NMAX == 32 && NT == 256));
+};
+template <int NMAX, bool WIDE> struct DirectFactors {
+    double l[NMAX * (NMAX + 1)];
+};
+template <int NMAX> struct DirectFactors<NMAX, false> {};
+
 template <typename T, int NMAX, int NT>
 struct Smem {
     static constexpr int LD = NMAX + 1;  // odd row stride: column walks hit distinct banks
     static constexpr int NW = NT / 64;
     static constexpr int G = NT / NMAX;
     T Q0[NMAX * LD];  // eigenvector blocks (ping)
-    T Q1[NMAX * LD];  // eigenvector blocks (pong)
-    T M[NMAX * LD];   // load staging, merge matrix, output staging
+    union {
+        struct {
+            T Q1[NMAX * LD];  // eigenvector blocks (pong)
+            T M[NMAX * LD];   // load staging, merge matrix, output staging
+        };
+        DirectFactors<NMAX, DirectWide<T, NMAX, NT>::value> fm;
+    };
     // reflector k in row k: Vt[k*VLD + r] = v_k[r].  Compact WY: the odd row
     // stride keeps the MFMA operand reads (16 reflectors x 4 rows per
     // instruction) on distinct banks.  Explicit Q_H: 16-byte aligned rows for
@@ -190,7 +205,10 @@ struct Smem {
         MergeArrays<T, NMAX> m;
         struct {  // direct solver
             DirectArrays<NMAX> t;
-            DirectGrid<NT> g;
+            union {
+                DirectGrid<NT> g;  // during the first grid
+                DirectFactors<NMAX, DirectWide<T, NMAX, NT>::value> f;
+            };
         } d;
         struct {  // back-transform: per block of 16 reflectors, Gram matrix and T factor
             // 16 x 16 tiles with row stride 17 (bank-conflict free column reads)
@@ -1766,56 +1784,59 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
 // toward the next row, rounded to binary32 (a relative perturbation of the
 // vector's entries).  A zero pivot becomes 1e-25, far below the rounding of T.
 //
-// The lanes of an eigenvalue meet in the middle, and each forms on its second
-// half gamma_i = D_i - b l', its own pivot in binary64 and the other one's l' of
+// F = float: the lanes of an eigenvalue meet in the middle, and each forms on its
+// second half gamma_i = D_i - b l', its own pivot in binary64 and the other one's l' of
 // the row ahead: as two binary32 parts, the low one kept where the lane itself
 // will write that row.  The twist has to come from there: gamma from the rounded
 // factors is known to about 5e-8 of T, and where T comes apart (a vanishing
 // coupling, which no product of factors crosses) such noise chose between the
 // parts' rows for eigenvalues that the parts share to less than that.  The row of
 // smallest |gamma_i| + 2^-46 |D_i| (2^-46: the parts' rounding) goes to D.twist,
-// one entry per lane.  (Batch 512, a solve with gamma of the rounded factors, formed
-// in direct_vector, and so: n = 32 32.4 and 33.0 us, n = 64 72.8 and 74.2, n = 128
-// 314.8 and 313.2.)
-template <int NMAX, int NT, int NC, int LPR, int LD>
-__device__ __forceinline__ void direct_factors(DirectArrays<NMAX>& D, float* Lp, float* Lm,
-                                               const int n, const int t, const int c0)
+// one entry per lane.  F = double keeps the factors in full, where LDS has room, and
+// leaves gamma to direct_vector, whose lanes share the rows.  (Batch 64, us, gamma of
+// rounded factors / in halves / in full: n = 16 17.2, 18.0, 17.5, n = 32 25.8, 26.5,
+// 26.3; batch 512: n = 64 72.3, 72.9, n = 128 314.8, 313.2, no room for the full ones.)
+template <int NMAX, int NT, int NC, int LPR, int LD, typename F>
+__device__ __forceinline__ void direct_factors(DirectArrays<NMAX>& D, F* Lp, F* Lm, const int n,
+                                               const int t, const int c0)
 {
+    constexpr bool WIDE = sizeof(F) == 8;
     const int j = t % NC, e = c0 + j;
     const bool up = t / NC != 0;
     const bool act = t < 2 * NC && e < n;
     const double x = D.lam[act ? e : 0];
     const double* ar = &D.ab[up ? 1 : 0][up ? direct_order<LPR>(n) - n : 0][0];
     const double* bk = &D.b[up ? 1 : 0][0];
-    if (act && up && n < NMAX) Lm[n * LD + j] = 0.f;  // below the last row (its coupling is zero)
+    if (act && up && n < NMAX) Lm[n * LD + j] = F(0);  // below the last row (its coupling is zero)
     const int dL = up ? -LD : LD, first = up ? (n - 1) * LD + j : j;
-    float* L = (up ? Lm : Lp) + first;  // this lane's factors, at row k
-    float* O = (up ? Lp : Lm) + first;  // the other lane's
-    const int h = up ? n - n / 2 : n / 2;
+    F* L = (up ? Lm : Lp) + first;  // this lane's factors, at row k
+    F* O = (up ? Lp : Lm) + first;  // the other lane's
+    const int h = WIDE ? n : (up ? n - n / 2 : n / 2);
     double bp = 0.0, l = 0.0;
     auto pivot = [&](const int k) { return fma(-bp, l, ar[2 * k] - x); };
-    auto next = [&](double d, const double bn, float* at) {
+    auto next = [&](double d, const double bn, F* at) {
         d = f_abs(d) < 1e-25 ? 1e-25 : d;
         // b / d: one third-order step from the hardware's estimate
         const double r = __builtin_amdgcn_rcp(d), br = bn * r, er = fma(-d, r, 1.0);
         l = fma(br, fma(er, er, er), br);
         bp = bn;
-        *at = float(l);
+        *at = F(l);
     };
     if (act) {
 #pragma unroll 4
         for (int k = 0; k < h; ++k) {
             next(pivot(k), bk[k], L);
-            *O = float(l - double(*L));
+            if constexpr (!WIDE) *O = F(l - double(*L));
             L += dL;
             O += dL;
         }
     }
+    if constexpr (WIDE) return;
     if constexpr (2 * NC > 64) team_sync<NT>();  // the two lanes sit in different waves
     else wave_sync();
     if (act) {
         uint32_t best = ~0u;
-        float oh = 0.f, ol = 0.f;  // the other lane's factor of the row ahead
+        F oh = F(0), ol = F(0);  // the other lane's factor of the row ahead
         auto ahead = [&] {
             oh = O[dL];
             ol = L[dL];
@@ -1847,12 +1868,11 @@ __device__ __forceinline__ void direct_factors(DirectArrays<NMAX>& D, float* Lp,
 // outward; rows of a group's lane are consecutive, its products are finished by
 // a scan over the group.  act: lanes that hold an eigenvalue (the others compute
 // on a valid column).  Rows past n hold anything; the products stop at n.
-template <int NMAX, int LPR, int LD>
-__device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const float* Lp,
-                                              const float* Lm, const int e, const bool act,
-                                              const int n, const int t, float (&out)[NMAX / LPR])
+template <int NMAX, int LPR, int LD, typename T>
+__device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const T* Lp, const T* Lm,
+                                              const int e, const bool act, const int n, const int t,
+                                              float (&out)[NMAX / LPR])
 {
-    using T = float;
     constexpr int SG = NMAX / LPR;
     const int lane = t & 63, sub = t % LPR;
     const int i0 = sub * SG;
@@ -1862,7 +1882,31 @@ __device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const
         lp[s] = Lp[(i0 + s) * LD];
         lm[s] = Lm[(i0 + s) * LD];
     }
-    int r = min(D.twist[0][e], D.twist[1][e]) & 127u;
+    int r;
+    if constexpr (sizeof(T) == 8) {
+        const double x = D.lam[e];
+        const int ia = max(i0 - 1, 0);
+        double lprev = Lp[ia * LD], bprev = i0 > 0 ? D.b[0][ia] : 0.0;  // of the row before
+        const double lafter = Lm[min(i0 + SG, NMAX - 1) * LD];
+        int best = 0x7fffffff;
+#pragma unroll
+        for (int s = 0; s < SG; ++s) {
+            const int i = i0 + s;
+            const double bn = D.b[0][i];  // zero at the last row
+            const double below = bn * (s + 1 < SG ? lm[s + 1 < SG ? s + 1 : 0] : lafter);
+            const double gam = fma(-bprev, lprev, D.ab[0][i][0] - x - below);
+            const int key = (__float_as_int(float(fma(0x1p-46, f_abs(below), f_abs(gam)))) & ~127) | i;
+            best = i < n ? min(best, key) : best;
+            lprev = lp[s];
+            bprev = bn;
+        }
+        best = min(best, xmove<1>(best, lane));
+        best = min(best, xmove<2>(best, lane));
+        if constexpr (LPR == 8) best = min(best, xmove<4>(best, lane));
+        r = best & 127;
+    } else {
+        r = min(D.twist[0][e], D.twist[1][e]) & 127u;
+    }
     double z[SG];
     double n2 = 0.0;
     // second pass: from the largest entry, where the first twist row was
@@ -1922,7 +1966,7 @@ __device__ __forceinline__ void direct_vector(const DirectArrays<NMAX>& D, const
     }
     const double sc = d_rsqrt_nr(n2);
 #pragma unroll
-    for (int s = 0; s < SG; ++s) out[s] = T(z[s] * sc);
+    for (int s = 0; s < SG; ++s) out[s] = float(z[s] * sc);
 }
 
 // One wave: Gram-Schmidt along each run of close eigenvalues, in order; at(i, j)
@@ -1988,7 +2032,12 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
     DirectArrays<NMAX>& D = S.u.d.t;
     if (!direct_eigenvalues<NMAX, NT>(D, S.u.d.g, n, t, want_q, Lc)) return false;
     if (!want_q) return true;
-    direct_factors<NMAX, NT, NMAX, LPR, LD>(D, S.Q0, S.Q1, n, t, 0);
+    constexpr bool WIDE = DirectWide<T, NMAX, NT>::value;
+    auto factors = [&](const int q) {
+        if constexpr (WIDE) return q ? S.fm.l : S.u.d.f.l;
+        else return q ? S.Q1 : S.Q0;
+    };
+    direct_factors<NMAX, NT, NMAX, LPR, LD>(D, factors(0), factors(1), n, t, 0);
     team_sync<NT>();
     BED_PHASE(6);
     {
@@ -1997,7 +2046,7 @@ __device__ __forceinline__ bool direct_solve(Smem<T, NMAX, NT>& S, const int n, 
         const bool act = j < n;
         const int e = act ? j : 0;
         float z[SG];
-        direct_vector<NMAX, LPR, LD>(D, S.Q0 + e, S.Q1 + e, e, act, n, t, z);
+        direct_vector<NMAX, LPR, LD>(D, factors(0) + e, factors(1) + e, e, act, n, t, z);
         wave_sync();
         if (act) {
 #pragma unroll
