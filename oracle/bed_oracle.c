@@ -75,6 +75,11 @@ int orc_tridiag(int n, const double *A, double *a, double *b, double *V, double 
     for (int i = 0; i < n; ++i)
         for (int j = 0; j < n; ++j) W[i * n + j] = (j <= i) ? A[i * n + j] : A[j * n + i];
     memset(V, 0, sizeof(double) * (size_t)n * n);
+    /* A sub-column this far below the matrix is rounding of rounding (a null block);
+     * its squares would underflow and its reflector not be orthogonal. */
+    double amax = 0.0;
+    for (int i = 0; i < n * n; ++i) amax = fmax(amax, fabs(W[i]));
+    const double none = (1e-50 * amax) * (1e-50 * amax);
 
     for (int k = 0; k + 2 < n; ++k) {
         a[k] = W[k * n + k];
@@ -82,7 +87,7 @@ int orc_tridiag(int n, const double *A, double *a, double *b, double *V, double 
         double sig = 0.0; /* ||x(2:end)||^2 */
         for (int i = k + 2; i < n; ++i) sig += W[i * n + k] * W[i * n + k];
         V[(k + 1) * n + k] = 1.0;
-        if (sig == 0.0) {
+        if (sig <= none) {
             tau[k] = 0.0;
             b[k] = x0;
             continue;

@@ -438,3 +438,18 @@ def test_backward_eigenvalue_only_and_guard():
     lam_d = np.full(n, 1.5)
     dA = oracle.syevd_backward(lam_d, Q, dlam, rng.standard_normal((n, n)))
     np.testing.assert_allclose(dA, (Q * dlam) @ Q.T, atol=1e-14)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e100])
+def test_null_blocks(scale):
+    """All-ones and sparse matrices: the reduction leaves rounding's rounding in the
+    null block, down to where its squares underflow."""
+    rng = np.random.default_rng(95)
+    for n in (16, 31, 32, 33, 40, 64, 97, 128):
+        W = np.triu(rng.uniform(size=(n, n)) < 1.0 / n, 1).astype(float)
+        for A in (np.ones((n, n)), np.diag((W + W.T).sum(axis=1)) - W - W.T):
+            lam, Q, _ = oracle.syevd(A * scale)
+            ref = np.linalg.eigvalsh(A)
+            assert np.abs(lam / scale - ref).max() <= 1e-13 * n * np.abs(ref).max()
+            assert np.linalg.norm(Q.T @ Q - np.eye(n)) <= 1e-14 * n
+            assert np.linalg.norm(A @ Q - Q * (lam / scale)) <= 1e-14 * n * np.linalg.norm(A)
