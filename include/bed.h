@@ -103,7 +103,9 @@ typedef struct bed_tune {
 typedef struct bed_plan bed_plan;
 
 /* One-shot solve: lambda, Q (and info) for a packed batch.  batch == 0 is a
- * no-op.  A uniform batch is one launch with no descriptor.  Mixed sizes (or
+ * no-op.  A uniform batch is one launch with no descriptor (of order n <= 4, on
+ * a kernel of its own, whose results agree with those of the same matrices in a
+ * mixed batch to rounding, not bit for bit).  Mixed sizes (or
  * a stored persistent schedule) use a plan from an internal cache keyed by
  * (dtype, n[], stream); the first call for a new key allocates its descriptor
  * (refused under capture, BED_ERR_CAPTURE).  A uniform binary32 batch of

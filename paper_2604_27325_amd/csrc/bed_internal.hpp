@@ -49,7 +49,12 @@ hipError_t launch_uniform(bed_dtype dt, TeamShape ts, const void *A, int n, int6
                           void *lam, void *Q, int32_t *info, hipStream_t s);
 
 // Uniform batch of order n <= SMALL_MAX: one lane per matrix (launch_uniform's
-// choice where no cutoff of the divide step is asked for).
+// choice where no cutoff of the divide step is asked for).  Up to 4 it is the faster
+// one at every batch (n = 4, binary32: 7.7 us at batch 1, 9.8 at 65536, where teams of 64
+// threads took 214).  From 5 on that depends on the batch: one lane's chain is longer
+// than a team's (n = 5, 6, 8 at batch 1: 12.2, 18.7, 38 us, teams 10.6, 10.8, 11.5),
+// thousands of matrices still gain by it (batch 65536: 17, 28, 57 us, teams 244, 265,
+// 304); no such rule is built.
 constexpr int SMALL_MAX = 4;
 hipError_t launch_small(bed_dtype dt, const void *A, int n, int64_t batch, void *lam, void *Q,
                         int32_t *info, hipStream_t s);

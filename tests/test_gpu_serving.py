@@ -158,3 +158,37 @@ def test_latency_and_throughput_reported():
     print(f"[serving] {mats / el:.0f} matrices/s p50 {np.percentile(lats, 50):.0f} us "
           f"p99 {np.percentile(lats, 99):.0f} us", flush=True)
     assert np.all(lats > 0)
+
+
+def test_requests_from_two_threads():
+    """Two threads submit from streams of their own while the scheduler launches: every
+    request's result is that of a solo solve."""
+    import threading
+    reqs = make_requests(80, seed=8000)
+    solo = [bed.syevd(A) for A in reqs]
+    torch.cuda.synchronize()
+    srv = bed.Server(streams=3, max_step=64)
+    outs = [(torch.empty(A.shape[0], A.shape[1], device=DEV), torch.empty_like(A)) for A in reqs]
+    tickets, errors = [None] * len(reqs), []
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    torch.cuda.synchronize()
+
+    def submit(k):
+        try:
+            for i in range(k, len(reqs), 2):
+                tickets[i] = srv.submit(reqs[i], *outs[i], stream=streams[k])
+        except Exception as e:  # reported by the main thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=submit, args=(k,)) for k in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert not errors and None not in tickets
+    srv.drain()
+    assert len(set(tickets)) == len(reqs)
+    for tk, (lam, Q), (lam_s, Q_s) in zip(tickets, outs, solo):
+        assert srv.poll(tk)[0]
+        assert torch.equal(lam, lam_s) and torch.equal(Q, Q_s)
+    srv.close()
