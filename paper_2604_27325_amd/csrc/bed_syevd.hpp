@@ -157,6 +157,7 @@ struct DirectArrays {
     uint32_t twist[2][NMAX];  // per half of the rows: float bits of gamma (upper 25), row
     uint64_t close[(NMAX + 63) / 64];  // bit j: eigenvalues j and j + 1 are close
     int ok;
+    int single;  // eigenvalues that the first grid shows apart from the others
 };
 
 // Its factors: of the default teams for n <= 32 in binary64, one set of them beside its
@@ -1433,10 +1434,12 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
 // determinants leave the exponent range, goes through the divide step, which does not
 // depend on gaps.  (DIRECT_GAP: at 4e-12 the two vectors of a pair are still a few
 // hundredths from orthogonal at most before they are made so; an eigenvalue repeated
-// exactly in a dense binary32 matrix is 1e-9 apart in most and 1e-10 in some.)
+// exactly in a dense binary32 matrix is 1e-9 apart in most and 1e-10 in some.
+// DIRECT_MOST: 64 eigenvalues over four decades leave six close pairs now and then;
+// the solve then takes 83 us, with the divide step after all rounds it took 118.)
 // Distances are of the Gershgorin interval's scale (|T| in [1/2, 1)).
 constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 4e-12;
-constexpr int DIRECT_MOST = 4;
+constexpr int DIRECT_MOST = 8;
 constexpr int DIRECT_CAP = 64;       // rounds per eigenvalue
 constexpr int DIRECT_LOOK = 6;       // rounds that separated spectra do with
 // With vectors, a matrix that will be refused is to be known early: the divide step
@@ -1536,6 +1539,7 @@ __device__ __forceinline__ void direct_setup(DirectArrays<NMAX>& D, const double
         D.lo = -double(nlo) * sc - 1e-6;
         D.hi = double(hi) * sc + 1e-6;
         D.unscale = double(fexp<float>::pow2(-sh));
+        D.single = 0;
         D.ok = (n >= 2 && ex > fexp<float>::BIAS - 64 && !several) ? 1 : 0;
     }
 }
@@ -1679,16 +1683,15 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
                 F[q] = G.f[k0 + q];
             }
         }
-        // A wave none of whose (at least eight) eigenvalues is alone in its cell (a
-        // quarter of the mean spacing wide) and none in a crowd: multiple eigenvalues.
-        // (Graded spectra have the crowd at one end and lone ones at the other.)
+        // Hardly an eigenvalue alone in its cell (a quarter of the mean spacing wide) or in
+        // a crowd: they are multiple ones.  (Graded spectra have a crowd at one end and
+        // lone ones at the other.)
         if (want_q) {
-            if (__popcll(__ballot(act)) >= 8 * LPR &&
-                !__ballot(act && (chi - clo == 1 || 4 * (chi - clo) > n)))
-                bad = true;
-            if (__ballot(bad)) D.ok = 0;
+            const int own = __popcll(__ballot(act && (chi - clo == 1 || 4 * (chi - clo) > n))) / LPR;
+            if (lane == 0 && own > 0) atomicAdd(&D.single, own);
+            if (__ballot(bad) && lane == 0) D.ok = 0;
             team_sync<NT>();
-            if (!D.ok) return false;
+            if (!D.ok || 8 * D.single <= n) return false;
         }
         const int pt = sub & 3;
         const double spread = pt == 0 ? -8.0 : (pt == 1 ? -1.0 : (pt == 2 ? 1.0 : 8.0));

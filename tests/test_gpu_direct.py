@@ -164,3 +164,21 @@ def test_eigenvalues_alone_of_null_and_repeated_blocks(n):
     ref = np.linalg.eigvalsh(A.astype(np.float64))
     assert np.isfinite(vals).all() and (np.diff(vals, axis=1) >= 0).all()
     assert (np.abs(vals - ref).max(axis=1) <= 1e-5 * np.abs(ref).max(axis=1)).all()
+
+
+@pytest.mark.parametrize("n", [16, 24, 32, 48, 64])
+def test_graded_spectra_and_many_close_pairs(n):
+    """Eigenvalues over four decades (crowded at one end of the first grid), and two to
+    nine close pairs or runs."""
+    rng = np.random.default_rng(9340 + n)
+    mats = []
+    for t in range(24):
+        w = np.sort(10.0 ** rng.uniform(-4.0, 0.0, n))
+        k = min(2 + t // 3, n // 2)
+        if t % 3 == 1:
+            w[1:2 * k:2] = w[:2 * k:2] * (1.0 + 1e-7)
+        elif t % 3 == 2:
+            w[n - k:] = 1.0 + 1e-8 * np.arange(k)
+        V, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        mats.append((V * w) @ V.T)
+    check(np.stack(mats), f"graded n={n}")
