@@ -510,11 +510,13 @@ struct DirSmem {
 // The spectrum of T directly, as for n <= 64 (direct_solve), and the back-transform;
 // a matrix that it does not take is torn at s = floor(n/2) (Eq. (3)) for
 // the children and the top merge.  The eigenvectors are formed in two halves of
-// 64 columns, whose factors leave room (75 KB) for two teams per CU: one team's
+// 64 columns, whose factors leave room (76 KB) for two teams per CU: one team's
 // serial factorizations run beside the other's matrix products and sections.
-// Batch 512, n = 128: 140 us for the 241 that forming Q_H, the children and the top
-// merge took; 38 without eigenvectors, for 186.  The binary64 pipe bounds it: the sections
-// (about 35 us) and the back-transform's matrix products (40) both fill it.
+// Batch 512, n = 128: 138 us for the 241 that forming Q_H, the children and the top
+// merge took; 38 without eigenvectors, for 186.  No unit is full: counted with 10%
+// planted pairs (159 us), each SIMD issues vector instructions for 64 us (a third of
+// them binary64) and its matrix core is busy for 36; the waves wait for half of their
+// cycles, in the sections' and the factors' dependent chains.
 __global__ void __launch_bounds__(BT, 4)  // two teams per CU
 k_big_direct(int n, int64_t batch, float *__restrict__ lam, float *__restrict__ Q,
              int32_t *__restrict__ info, Ws ws)

@@ -1435,13 +1435,14 @@ __device__ __forceinline__ int householder(Smem<T, NMAX, NT>& S, const int n, co
 // depend on gaps.  (DIRECT_GAP: at 4e-12 the two vectors of a pair are still a few
 // hundredths from orthogonal at most before they are made so; an eigenvalue repeated
 // exactly in a dense binary32 matrix is 1e-9 apart in most and 1e-10 in some.
-// DIRECT_MOST: 64 eigenvalues over four decades leave six close pairs now and then;
-// the solve then takes 83 us, with the divide step after all rounds it took 118.)
+// DIRECT_MOST: 64 eigenvalues over four decades leave six close pairs now and then,
+// beside one that is 6400 times as large ten; with them n = 64 takes 83 and 93 us, by
+// the divide step after all rounds 118 and 142.)
 // Distances are of the Gershgorin interval's scale (|T| in [1/2, 1)).
 constexpr double DIRECT_CLOSE = 1e-6, DIRECT_GAP = 4e-12;
-constexpr int DIRECT_MOST = 8;
+constexpr int DIRECT_MOST = 16;
 constexpr int DIRECT_CAP = 64;       // rounds per eigenvalue
-constexpr int DIRECT_LOOK = 6;       // rounds that separated spectra do with
+constexpr int DIRECT_LOOK = 5;       // rounds that separated spectra do with
 // With vectors, a matrix that will be refused is to be known early: the divide step
 // alone takes as long as it took without a direct solver, so the rounds ahead of it
 // were lost.  Three looks (us a solve at n = 32 and 64, batch 512, without and with it):
@@ -1650,6 +1651,7 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
         double X[4] = {0.0, 0.0, 0.0, 0.0}, F[4] = {0.0, 0.0, 0.0, 0.0};
         bool have = false;    // X, F hold four points
         bool strict = false;  // they enclose this eigenvalue and no other
+        int near = 0;         // eigenvalues that the first four enclose
         {
             int c;
             bool tiny;
@@ -1676,6 +1678,7 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
             {
                 const int ca = G.c[k0], cb = G.c[k0 + 3];
                 strict = ca == j && cb == j + 1;
+                near = cb - ca;
             }
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
@@ -1683,15 +1686,16 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
                 F[q] = G.f[k0 + q];
             }
         }
-        // Hardly an eigenvalue alone in its cell (a quarter of the mean spacing wide) or in
-        // a crowd: they are multiple ones.  (Graded spectra have a crowd at one end and
-        // lone ones at the other.)
+        // Most eigenvalues in cells (a quarter of the mean spacing wide) with others, the
+        // cells beside them empty: they are multiple ones.  Graded and clustered spectra
+        // fill neighbouring cells, or crowd one.
         if (want_q) {
-            const int own = __popcll(__ballot(act && (chi - clo == 1 || 4 * (chi - clo) > n))) / LPR;
+            const int here = chi - clo;
+            const int own = __popcll(__ballot(act && (here == 1 || near != here || 4 * here > n))) / LPR;
             if (lane == 0 && own > 0) atomicAdd(&D.single, own);
             if (__ballot(bad) && lane == 0) D.ok = 0;
             team_sync<NT>();
-            if (!D.ok || 8 * D.single <= n) return false;
+            if (!D.ok || 4 * D.single <= n) return false;
         }
         const int pt = sub & 3;
         const double spread = pt == 0 ? -8.0 : (pt == 1 ? -1.0 : (pt == 2 ? 1.0 : 8.0));
@@ -1725,10 +1729,11 @@ __device__ __forceinline__ bool direct_eigenvalues(DirectArrays<NMAX>& D, Direct
             lam = done ? lam : est;
             done = done || stop;
             if (rounds >= (want_q ? DIRECT_LOOK : DIRECT_CAP)) {
-                // what the checks below would refuse: no use in finding it exactly
+                // what the checks below will most likely refuse (seven of the wave's 16, four
+                // of its 8 eigenvalues next to another): no use in finding it exactly
                 const bool pair = want_q && act && j + 1 < chi;  // the next one is in here too
                 bad = bad || (pair && w < DIRECT_GAP) || (rounds >= DIRECT_CAP && !done);
-                if (__ballot(bad) || __popcll(__ballot(pair && w < DIRECT_CLOSE)) > LPR * DIRECT_MOST)
+                if (__ballot(bad) || __popcll(__ballot(pair && w < 6.0 * DIRECT_CLOSE)) >= 28)
                     bad = done = true;
             }
             if (!__ballot(!done)) break;  // Eq. (22): converged lanes idle till here

@@ -182,3 +182,26 @@ def test_graded_spectra_and_many_close_pairs(n):
         V, _ = np.linalg.qr(rng.standard_normal((n, n)))
         mats.append((V * w) @ V.T)
     check(np.stack(mats), f"graded n={n}")
+
+
+@pytest.mark.parametrize("n", [16, 32, 33, 64])
+def test_clusters_and_runs_of_close_eigenvalues(n):
+    """Neighbouring cells of the first grid full (two clusters, a spike beside a narrow
+    bulk), pairs at random places, and runs of up to twenty close eigenvalues."""
+    rng = np.random.default_rng(9350 + n)
+    mats = []
+    for t in range(20):
+        h = n // 2
+        if t % 4 == 0:
+            w = np.concatenate([rng.uniform(0.0, 0.02, h), rng.uniform(1.0, 1.02, n - h)])
+        elif t % 4 == 1:
+            w = np.concatenate([rng.uniform(0.25, 2.25, n - 1), [10.0 ** (1 + t / 5)]])
+        elif t % 4 == 2:
+            w = np.repeat(rng.uniform(-1.0, 1.0, (n + 1) // 2), 2)[:n]
+        else:
+            w = rng.uniform(-1.0, 1.0, n)
+            k = min(t, n - 2)
+            w[:k] = w[0] + 1e-7 * np.arange(k)
+        V, _ = np.linalg.qr(rng.standard_normal((n, n)))
+        mats.append((V * w) @ V.T)
+    check(np.stack(mats), f"clusters n={n}")
