@@ -87,10 +87,11 @@ typedef enum {
  *   leaf          cutoff of the divide step (Sec. 2.2): nodes of at most leaf
  *                 elements (2, 4 or 8) are solved by cyclic Jacobi instead of
  *                 being split further; 0: binary32 spectra of at least four
- *                 threads per row are solved directly (sections and secants of
- *                 det(T - x I), twisted factorizations), the divide step taking
- *                 the matrices with nearly equal eigenvalues and binary64 (cutoff
- *                 8 for n > 32, else 4) */
+ *                 threads per row are solved directly (sections and inverse
+ *                 interpolation of det(T - x I), twisted factorizations), the
+ *                 divide step taking the matrices with nearly equal eigenvalues
+ *                 or that come apart, and binary64 (cutoff 8 for n > 32, else
+ *                 4) */
 typedef struct bed_tune {
     int32_t threads_big;
     int32_t threads_mid;

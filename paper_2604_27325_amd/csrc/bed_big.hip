@@ -512,7 +512,7 @@ struct DirSmem {
 // the children and the top merge.  The eigenvectors are formed in two halves of
 // 64 columns, whose factors leave room (76 KB) for two teams per CU: one team's
 // serial factorizations run beside the other's matrix products and sections.
-// Batch 512, n = 128: 138 us for the 241 that forming Q_H, the children and the top
+// Batch 512, n = 128: 140 us for the 241 that forming Q_H, the children and the top
 // merge took; 38 without eigenvectors, for 186.  No unit is full: counted with 10%
 // planted pairs (159 us), each SIMD issues vector instructions for 64 us (a third of
 // them binary64) and its matrix core is busy for 36; the waves wait for half of their
