@@ -94,3 +94,21 @@ def test_decoupled_blocks_that_share_eigenvalues(n):
 def test_weakly_coupled_blocks_that_share_eigenvalues(n, link):
     check(workloads.decoupled_pairs(np.random.default_rng(9610 + n), 24, n, link),
           f"linked {link} n={n}")
+
+
+@pytest.mark.parametrize("width", [2e-4, 2e-5])
+@pytest.mark.parametrize("n", [65, 80, 97, 128])
+def test_eigenvalues_alone_of_a_narrow_bulk(n, width):
+    """Beside one large eigenvalue: the determinant falls by up to 2300 bits over the
+    bulk.  Found directly, an eigenvalue is known to 2^-44 of the interval (here below
+    8 |A|), then rounded to binary32."""
+    rng = np.random.default_rng(9620 + n)
+    A = np.stack([rotated(rng, np.r_[rng.uniform(0.0, width, n - 1), s])
+                  for s in (1.0, -1.0, 40.0 * width, 1.0)]).astype(np.float32)
+    A = np.ascontiguousarray(np.tril(A) + np.swapaxes(np.tril(A, -1), 1, 2))
+    lam = bed.syevals(torch.from_numpy(A).cuda()).cpu().numpy().astype(np.float64)
+    ref = np.linalg.eigvalsh(A.astype(np.float64))
+    tol = 2.0 ** -24 * np.abs(ref) + 2.0 ** -41 * np.abs(ref).max(axis=1, keepdims=True)
+    print(f"n={n} {width}: worst {(np.abs(lam - ref) / tol).max():.3g} of the bound", flush=True)
+    assert (np.abs(lam - ref) <= tol).all()
+    assert (np.diff(lam) >= 0).all()
